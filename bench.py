@@ -35,6 +35,11 @@ def flop_per_env_step(w) -> int:
     return 2 * (o * h + (w.num_hidden - 1) * h * h + h * a) + 2 * (o * o + o * a)
 
 
+def columns_per_pass(kernel: str) -> int:
+    """Columns of a matrix-core rollout kernel that the environment copies fill: four on the 4x4 shapes, else sixteen."""
+    return 4 if "_quad_" in kernel else 16
+
+
 def update_bytes(w, ctx) -> int:
     """Algorithmic bytes of es_update: the noise matrix once, theta/m/v read and written, the weights."""
     elt = 2 if w.noise_dtype in (1, 5) else 4
@@ -306,10 +311,9 @@ def main() -> int:
                 "unit": "TFLOP/s", "frac": ach / peak, "traffic": None,
                 "flop_per_launch": flops, "avg_launch_ms": roll_ms}
     if "mfma" in ctx.rollout_kernel:
-        # the environment copies are the 16 columns of the matrix-core tile: with fewer episodes per individual only
-        # that share of every MFMA is algorithmic work, whatever the kernel does
-        # (the four-copy binary32 kernel uses the 4x4x1 shape: four columns per pass)
-        width = 4 if "copies4" in ctx.rollout_kernel else 16
+        # the environment copies are the columns of the matrix-core tile: with fewer episodes per individual only that share of
+        # every MFMA is algorithmic work, whatever the kernel does
+        width = columns_per_pass(ctx.rollout_kernel)
         passes = (ctx.episodes + width - 1) // width
         share = ctx.episodes / (width * passes)
         roofline["column_ceiling"] = share

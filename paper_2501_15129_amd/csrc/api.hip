@@ -134,7 +134,7 @@ int es_create(const es_config* cfg, es_ctx** out) {
   ctx->reg_variant = reg_variant_for(c);
   if (quad_fits(c, ctx->shp.E, cus)) {
     ctx->rollout_kind = ROLLOUT_QUAD;
-    ctx->kernel_name = quad_variant_name(c, ctx->shp.E);
+    ctx->kernel_name = quad_variant_name(c);
   } else if (ctx->reg_variant >= 0) {
     ctx->rollout_kind = ROLLOUT_WAVE_REG;
     ctx->kernel_name = reg_variant_name(ctx->reg_variant, c.dtype == 1, (uint32_t)m);
@@ -145,6 +145,7 @@ int es_create(const es_config* cfg, es_ctx** out) {
     ctx->rollout_kind = ROLLOUT_MFMA_REG;
     ctx->kernel_name = mfma_variant_name(ctx->mfma_variant);
     if (m != 2) ctx->kernel_name += ",depth" + std::to_string(m);
+    if (c.env_dtype == 1) ctx->kernel_name += ",env_f32";
   } else {
     ctx->rollout_kind = ROLLOUT_WAVE_LDS;
     ctx->kernel_name = c.dtype == 1 ? "rollout_wave_lds_bf16" : "rollout_wave_lds_f32";

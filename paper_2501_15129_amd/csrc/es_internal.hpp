@@ -105,7 +105,7 @@ int launch_rollout_quad(es_ctx* ctx, uint32_t gen, const float* theta, const voi
                         const float* A, const float* B, float* returns, int32_t* ep_len,
                         float* fitness, void* ws, hipStream_t st);
 bool quad_fits(const es_config& cfg, uint32_t copies, int cus);   // copies = episodes evaluated per individual
-std::string quad_variant_name(const es_config& cfg, uint32_t copies);
+std::string quad_variant_name(const es_config& cfg);
 bool mfma_f32_fits(const es_config& cfg);
 const char* mfma_f32_variant_name(const es_config& cfg);
 int launch_fitness(es_ctx* ctx, const float* returns, float* fitness, hipStream_t st);

@@ -29,9 +29,7 @@ std::string reg_variant_name(int v, bool bf16, uint32_t m) {
   v -= REG_EXACT;
   static const char* obs[] = {"16", "32", "64"}, *hid[] = {"16", "32", "64"}, *act[] = {"4", "8", "16"};
   std::string s = std::string(bf16 ? "rollout_wave_reg_bf16<obs<=" : "rollout_wave_reg_f32<obs<=") + obs[v / 9] + ",hid<=" + hid[(v / 3) % 3] + ",act<=" + act[v % 3] + ">";
-  // (callers know the other depths by the general kernel's class)
-  if (m != 2) s += ",depth" + std::to_string(m) + (bf16 ? ",class=wave_lds_bf16" : ",class=wave_lds_f32");
-  return s;
+  return m == 2 ? s : s + ",depth" + std::to_string(m);
 }
 
 template <int CJ, int NQ, int NAR>

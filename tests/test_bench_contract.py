@@ -2,6 +2,7 @@
 import json
 import subprocess
 import sys
+from dataclasses import replace
 from pathlib import Path
 
 import pytest
@@ -13,6 +14,17 @@ def test_more_than_one_gpu_is_refused_with_a_message():
     r = subprocess.run([sys.executable, str(ROOT / "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert r.returncode != 0
     assert "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_columns_per_pass_follow_the_kernel():
+    """The four-copy kernels have four columns whatever the number of copies, the padded ones sixteen."""
+    from bench import columns_per_pass
+    from paper_2501_15129_amd import EsContext
+    from paper_2501_15129_amd.workloads import Workload
+    base = Workload("paper-base", pop=128, envs=1, horizon=1000, obs=8, hid=256, act=2, dtype=0, noise_dtype=0, seed=5)
+    for kw, columns in ((dict(), 4), (dict(pop=64, episodes=16), 4), (dict(episodes=16), 16), (dict(episodes=8), 4), (dict(dtype=1, noise_dtype=1), 4),
+                        (dict(dtype=1, noise_dtype=1, episodes=16), 16), (dict(dtype=1, noise_dtype=1, envs=4, obs=244, act=17), 16)):
+        assert columns_per_pass(EsContext(replace(base, **kw)).rollout_kernel) == columns, kw
 
 
 @pytest.mark.gpu

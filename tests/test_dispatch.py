@@ -28,3 +28,25 @@ def test_env_dtype_counts_with_bf16_operands_only(kernel, obs, hid, act, envs, l
     """A binary32 context is binary32 throughout whatever env_dtype says, so the field must not move it to another kernel."""
     w = replace(F32, obs=obs, hid=hid, act=act, envs=envs, num_hidden=layers, pop=pop)
     assert kernel(replace(w, env_dtype=1)) == kernel(w)
+
+
+@pytest.mark.parametrize("kw,name", [
+    (dict(), "rollout_mfma_quad_f32<obs32,hid256,act16>"),
+    (dict(obs=16, envs=16, pop=16), "rollout_mfma_quad_f32<obs16,hid256,act16>"),
+    (dict(envs=16), "rollout_mfma_reg_f32<obs32,hid256,act16>"),
+    (dict(envs=16, hid=128), "rollout_mfma_quad_f32<obs32,hid128,act16>"),
+    (dict(hid=64, obs=17, act=6), "rollout_wave_reg_f32<17,64,6>"),
+    (dict(hid=64, obs=17, act=6, envs=16, pop=1000), "rollout_mfma_quad_f32<obs32,hid64,act16>"),
+    (dict(hid=64, obs=17, act=6, num_hidden=3), "rollout_wave_reg_f32<obs<=32,hid<=64,act<=8>,depth3"),
+    (dict(hid=24, num_hidden=5), "rollout_wave_lds_f32"),
+    (dict(obs=70, hid=100), "rollout_wave_lds_f32"),
+    (dict(dtype=1, noise_dtype=1, hid=48, num_hidden=1), "rollout_wave_reg_bf16<obs<=32,hid<=64,act<=8>,depth1"),
+    (dict(dtype=1, noise_dtype=1, hid=100, obs=70), "rollout_mfma_quad_bf16<obs128,hid128,act32>"),
+    (dict(dtype=1, noise_dtype=1, num_hidden=3), "rollout_mfma_quad_bf16<obs32,hid256,act16>,depth3"),
+    (dict(dtype=1, noise_dtype=1, envs=16, pop=512, num_hidden=3), "rollout_mfma_reg_bf16<obs32,hid256,act16>,depth3"),
+    (dict(dtype=1, noise_dtype=1, envs=4, obs=244, act=17), "rollout_mfma_reg_bf16<obs256,hid256,act32>"),
+    (dict(dtype=1, noise_dtype=1, env_dtype=1), "rollout_mfma_reg_bf16<obs32,hid256,act16>,env_f32"),
+    (dict(dtype=1, noise_dtype=1, obs=70, hid=40), "rollout_wave_lds_bf16"),
+], ids=lambda v: v if isinstance(v, str) else "")
+def test_the_name_is_that_of_the_kernel(kernel, kw, name):
+    assert kernel(replace(F32, **kw)) == name

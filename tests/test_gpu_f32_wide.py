@@ -1,6 +1,7 @@
-"""Binary32 policies at the paper's width (Sec. 5.1: hidden layers of 256 units) on the fp32 matrix-core
-kernel, against the CPU checker: shapes across its range (65..256 hidden units, obs <= 64, act <= 16), both
-activations, observation statistics, every noise mode, several passes of 16 copies, degenerate cases."""
+"""Binary32 policies at the paper's width (Sec. 5.1: hidden layers of 256 units), against the CPU checker: shapes across
+the range (65..256 hidden units, obs <= 64, act <= 16), both activations, observation statistics, every noise mode, several
+passes, degenerate cases.  Populations this small run in passes of four copies; the sixteen-column kernel, which takes over
+when the passes outnumber the compute units, has its own cases in test_gpu_sixteen_columns.py."""
 import math
 from dataclasses import replace
 
@@ -28,7 +29,7 @@ def _case(es, w, gen=1, obs_norm=None):
     a_mat, b_mat, theta = make_inputs(w)
     theta = (theta + np.random.default_rng(w.seed).standard_normal(theta.size) * 0.02).astype(np.float32)     # non-zero biases
     ctx = es.EsContext(w)
-    assert "mfma_reg_f32" in ctx.rollout_kernel, ctx.rollout_kernel
+    assert "quad_f32" in ctx.rollout_kernel, ctx.rollout_kernel
     keep = None
     if obs_norm is not None:
         keep = (dev(obs_norm[0]), dev(obs_norm[1]))
@@ -87,12 +88,14 @@ def test_rollout_f32_wide(es, w):
     _case(es, w)
 
 
-def test_four_copy_variant_is_chosen_up_to_eight_copies(es):
-    for envs, episodes, narrow in ((1, 1, True), (4, 2, True), (8, 1, True), (3, 3, False), (16, 1, False)):
-        ctx = es.EsContext(replace(BASE, envs=envs, episodes=episodes))
-        assert ("copies4" in ctx.rollout_kernel) == narrow, (envs, episodes, ctx.rollout_kernel)
+def test_four_copy_variant_is_chosen_up_to_eight_copies_or_one_pass_per_compute_unit(es):
+    for envs, episodes, pop, four in ((1, 1, 6, True), (4, 2, 6, True), (8, 1, 6, True), (3, 3, 6, True), (16, 1, 6, True), (16, 1, 64, True),
+                                      (8, 1, 1000, True), (3, 3, 86, False), (16, 1, 66, False), (16, 1, 1000, False)):
+        ctx = es.EsContext(replace(BASE, envs=envs, episodes=episodes, pop=pop))
+        assert ("quad_f32" in ctx.rollout_kernel) == four, (envs, episodes, pop, ctx.rollout_kernel)
+        assert ("mfma_reg_f32" in ctx.rollout_kernel) != four, (envs, episodes, pop, ctx.rollout_kernel)
     ctx = es.EsContext(replace(BASE, num_hidden=1))
-    assert "copies4" in ctx.rollout_kernel and "depth1" in ctx.rollout_kernel, ctx.rollout_kernel
+    assert "quad_f32" in ctx.rollout_kernel and "depth1" in ctx.rollout_kernel, ctx.rollout_kernel
 
 
 def test_rollout_f32_wide_with_observation_statistics(es):

@@ -40,7 +40,7 @@ RELU_CASES = [
     (Workload("relu-odd", pop=10, envs=5, horizon=60, obs=13, hid=29, act=7, dtype=0, noise_dtype=0, seed=22, hidden_act=1), "wave_reg"),
     (Workload("relu-wide", pop=4, envs=2, horizon=40, obs=70, hid=100, act=9, dtype=0, noise_dtype=0, seed=24, hidden_act=1), "wave_lds_f32"),
     (Workload("relu-odd-bf16", pop=10, envs=5, horizon=60, obs=13, hid=29, act=7, dtype=1, noise_dtype=1, seed=22, hidden_act=1), "wave_reg_bf16"),
-    (Workload("relu-wide-bf16", pop=4, envs=2, horizon=40, obs=70, hid=100, act=9, dtype=1, noise_dtype=1, seed=25, hidden_act=1), "wave_lds_bf16"),
+    (Workload("relu-wide-bf16", pop=4, envs=2, horizon=40, obs=70, hid=100, act=9, dtype=1, noise_dtype=1, seed=25, hidden_act=1), "quad_bf16"),
     (Workload("relu-linear-out", pop=6, envs=3, horizon=40, obs=13, hid=29, act=7, dtype=0, noise_dtype=0, seed=23, hidden_act=1, out_tanh=0), "wave_reg"),
     (replace(CONFIGS[0], name="relu-cfg0", hidden_act=1), "wave_reg"),
     (replace(CONFIGS[1], name="relu-cfg1-T150", hidden_act=1, horizon=150), "wave_reg"),
@@ -170,7 +170,7 @@ def test_rollout_other_depths(es, w):
     a_mat, b_mat, theta = make_inputs(w)
     theta = (theta + np.random.default_rng(w.seed).standard_normal(theta.size) * 0.02).astype(np.float32)   # non-zero biases
     ctx = es.EsContext(w)
-    assert ctx.param_count == w.n_params and "wave_lds" in ctx.rollout_kernel
+    assert ctx.param_count == w.n_params and ("wave_lds" if w.act > 16 else "wave_reg") in ctx.rollout_kernel
     eps = oracle.sample_population(ws, 2)
     noise = None if ctx.noise_regenerated else noise_to_device(ctx, eps)
     got = run_rollout(ctx, w, 2, theta, noise, a_mat, b_mat)

@@ -62,7 +62,7 @@ def _case(es, w, norm=False):
 def test_bf16_edges(es, obs, hid, act, envs, layers, kw):
     w = replace(B, name=f"quad-{obs}-{hid}x{layers}-{act}-E{envs}", obs=obs, hid=hid, act=act, envs=envs, num_hidden=layers, seed=401 + obs + hid)
     ctx = _case(es, replace(w, **kw))
-    assert "copies4" in ctx.rollout_kernel
+    assert "quad_bf16" in ctx.rollout_kernel
 
 
 @pytest.mark.parametrize("w", [B, replace(B, name="quad-norm-60-E1-relu", obs=60, envs=1, hidden_act=1), replace(B, name="quad-norm-mid-spread", obs=90, hid=100, act=12),
@@ -87,7 +87,7 @@ F = Workload("quadf", pop=4, envs=4, horizon=30, obs=27, hid=256, act=8, dtype=0
 def test_f32_edges(es, obs, hid, act, envs, layers, kw):
     w = replace(F, name=f"quadf-{obs}-{hid}x{layers}-{act}-E{envs}", obs=obs, hid=hid, act=act, envs=envs, num_hidden=layers, seed=501 + obs + hid)
     ctx = _case(es, replace(w, **kw))
-    assert "mfma_reg_f32" in ctx.rollout_kernel
+    assert "quad_f32" in ctx.rollout_kernel
 
 
 @pytest.mark.parametrize("w", [
@@ -96,7 +96,8 @@ def test_f32_edges(es, obs, hid, act, envs, layers, kw):
     replace(B, name="quadn-bf16-32-64", pop=1100, envs=8, horizon=12, obs=32, hid=64, act=16), replace(B, name="quadn-bf16-33-16", pop=900, envs=11, horizon=12, obs=33, hid=16, act=1)],
     ids=lambda w: w.name)
 def test_narrow_policies_in_numbers(es, w):
-    assert "hid64" in _case(es, w).rollout_kernel
+    name = _case(es, w).rollout_kernel
+    assert "quad" in name and "hid64" in name
     _case(es, w, norm=True)
 
 
