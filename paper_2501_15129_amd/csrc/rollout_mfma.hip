@@ -1123,8 +1123,10 @@ int mfma_variant_for(const es_config& c) {
   if (c.dtype != 1 || c.hid_dim > (uint32_t)NHP || m < 1 || m > 4) return -1;
   // a binary32 environment is built for the two narrow-observation shapes with two hidden layers
   if (c.env_dtype == 1 && (m != 2 || c.obs_dim > 64 || c.act_dim > 16)) return -1;
-  // narrow policies are served better by the one-wavefront-per-episode kernel when it fits
-  if (c.hid_dim < 128 && wave_rollout_lds_bytes(c) <= 160 * 1024) return -1;
+  // narrow policies of one or two layers are served better by the one-wavefront-per-episode kernel when it fits; three and four
+  // layers of 65 to 127 units never are (obs 27, 512 individuals x 16 copies x 40 steps, here against the LDS kernel: three layers
+  // of 65 / 96 / 127 units 0.28 / 0.23 / 0.30 against 5.3 / 13.3 / 25.2 ms, four layers 0.38 / 0.30 / 0.40 against 9.2 / 25.4 / 66.8 ms)
+  if (c.hid_dim < 128 && (m <= 2 || c.hid_dim <= 64) && wave_rollout_lds_bytes(c) <= 160 * 1024) return -1;
   for (int v = 0; v < 4; ++v)
     if ((int)c.obs_dim <= kVariants[v].max_obs && (int)c.act_dim <= kVariants[v].max_act)
       return (m != 2 && v > 1) ? -1 : v;      // one, three and four hidden layers: the two narrow-observation shapes only

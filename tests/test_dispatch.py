@@ -50,3 +50,11 @@ def test_env_dtype_counts_with_bf16_operands_only(kernel, obs, hid, act, envs, l
 ], ids=lambda v: v if isinstance(v, str) else "")
 def test_the_name_is_that_of_the_kernel(kernel, kw, name):
     assert kernel(replace(F32, **kw)) == name
+
+
+@pytest.mark.parametrize("layers", [3, 4])
+@pytest.mark.parametrize("hid", [65, 96, 127])
+@pytest.mark.parametrize("pop,envs", [(200, 5), (512, 16), (256, 20), (128, 4), (64, 16), (2, 21)])
+def test_three_and_four_middle_layers_stay_on_the_matrix_cores(kernel, layers, hid, pop, envs):
+    """bf16 policies of 65..127 units with three or four hidden layers: a matrix-core kernel holds them whatever the number of passes."""
+    assert "mfma" in kernel(replace(F32, dtype=1, noise_dtype=1, hid=hid, num_hidden=layers, pop=pop, envs=envs))
