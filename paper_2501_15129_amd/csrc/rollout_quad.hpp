@@ -24,7 +24,7 @@
 // (8.5 cycles per 4x4 instruction, measured) plus the vector work of the activations (5.8 cycles per instruction of a
 // lone wavefront).
 // Measured, whole rollout, T = 1000 unless noted: bf16 8-256-256-2, 128 individuals x 1 copy 1.23 ms (padded 16-column
-// kernel) -> 0.75 ms, x 4 copies 1.26 -> 0.97 ms; bf16 27-100-100-8, 128 x 5 copies, T = 400: 8.07 ms (LDS kernel) -> 0.33 ms.
+// kernel) -> 0.75 ms, x 4 copies 1.26 -> 0.97 ms; bf16 27-100-100-8, 128 x 5 copies, T = 400: 8.07 ms (LDS kernel) -> 0.36 ms.
 #pragma once
 
 #include <type_traits>
@@ -145,7 +145,9 @@ __device__ __forceinline__ void pin_agpr(f32x4& v) {
 
 // tanh(x + b) as 1 - 2 / (2^{c (x + b)} + 1) with cb = c b, c = 2 log2 e: the bias costs no instruction of its own
 constexpr float TANH_C = 2.88539008f;
+template <bool NEAR>
 __device__ __forceinline__ float tanh_b(float x, float cb) {
+  if (NEAR) return tanh_near(__fmaf_rn(x, TANH_C, cb));
   const float ex = __builtin_amdgcn_exp2f(__fmaf_rn(x, TANH_C, cb));
   return __fmaf_rn(-2.0f, __builtin_amdgcn_rcpf(ex + 1.0f), 1.0f);
 }
@@ -156,11 +158,12 @@ __device__ __forceinline__ float tanh_b(float x, float cb) {
 // wavefront holds the whole state; else the rows are spread, 64 NW >= 4 KG).  M: hidden layers.  NC: copies a pass serves
 // (4, or 1: the activations of the three idle copies and most of the transposes drop out).  RELU / NORM: hidden
 // activation, observation statistics (compile-time: a taken branch costs a single wavefront some sixty cycles).
-template <bool BF16_, int NW_, int KG_, int M_, int NC_, bool RELU_, bool NORM_>
+// NEAR: the tanh that is accurate near zero (bf16 policies of fewer than 128 units).
+template <bool BF16_, int NW_, int KG_, int M_, int NC_, bool RELU_, bool NORM_, bool NEAR_>
 struct QuadShape {
   using O = quad::Oper<BF16_>;
   using Elem = typename O::Elem;
-  static constexpr bool BF16 = BF16_, RELU = RELU_, NORM = NORM_;
+  static constexpr bool BF16 = BF16_, RELU = RELU_, NORM = NORM_, NEAR = NEAR_;
   static constexpr int NW = NW_, KG = KG_, M = M_, NC = NC_;
   static constexpr int NT = 64 * NW, HID = 64 * NW, HG = 16 * NW;        // threads, padded hidden width, its K groups
   static constexpr bool SPREAD = KG > 16;                                // state rows over the wavefronts
@@ -452,7 +455,7 @@ void rollout_quad_kernel(const QuadArgs a) {
 #pragma unroll
           for (int c = 0; c < NC; ++c) {
             const float z = v[0][c] + v[1][c];
-            h[c] = S::RELU ? fmaxf(z + b, 0.f) : tanh_b(z, b);
+            h[c] = S::RELU ? fmaxf(z + b, 0.f) : tanh_b<S::NEAR>(z, b);
           }
         };
         using I0 = std::integral_constant<int, 0>; using I1 = std::integral_constant<int, 1>; using I2 = std::integral_constant<int, 2>;
@@ -566,7 +569,7 @@ void rollout_quad_kernel(const QuadArgs a) {
           float sq = 0.0f;
 #pragma unroll
           for (int r = 0; r < RPL; ++r) {
-            const float z = av[r] + b3[r], tz = tanh_b(z, 0.0f);
+            const float z = av[r] + b3[r], tz = tanh_b<S::NEAR>(z, 0.0f);
             av[r] = squash ? tz : z;
             sq = r == 0 ? av[0] * av[0] : __fmaf_rn(av[r], av[r], sq);
           }
@@ -575,7 +578,7 @@ void rollout_quad_kernel(const QuadArgs a) {
         } else {
 #pragma unroll
           for (int c = 0; c < NC; ++c) {
-            const float z = av[c] + b3[0], tz = tanh_b(z, 0.0f);
+            const float z = av[c] + b3[0], tz = tanh_b<S::NEAR>(z, 0.0f);
             av[c] = squash ? tz : z;
             Rs[c] = __fmaf_rn(av[c] * av[c], ncost[c], Rs[c]);
           }
@@ -587,7 +590,7 @@ void rollout_quad_kernel(const QuadArgs a) {
           O::template mac<4, S::ROWS_COPY ? (RPL == 2 ? 2 * g : 4 * g) : g, g>(aop, Be[g], accE);
         });
 #pragma unroll
-        for (int c = 0; c < NC; ++c) s[c] = tanh_b(accE[0][c] + accE[1][c], 0.0f);       // padded rows: tanh(0) = 0
+        for (int c = 0; c < NC; ++c) s[c] = tanh_b<S::NEAR>(accE[0][c] + accE[1][c], 0.0f);       // padded rows: tanh(0) = 0
         // ---- termination: max |s| > threshold ends a copy after this step ----
         unsigned long long over[NC], any = 0ull;
 #pragma unroll
@@ -691,35 +694,37 @@ int launch_quad_shape(es_ctx* ctx, QuadArgs a, float* fitness, hipStream_t st) {
 }
 
 // Activation and observation statistics chosen at compile time; statistics only where WITH_NORM.
-template <bool BF16, int NW, int KG, int M, int NC, bool WITH_NORM>
+template <bool BF16, int NW, int KG, int M, int NC, bool WITH_NORM, bool NEAR>
 int launch_quad_options(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st) {
   const bool relu = ctx->cfg.hidden_act == 1;
   if constexpr (WITH_NORM) {
     if (a.obs_mean)
-      return relu ? launch_quad_shape<QuadShape<BF16, NW, KG, M, NC, true, true>>(ctx, a, fitness, st)
-                  : launch_quad_shape<QuadShape<BF16, NW, KG, M, NC, false, true>>(ctx, a, fitness, st);
+      return relu ? launch_quad_shape<QuadShape<BF16, NW, KG, M, NC, true, true, NEAR>>(ctx, a, fitness, st)
+                  : launch_quad_shape<QuadShape<BF16, NW, KG, M, NC, false, true, NEAR>>(ctx, a, fitness, st);
   }
-  return relu ? launch_quad_shape<QuadShape<BF16, NW, KG, M, NC, true, false>>(ctx, a, fitness, st)
-              : launch_quad_shape<QuadShape<BF16, NW, KG, M, NC, false, false>>(ctx, a, fitness, st);
+  return relu ? launch_quad_shape<QuadShape<BF16, NW, KG, M, NC, true, false, NEAR>>(ctx, a, fitness, st)
+              : launch_quad_shape<QuadShape<BF16, NW, KG, M, NC, false, false, NEAR>>(ctx, a, fitness, st);
 }
 // obs <= 64: the width class (in binary32, where a group of four costs four instructions twice a step, one more class;
 // observation statistics only in the widest) and the number of copies of a pass
-template <bool BF16, int NW, int KG, int M, bool WITH_NORM>
+template <bool BF16, int NW, int KG, int M, bool WITH_NORM, bool NEAR>
 int launch_quad_copies(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st) {
-  return a.E == 1 ? launch_quad_options<BF16, NW, KG, M, 1, WITH_NORM>(ctx, a, fitness, st) : launch_quad_options<BF16, NW, KG, M, 4, WITH_NORM>(ctx, a, fitness, st);
+  return a.E == 1 ? launch_quad_options<BF16, NW, KG, M, 1, WITH_NORM, NEAR>(ctx, a, fitness, st) : launch_quad_options<BF16, NW, KG, M, 4, WITH_NORM, NEAR>(ctx, a, fitness, st);
 }
-template <bool BF16, int NW, int M>
+template <bool BF16, int NW, int M, bool NEAR>
 int launch_quad_obs64(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st) {
   if constexpr (!BF16) {
-    if (a.no <= 16 && !a.obs_mean) return launch_quad_copies<BF16, NW, 4, M, false>(ctx, a, fitness, st);
+    if (a.no <= 16 && !a.obs_mean) return launch_quad_copies<BF16, NW, 4, M, false, NEAR>(ctx, a, fitness, st);
   }
-  if (a.no <= 32 && !a.obs_mean) return launch_quad_copies<BF16, NW, 8, M, false>(ctx, a, fitness, st);
-  return launch_quad_copies<BF16, NW, 16, M, true>(ctx, a, fitness, st);
+  if (a.no <= 32 && !a.obs_mean) return launch_quad_copies<BF16, NW, 8, M, false, NEAR>(ctx, a, fitness, st);
+  return launch_quad_copies<BF16, NW, 16, M, true, NEAR>(ctx, a, fitness, st);
 }
 
 // one source file each (compile time); M = hidden layers of the context
 int launch_quad_bf16_mid(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st);     // two wavefronts, one or two layers
 int launch_quad_bf16_wide(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st);    // four wavefronts, one or two layers
+int launch_quad_bf16_mid3(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st);    // four wavefronts, three layers, fewer than 128 units
+int launch_quad_bf16_mid4(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st);    // ... four layers
 int launch_quad_bf16_deep3(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st);   // four wavefronts, three layers
 int launch_quad_bf16_deep4(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st);   // ... four layers
 int launch_quad_f32_mid(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st);      // two wavefronts, one to three layers

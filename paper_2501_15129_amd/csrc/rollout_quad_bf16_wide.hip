@@ -4,7 +4,7 @@
 namespace es {
 
 int launch_quad_bf16_wide(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st) {
-  return ctx->shp.m == 1 ? launch_quad_obs64<true, 4, 1>(ctx, a, fitness, st) : launch_quad_obs64<true, 4, 2>(ctx, a, fitness, st);
+  return ctx->shp.m == 1 ? launch_quad_obs64<true, 4, 1, false>(ctx, a, fitness, st) : launch_quad_obs64<true, 4, 2, false>(ctx, a, fitness, st);
 }
 
 }  // namespace es

@@ -4,8 +4,8 @@
 namespace es {
 
 int launch_quad_f32_mid(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st) {
-  if (ctx->shp.m == 1) return launch_quad_obs64<false, 2, 1>(ctx, a, fitness, st);
-  return ctx->shp.m == 2 ? launch_quad_obs64<false, 2, 2>(ctx, a, fitness, st) : launch_quad_obs64<false, 2, 3>(ctx, a, fitness, st);
+  if (ctx->shp.m == 1) return launch_quad_obs64<false, 2, 1, false>(ctx, a, fitness, st);
+  return ctx->shp.m == 2 ? launch_quad_obs64<false, 2, 2, false>(ctx, a, fitness, st) : launch_quad_obs64<false, 2, 3, false>(ctx, a, fitness, st);
 }
 
 }  // namespace es

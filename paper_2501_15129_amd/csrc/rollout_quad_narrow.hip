@@ -6,9 +6,9 @@ namespace es {
 
 int launch_quad_narrow(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st) {
   if (ctx->cfg.dtype == 1)
-    return a.no <= 32 && !a.obs_mean ? launch_quad_options<true, 1, 8, 2, 4, false>(ctx, a, fitness, st) : launch_quad_options<true, 1, 16, 2, 4, true>(ctx, a, fitness, st);
-  if (a.no <= 16) return launch_quad_options<false, 1, 4, 2, 4, true>(ctx, a, fitness, st);
-  return a.no <= 32 ? launch_quad_options<false, 1, 8, 2, 4, true>(ctx, a, fitness, st) : launch_quad_options<false, 1, 16, 2, 4, true>(ctx, a, fitness, st);
+    return a.no <= 32 && !a.obs_mean ? launch_quad_options<true, 1, 8, 2, 4, false, false>(ctx, a, fitness, st) : launch_quad_options<true, 1, 16, 2, 4, true, false>(ctx, a, fitness, st);
+  if (a.no <= 16) return launch_quad_options<false, 1, 4, 2, 4, true, false>(ctx, a, fitness, st);
+  return a.no <= 32 ? launch_quad_options<false, 1, 8, 2, 4, true, false>(ctx, a, fitness, st) : launch_quad_options<false, 1, 16, 2, 4, true, false>(ctx, a, fitness, st);
 }
 
 }  // namespace es
