@@ -118,6 +118,15 @@ def gauss_pair(xa: int, xb: int):
     return float(z[0]), float(z[1])
 
 
+def gauss_pairs(xa: np.ndarray, xb: np.ndarray):
+    """``gauss_pair`` of every pair of words: two float32 arrays."""
+    xa, xb = (np.ascontiguousarray(x, dtype=np.uint32) for x in (xa, xb))
+    assert xa.shape == xb.shape
+    zc, zs = np.empty(xa.shape, np.float32), np.empty(xa.shape, np.float32)
+    lib().orc_gauss_pairs(_p(xa, C.c_uint32), _p(xb, C.c_uint32), C.c_uint64(xa.size), _p(zc, C.c_float), _p(zs, C.c_float))
+    return zc, zs
+
+
 def bf16_round(x):
     a = np.asarray(x, dtype=np.float32)
     out = np.empty_like(a)

@@ -167,6 +167,17 @@ void orc_gauss_pair(uint32_t xa, uint32_t xb, float z[2]) {
   z[1] = rad * sn;
 }
 
+/* The same for n pairs of words. */
+void orc_gauss_pairs(const uint32_t *xa, const uint32_t *xb, uint64_t n, float *zc, float *zs) {
+#pragma omp parallel for schedule(static)
+  for (uint64_t i = 0; i < n; ++i) {
+    float z[2];
+    orc_gauss_pair(xa[i], xb[i], z);
+    zc[i] = z[0];
+    zs[i] = z[1];
+  }
+}
+
 static uint32_t noise_rows(const orc_config *cfg) { return cfg->antithetic ? cfg->pop / 2 : cfg->pop; }
 
 static uint32_t hidden_layers(const orc_config *cfg) { return cfg->num_hidden ? cfg->num_hidden : 2u; }

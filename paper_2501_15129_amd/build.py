@@ -44,11 +44,12 @@ def build(verbose: bool = True) -> Path:
     tmp = LIB.with_suffix(f".tmp{os.getpid()}.so")
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", str(tmp), *map(str, objs)])
     os.replace(tmp, LIB)
-    # rate micro-benchmarks (bench.py --peaks): a library of their own, not part of the boundary
+    # rate micro-benchmarks (bench.py --peaks) and the Gaussian transform on given words: a library of their own, not part of the boundary
     tmp = MICRO_LIB.with_suffix(f".tmp{os.getpid()}.so")
+    micro = [CSRC / "microbench.o", _compile("gauss_words.hip")]      # (the transform is compiled with the product's flags)
     subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
-                           "-packed-fp32-ops", "-Wall", "-Wno-unused-command-line-argument", "-shared", "-o", str(tmp),
-                           str(CSRC / "microbench.hip")])
+                           "-packed-fp32-ops", "-Wall", "-Wno-unused-command-line-argument", "-c", str(CSRC / "microbench.hip"), "-o", str(micro[0])])
+    subprocess.check_call([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", str(tmp), *map(str, micro)])
     os.replace(tmp, MICRO_LIB)
     if verbose:
         print(f"built {LIB} and {MICRO_LIB}", file=sys.stderr)
