@@ -717,6 +717,13 @@ int launch_quad_obs64(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_
     if (a.no <= 16 && !a.obs_mean) return launch_quad_copies<BF16, NW, 4, M, false, NEAR>(ctx, a, fitness, st);
   }
   if (a.no <= 32 && !a.obs_mean) return launch_quad_copies<BF16, NW, 8, M, false, NEAR>(ctx, a, fitness, st);
+  if constexpr (BF16 && M == 4) {      // (wide observations of several copies: quad_fits)
+    if (a.E > 1u && !a.obs_mean) return fail(ctx, ES_EUNSUPPORTED, "es_rollout: no four-copy variant for four layers and more than 32 observations");
+    if (a.E > 1u)
+      return ctx->cfg.hidden_act == 1 ? launch_quad_shape<QuadShape<BF16, NW, 16, M, 4, true, true, NEAR>>(ctx, a, fitness, st)
+                                      : launch_quad_shape<QuadShape<BF16, NW, 16, M, 4, false, true, NEAR>>(ctx, a, fitness, st);
+    return launch_quad_options<BF16, NW, 16, M, 1, true, NEAR>(ctx, a, fitness, st);
+  }
   return launch_quad_copies<BF16, NW, 16, M, true, NEAR>(ctx, a, fitness, st);
 }
 

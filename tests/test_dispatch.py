@@ -58,3 +58,10 @@ def test_the_name_is_that_of_the_kernel(kernel, kw, name):
 def test_three_and_four_middle_layers_stay_on_the_matrix_cores(kernel, layers, hid, pop, envs):
     """bf16 policies of 65..127 units with three or four hidden layers: a matrix-core kernel holds them whatever the number of passes."""
     assert "mfma" in kernel(replace(F32, dtype=1, noise_dtype=1, hid=hid, num_hidden=layers, pop=pop, envs=envs))
+
+
+@pytest.mark.parametrize("hid", [100, 200, 256])
+@pytest.mark.parametrize("obs,envs,name", [(32, 4, "quad"), (33, 4, "reg"), (64, 16, "reg"), (33, 2, "reg"), (64, 1, "quad")])
+def test_four_layers_of_several_copies_and_wide_observations_run_in_sixteen_columns(kernel, hid, obs, envs, name):
+    """The four-copy kernel spills there; the 16-column kernel is 10 to 17 % faster."""
+    assert f"rollout_mfma_{name}_bf16" in kernel(replace(F32, dtype=1, noise_dtype=1, num_hidden=4, pop=32, hid=hid, obs=obs, envs=envs))

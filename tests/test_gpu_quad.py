@@ -55,7 +55,7 @@ def _case(es, w, norm=False):
     (1, 65, 1, 1, 2, {}), (32, 128, 16, 4, 2, {}), (33, 127, 16, 3, 1, {}), (64, 100, 15, 5, 2, dict(hidden_act=1)),
     (65, 128, 1, 4, 2, {}), (128, 66, 32, 2, 1, {}), (20, 128, 17, 7, 2, {}), (97, 99, 20, 16, 2, dict(done_thresh=math.inf)),
     (32, 129, 16, 1, 2, dict(hidden_act=1)), (33, 192, 3, 4, 2, {}), (64, 193, 16, 2, 1, {}), (8, 255, 5, 1, 1, dict(out_tanh=0)),
-    (32, 256, 1, 8, 2, {}), (27, 256, 8, 6, 3, {}), (64, 256, 16, 1, 3, dict(hidden_act=1)), (64, 256, 16, 4, 4, {}), (31, 200, 9, 1, 4, {}),
+    (32, 256, 1, 8, 2, {}), (27, 256, 8, 6, 3, {}), (64, 256, 16, 1, 3, dict(hidden_act=1)), (64, 256, 16, 1, 4, {}), (31, 200, 9, 1, 4, {}),
     (17, 256, 6, 3, 4, dict(noise_dtype=3)), (40, 256, 7, 4, 2, dict(noise_dtype=0, antithetic=0, pop=3)), (27, 256, 8, 4, 2, dict(done_thresh=1e-6)),
     (27, 256, 8, 1, 2, dict(horizon=1)), (13, 130, 4, 2, 2, dict(envs=3, episodes=3)), (75, 90, 11, 4, 2, dict(done_thresh=0.5))],
     ids=lambda v: str(v) if not isinstance(v, dict) else "-".join(f"{k}{x}" for k, x in v.items()))
