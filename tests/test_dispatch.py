@@ -65,3 +65,11 @@ def test_three_and_four_middle_layers_stay_on_the_matrix_cores(kernel, layers, h
 def test_four_layers_of_several_copies_and_wide_observations_run_in_sixteen_columns(kernel, hid, obs, envs, name):
     """The four-copy kernel spills there; the 16-column kernel is 10 to 17 % faster."""
     assert f"rollout_mfma_{name}_bf16" in kernel(replace(F32, dtype=1, noise_dtype=1, num_hidden=4, pop=32, hid=hid, obs=obs, envs=envs))
+
+
+@pytest.mark.parametrize("kw,name", [(dict(), "reg"), (dict(envs=13), "reg"), (dict(envs=12), "quad"), (dict(envs=32), "reg"), (dict(pop=510), "quad"), (dict(obs=33), "quad"), (dict(hid=127), "quad"),
+                                     (dict(act=17), "quad"), (dict(envs=8, episodes=2), "reg")], ids=str)
+@pytest.mark.parametrize("layers", [1, 2])
+def test_128_units_on_full_columns(kernel, layers, kw, name):
+    w = replace(F32, dtype=1, noise_dtype=1, num_hidden=layers, pop=512, hid=128, envs=16)
+    assert f"rollout_mfma_{name}_bf16" in kernel(replace(w, **kw))

@@ -103,6 +103,12 @@ def test_bf16(es, layers, kw, norm):
     _run(es, replace(w, **kw), _bf16_name(replace(w, **kw)), norm)
 
 
+@pytest.mark.parametrize("layers,norm", [(1, False), (2, True)])
+def test_bf16_128_units(es, layers, norm):
+    w = replace(B, name=f"bf16c16-m{layers}-hid128", hid=128, pop=512, envs=15, horizon=8, num_hidden=layers)
+    _run(es, w, _bf16_name(w), norm)
+
+
 @pytest.mark.parametrize("layers", [3, 4])
 @pytest.mark.parametrize("hid,obs,norm", [(65, 27, False), (96, 64, True), (127, 20, False)])
 def test_bf16_three_and_four_middle_layers(es, layers, hid, obs, norm):
