@@ -15,8 +15,6 @@ namespace es {
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-constexpr uint32_t SAMPLE_WGS = 22528;
-
 template <bool BF16>
 __device__ __forceinline__ void store4(void* __restrict__ out, size_t off, float z0, float z1, float z2, float z3) {
   if (BF16) {
@@ -105,13 +103,10 @@ int launch_table_offsets(es_ctx* ctx, uint32_t gen, void* noise, hipStream_t st)
 int launch_sample(es_ctx* ctx, uint32_t gen, void* noise, hipStream_t st) {
   const Shape& s = ctx->shp;
   const uint32_t k0 = (uint32_t)ctx->cfg.seed, k1 = (uint32_t)(ctx->cfg.seed >> 32);
-  // A row per workgroup while the matrix stays in the last-level cache (every size up to 80 MB measured fastest that way);
-  // beyond it about SAMPLE_WGS workgroups of several rows each (2048 x 132 881 bf16: 275 us with one row each, 231 us
-  // with twelve).  Grid dimensions end at 65 535.
-  const uint32_t gx = (s.ld / 4 + 255) / 256;
-  const bool cached = (uint64_t)s.rows * s.ld * (ctx->cfg.noise_dtype == 1 ? 2u : 4u) <= (256ull << 20);
-  const uint32_t want = cached ? 65535u : std::max(1u, SAMPLE_WGS / gx), per = (s.rows + want - 1) / want;
-  const dim3 grid(gx, (s.rows + per - 1) / per);
+  // A row of 1024 columns per workgroup, at every size (65 matrices of 2 MB to 1.2 GB, profiles/sample_update_rules.md): fewer
+  // workgroups of several rows each are at most 2 % faster anywhere and 2 to 16 % slower from 50 MB on (2048 x 133 120 bf16 between
+  // ranking and update: 306 us a generation, 327 us with 22 528 workgroups).  Grid dimensions end at 65 535.
+  const dim3 grid((s.ld / 4 + 255) / 256, std::min(s.rows, 65535u));
   if (ctx->cfg.noise_dtype == 1)
     hipLaunchKernelGGL(sample_kernel<true>, grid, dim3(256), 0, st, noise, s.rows, s.D, s.ld, gen, k0, k1);
   else
