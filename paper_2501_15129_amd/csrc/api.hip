@@ -159,7 +159,7 @@ int es_create(const es_config* cfg, es_ctx** out) {
   ctx->regen_generation = 0;
   ctx->regen_valid = false;
   const bool regen = c.noise_dtype == 2 || c.noise_dtype == 3, bf16_noise = c.noise_dtype == 1 || c.noise_dtype == 5;
-  ctx->upd_chunks = regen ? update_chunks_regen(s.rows, s.D) : update_chunks(s.rows, s.ld, bf16_noise);
+  ctx->upd_chunks = regen ? update_chunks_regen(s.rows, s.D) : update_chunks(s.rows, s.ld, bf16_noise, small_population(c, s.E));
   ctx->workspace_bytes = std::max<size_t>(256, (size_t)ctx->upd_chunks * s.ld * sizeof(double));
   *out = ctx;
   return ES_OK;

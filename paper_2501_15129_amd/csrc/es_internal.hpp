@@ -114,7 +114,8 @@ std::string reg_variant_name(int variant, bool bf16, uint32_t layers);
 int mfma_variant_for(const es_config& cfg);       // -1 when no register-resident kernel fits
 const char* mfma_variant_name(int variant);
 size_t wave_rollout_lds_bytes(const es_config& cfg);
-uint32_t update_chunks(uint32_t rows, uint32_t ld, bool bf16);
+bool small_population(const es_config& cfg, uint64_t copies);      // copies = episodes evaluated per individual
+uint32_t update_chunks(uint32_t rows, uint32_t ld, bool bf16, bool one_launch);
 uint32_t update_chunks_regen(uint32_t rows, uint32_t D);
 
 }  // namespace es

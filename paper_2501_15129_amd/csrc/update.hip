@@ -190,9 +190,9 @@ __device__ __forceinline__ void apply_step(const AdamArgs& ad, double sum, uint3
 
 // Stage 2.  WAVES = 1: a thread per column adds the few partial rows of a large matrix.  WAVES = 16: the many partial rows
 // of a narrow one (column tiles are few there, so the rows are split further) are shared by the wavefronts of a
-// workgroup of 64 columns and combined in their order; one thread per column took 33 us for 675 partial rows of 2000
-// columns, one memory latency after the other.
-constexpr uint32_t ADAM_SPLIT_CHUNKS = 32;      // from here on the rows are shared (19 rows of 115 200 columns: 6 us against 9)
+// workgroup of 64 columns and combined in their order: the whole update of 4096 x 1539 in 256 chunks takes 14.4 us, with one
+// thread per column, one memory latency after the other, 22.7 us (675 chunks: 23 / 48).
+constexpr uint32_t ADAM_SPLIT_CHUNKS = 32;      // from here on (fewer: equal for narrow matrices, 2 to 3 % slower for wide ones)
 
 template <int WAVES>
 __global__ __launch_bounds__(WAVES == 1 ? 256 : 64 * WAVES) void adam_kernel(const double* __restrict__ partial, uint32_t chunks,
@@ -359,16 +359,19 @@ uint32_t update_chunks_regen(uint32_t rows, uint32_t D) {
 }
 
 // Row chunks of the streaming path; 1 = the single-pass kernel.  A workgroup of that kernel has 64 rows in flight and takes
-// 1.1 us for them, whatever the width, while the chip streams 64 rows of t column tiles in t / 100 of that: with t tiles the
-// split saves rows (100 - t) / 100 / 64 * 1.1 us and costs 5 us (a second launch and the partial rows).  2000 rows of 14
-// tiles: 36 -> 11 us.
-uint32_t update_chunks(uint32_t rows, uint32_t ld, bool bf16) {
+// about 1.1 us for them, whatever the width, while the chip streams 64 rows of t column tiles in t / 100 of that; the split costs
+// a second launch and the partial rows, 13 us for any narrow matrix.  Measured (bf16, profiles/sample_update_rules.md), one
+// launch against the split: 256 rows of 26 tiles 13.7 / 13.3 us, 384 rows 15.5 / 13.7, 512 rows 18.3 / 13.8, 2000 rows 47 / 18.7;
+// of 98 tiles 384 rows 17.1 / 16.4, 2000 rows 51 / 41; from 130 tiles on the one launch is as fast or faster up to 640 rows and at
+// most 7 % slower at 1024.  (A binary32 matrix of 294 tiles, a few more than there are CUs, would be 17 % faster in two chunks.)
+// `one_launch`: the population is small enough for fitness, ranks and update by one launch, which the split would give up.
+uint32_t update_chunks(uint32_t rows, uint32_t ld, bool bf16, bool one_launch) {
   const uint32_t tile = 64u * (bf16 ? 8u : 4u);
   const uint32_t col_tiles = ld / tile;
   uint32_t chunks;
   if ((uint64_t)rows * ld * (bf16 ? 2u : 4u) >= (256ull << 20))
     chunks = std::min((2048u + col_tiles - 1) / col_tiles, std::max(1u, rows / 16u));
-  else if (rows > 512u && col_tiles < 100u && (uint64_t)rows * (100u - col_tiles) > 30000u)
+  else if (rows >= 384u && col_tiles < 120u && !one_launch)
     chunks = std::max(2u, std::min(1024u / col_tiles, rows / 32u));      // 32 rows: two loads in turn per wavefront
   else
     return 1;
@@ -393,11 +396,10 @@ static AdamArgs step_args(const es_ctx* ctx, uint64_t step) {
 }
 
 // Populations small enough for one launch of fitness, ranks and update.
-bool update_ranks(const es_ctx* ctx) {
-  const Shape& s = ctx->shp;
-  return ctx->cfg.algorithm == ES_OPENES && ctx->upd_chunks == 1u && ctx->cfg.noise_dtype != 2 && ctx->cfg.noise_dtype != 3 &&
-         s.N <= UPD_FUSED_POP && (uint64_t)s.N * s.E <= UPD_FUSED_EPISODES;
+bool small_population(const es_config& c, uint64_t copies) {
+  return c.algorithm == ES_OPENES && c.noise_dtype != 2 && c.noise_dtype != 3 && c.pop <= UPD_FUSED_POP && c.pop * copies <= UPD_FUSED_EPISODES;
 }
+bool update_ranks(const es_ctx* ctx) { return ctx->upd_chunks == 1u && small_population(ctx->cfg, ctx->shp.E); }
 
 template <bool FUSED>
 static void launch_single_pass(es_ctx* ctx, const NoiseView& nv, const float* shaped, const AdamArgs& ad, float* theta,

@@ -73,3 +73,14 @@ def test_four_layers_of_several_copies_and_wide_observations_run_in_sixteen_colu
 def test_128_units_on_full_columns(kernel, layers, kw, name):
     w = replace(F32, dtype=1, noise_dtype=1, num_hidden=layers, pop=512, hid=128, envs=16)
     assert f"rollout_mfma_{name}_bf16" in kernel(replace(w, **kw))
+
+
+@pytest.mark.parametrize("kw,split", [
+    (dict(pop=766), False), (dict(pop=768), True), (dict(pop=512, antithetic=0), False), (dict(pop=514, antithetic=0), True), (dict(pop=384, antithetic=0, envs=10), False),
+    (dict(pop=384, antithetic=0, envs=11), True), (dict(pop=512, antithetic=0, algorithm=2, num_elites=5), True), (dict(pop=768, obs=120, hid=128, act=17), False),
+    (dict(pop=2048, obs=64, hid=128, act=17), True), (dict(pop=8, obs=64, hid=128), False)], ids=str)
+def test_rows_of_the_update_are_split_where_it_pays(kw, split):
+    """From 384 rows on and below 120 column tiles, unless fitness, ranks and update are one launch."""
+    from paper_2501_15129_amd.binding import EsContext
+    ctx = EsContext(replace(replace(F32, obs=17, hid=64, act=6), **kw))
+    assert ctx.update_kernel == ("grad_partial_kernel+adam_kernel" if split else "update_single_pass_kernel")

@@ -53,6 +53,9 @@ MANY_ROWS = [
     replace(NARROW, pop=1300, antithetic=0),
     replace(NARROW, pop=2602, obs=13, hid=29, act=7, noise_dtype=1),
     replace(NARROW, pop=1026, noise_dtype=2),
+    replace(NARROW, pop=768),
+    replace(NARROW, pop=770, noise_dtype=1),
+    replace(NARROW, pop=385, antithetic=0, envs=11, noise_dtype=1),
     replace(NARROW, pop=1300, antithetic=0, obs=13, hid=29, act=7, noise_dtype=3),
 ]
 
