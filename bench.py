@@ -26,7 +26,9 @@ HBM_PEAK_GBS = 8000.0          # MI355X published HBM3E bandwidth
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # dense bf16 MFMA
 FP32_VALU_PEAK_TFLOPS = 157.3   # 256 CUs x 4 SIMDs x 16 lanes x 2 (packed) x 2 flop x 2.4 GHz
 VALU_PEAK_TLANEOPS = 78.6       # the same figure as vector-lane operations per second (one FMA = one operation)
-REGEN_VALU_OPS_PER_BLOCK = 245  # vector instructions per Philox block + two Gaussian transforms + four fp64 FMAs (counted in the built kernel)
+# vector instructions per Philox block + two Gaussian transforms + four fp64 FMAs, by noise_dtype (the loop of grad_regen_kernel
+# as the compiler writes it; rounding to bf16 costs twelve)
+REGEN_VALU_OPS_PER_BLOCK = {2: 159, 3: 171}
 
 
 def flop_per_env_step(w) -> int:
@@ -333,7 +335,7 @@ def main() -> int:
                        "bytes_per_launch": ub,
                        "avg_launch_ms": upd_ms}
     if w.noise_dtype in (2, 3):      # no noise matrix: the update recomputes every value and is bound by the vector ALUs
-        ops = w.noise_rows * ((w.n_params + 3) // 4) * REGEN_VALU_OPS_PER_BLOCK
+        ops = w.noise_rows * ((w.n_params + 3) // 4) * REGEN_VALU_OPS_PER_BLOCK[w.noise_dtype]
         tops = ops / (upd_ms * 1e-3) / 1e12
         roofline_update = {"kernel": ctx.update_kernel, "bound": "alu", "achieved": tops, "peak": VALU_PEAK_TLANEOPS,
                            "unit": "T lane-op/s", "frac": tops / VALU_PEAK_TLANEOPS, "traffic": None,
