@@ -3,7 +3,7 @@
 
 One "step" is one whole generation: es_sample_population -> es_rollout -> es_rank ->
 es_update, enqueued on one stream with every input already resident in HBM.  The default
-workload is the largest configuration (configs[4]: population 4096 x 4 environment copies,
+workload is the largest configuration (cfg4: population 4096 x 4 environment copies,
 T = 1000, MLP 244-256-256-17, bf16) under the paper's timing protocol of fixed-length
 episodes (Sec. 5.1); the same workload with its termination rule switched on is reported
 beside it.  Prints ONE JSON line.
@@ -197,11 +197,11 @@ def main() -> int:
                     help="k episodes per environment copy (auto-reset wrapper, paper Sec. 3.1); not the default workload")
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--cpu-full", action="store_true",
-                    help="run the CPU checker once over the WHOLE population instead of a bounded sample (about two minutes at configs[4])")
+                    help="run the CPU checker once over the WHOLE population instead of a bounded sample (about two minutes at cfg4)")
     ap.add_argument("--env-f32", action="store_true",
                     help="bf16 workloads: keep the environment's products A s + B a in binary32 (env_dtype = 1; obs <= 64)")
     ap.add_argument("--no-antithetic", action="store_true",
-                    help="independent noise rows for every individual (antithetic = 0): at configs[4] es_update then streams the literal "
+                    help="independent noise rows for every individual (antithetic = 0): at cfg4 es_update then streams the literal "
                          "4096 x 132k bf16 matrix, 1.09 GB")
     ap.add_argument("--no-second-variant", action="store_true", help="skip the extra timing with the termination rule on")
     ap.add_argument("--copy-calibration", action="store_true",

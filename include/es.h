@@ -95,7 +95,8 @@ typedef struct es_config {
                             case and the default are 2; 0 means 2).  Flat parameters: W1[hid,obs], b1,
                             then (m - 1) x (W[hid,hid], b[hid]), then W3[act,hid], b3.  The
                             register kernels serve m = 1..4 with obs, hid <= 64, act <= 16; in bf16 m = 2
-                            for hid <= 256, obs <= 256, act <= 32 and m = 1, 3, 4 for obs <= 64, act <= 16;
+                            for hid <= 256, obs <= 256, act <= 32 and m = 1, 3, 4 for obs <= 64, act <= 16
+                            (m = 1 up to 128 units: obs <= 128, act <= 32);
                             in binary32 m = 1, 2 for hid <= 256 and m = 3 for hid <= 128, obs <= 64,
                             act <= 16; everything else runs on the LDS kernel if the individual fits the
                             LDS (else ES_EUNSUPPORTED from es_rollout) */
@@ -109,7 +110,7 @@ typedef struct es_config {
                             side by side (with few copies this also fills matrix-core columns that would
                             otherwise idle) and the results equal the sequential schedule's exactly         */
   uint32_t env_dtype;    /* only with dtype = 1.  0: the environment's products A s + B a use bf16 operands too
-                            (A, B, the state and the action rounded; configs[4] needs that to hold A on chip).
+                            (A, B, the state and the action rounded; with 244 observations A fits on chip no other way).
                             1: the environment stays binary32 - "bf16 weights and activations" is a property of the
                             policy, not of the simulator it acts on; built for two hidden layers with obs_dim <= 64
                             (any width on the LDS kernel if the individual fits), else ES_EUNSUPPORTED from es_rollout */
@@ -132,7 +133,7 @@ typedef enum es_algorithm { ES_OPENES = 0, ES_ARS = 1, ES_VANILLA = 2 } es_algor
 typedef struct es_ctx es_ctx; /* opaque, host-side: validated config + kernel choice */
 
 /* Validate `cfg` and build a context.  Allocates host memory only.  Must be called with the
- * target GPU current; the kernel choice depends on that device's LDS size. */
+ * target GPU current; the kernel choice depends on that device's LDS size and compute units. */
 int es_create(const es_config* cfg, es_ctx** out);
 int es_destroy(es_ctx* ctx);
 

@@ -39,11 +39,12 @@ __device__ __forceinline__ Words4 philox4x32_10(uint32_t c0, uint32_t c1, uint32
 // The values are DEFINED with a correctly rounded division and square root, so that any conforming machine
 // reproduces them bit for bit.  The arguments here lie in a narrow range (m + 1 in (1.7, 2.42], 2 (-ln u1) in
 // [0, 33.3]), so the general sequences - scaling, special values, a second Newton step: half of the transform -
-// are not needed: one reciprocal (or reciprocal square root) and one residual correction round the same.  There
-// are only 2^24 radii and 2^24 angles: both were compared over all of them on gfx950, none differs.
+// are not needed: one reciprocal (or reciprocal square root) and one multiply-add of the residual (P. W. Markstein,
+// IBM J. Res. Dev. 34 (1990), pp. 111-119) round the same.  There are only 2^24 radii and 2^24 angles: tests/test_gpu_gauss.py
+// compares all of them with the general sequences.
 // Three more exact savings: m and n come out of one biased integer add; 4 ln m is carried scaled (num and the
 // coefficients hold powers of two), so that 2 (-ln u1) needs no doubling; the octant's signs are bits of xb
-// inserted into the products.  About 50 vector instructions instead of 94 per pair.
+// inserted into the products.  About 50 vector instructions per pair, 94 with the general sequences.
 __device__ __forceinline__ void gauss_pair(uint32_t xa, uint32_t xb, float& zc, float& zs) {
   // bits of k1 as a float, offset so that the exponent steps at sqrt(2) instead of at 2
   const uint32_t ix = __float_as_uint((float)((xa >> 8) + 1u)) + 0x004AFB0Cu;

@@ -74,7 +74,7 @@ def test_binary32_environment_with_observation_statistics(es):
 
 
 def test_binary32_environment_refused_where_no_kernel_holds_it(es):
-    """configs[4]'s 244 x 244 environment matrix does not fit on chip in binary32 beside the policy."""
+    """cfg4's 244 x 244 environment matrix does not fit on chip in binary32 beside the policy."""
     w = replace(CONFIGS[4], name="cfg4-envf", env_dtype=1, pop=4)
     ctx = es.EsContext(w)
     a_mat, b_mat, theta = make_inputs(w)
@@ -84,7 +84,7 @@ def test_binary32_environment_refused_where_no_kernel_holds_it(es):
 
 
 def test_config3_full_size_with_binary32_environment(es):
-    """configs[3] with the environment in binary32 (the reading that keeps "bf16 weights and activations" to the policy):
+    """cfg3 with the environment in binary32 (the reading that keeps "bf16 weights and activations" to the policy):
     whole population, contractive twin at T = 1000 held to the strict tolerance on 32 mirrored pairs, and the workload as
     specified on 32 pairs."""
     for w in (replace(CONFIGS[3].contractive(), name="cfg3-contractive-envf", env_dtype=1), replace(CONFIGS[3], name="cfg3-envf", env_dtype=1)):

@@ -78,7 +78,7 @@ def test_generation_with_episodes_per_env(es):
 
 @pytest.mark.parametrize("idx", [3, 4])
 def test_full_size_configs_with_four_episodes_per_env(es, idx):
-    """configs[3] / [4] at full population with k = 4 (config 4 then fills all 16 matrix-core columns), in the
+    """cfg3 / cfg4 at full population with k = 4 (config 4 then fills all 16 matrix-core columns), in the
     launch configuration of `bench.py --episodes-per-env 4`.  At the long horizon the outputs are checked for
     the properties that hold at any size; the checker recomputes sampled mirrored pairs at a horizon short
     enough for bf16 trajectories not to have diverged (the per-step code path is the same for every step)."""

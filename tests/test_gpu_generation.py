@@ -83,7 +83,7 @@ def test_three_generations_chained(es, w):
 
 @pytest.mark.parametrize("idx", [3, 4])
 def test_one_generation_full_size_chained(es, idx):
-    """configs[3] and configs[4] exactly as specified, whole population, the four calls chained on the GPU:
+    """cfg3 and cfg4 exactly as specified, whole population, the four calls chained on the GPU:
     sampled noise rows bit-equal to the checker's, 32 sampled mirrored pairs of the rollout against the checker,
     ranks of the GPU's own fitness bit-equal, and the update of all parameters against the checker's update fed
     with the checker's own full noise matrix and those ranks."""

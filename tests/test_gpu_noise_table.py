@@ -131,7 +131,7 @@ def test_update_reads_its_rows_from_the_table(es, w):
 
 
 def test_generation_with_table_full_size_cfg4(es):
-    """configs[4] with a 64 M-entry bf16 table (128 MB instead of the 545 MB matrix): sampled mirrored pairs
+    """cfg4 with a 64 M-entry bf16 table (128 MB instead of the 545 MB matrix): sampled mirrored pairs
     of the rollout and the whole 132 881-parameter update against the checker."""
     n = 1 << 26
     base = CONFIGS[4]

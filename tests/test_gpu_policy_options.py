@@ -69,7 +69,7 @@ def test_rollout_small_16_16_network(es, hidden_act, dtype):
 
 @pytest.mark.parametrize("idx", [3, 4])
 def test_rollout_relu_full_size_bf16_configs(es, idx):
-    """configs[3] and [4] with ReLU hidden layers, full population, in the launch configuration of
+    """cfg3 and cfg4 with ReLU hidden layers, full population, in the launch configuration of
     `bench.py --hidden-act relu`; the checker recomputes sampled mirrored pairs."""
     w = replace(CONFIGS[idx], name=f"cfg{idx}-relu", hidden_act=1)
     a_mat, b_mat, theta = make_inputs(w)

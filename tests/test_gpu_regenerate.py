@@ -111,7 +111,7 @@ def test_update_regenerated_needs_a_generation(es):
 
 
 def test_generation_regenerated_full_size_cfg4(es):
-    """configs[4] at full size without a noise matrix: one whole generation.  The stored-matrix
+    """cfg4 at full size without a noise matrix: one whole generation.  The stored-matrix
     mode of the same library (checked against the checker elsewhere) must be reproduced bit for
     bit by the rollout; the update is compared with the checker on the full parameter vector."""
     base = CONFIGS[4]

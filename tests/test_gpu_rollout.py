@@ -63,7 +63,7 @@ def test_rollout_small_shapes(es, w):
 
 @pytest.mark.parametrize("idx", [0, 1, 2])
 def test_rollout_fp32_configs_full(es, idx):
-    """configs[0..2] at full size, every (individual, environment) pair compared."""
+    """cfg0 to cfg2 at full size, every (individual, environment) pair compared."""
     _case(es, CONFIGS[idx], gen=0)
 
 
@@ -77,7 +77,7 @@ def test_rollout_fp32_configs_fixed_length(es, idx):
 
 @pytest.mark.parametrize("idx", [1, 2])
 def test_rollout_fp32_configs_short_horizon_strict(es, idx):
-    """The first 60 steps of configs[1..2], where no trajectory has had time to diverge:
+    """The first 60 steps of cfg1 to cfg2, where no trajectory has had time to diverge:
     every episode must meet the strict tolerance (no sensitive-episode allowance)."""
     w = replace(CONFIGS[idx], name=f"cfg{idx}-T60", horizon=60)
     a_mat, b_mat, theta = make_inputs(w)
@@ -205,14 +205,14 @@ def _full_size_sampled(es, w, gen, n_blocks, allow_chaotic=False, probes=None):
 
 @pytest.mark.parametrize("idx", [3, 4])
 def test_rollout_bf16_configs_full_size(es, idx):
-    """configs[3] and [4] exactly as specified (termination rule on), full population, 64 sampled pairs."""
+    """cfg3 and cfg4 exactly as specified (termination rule on), full population, 64 sampled pairs."""
     _full_size_sampled(es, CONFIGS[idx], gen=0, n_blocks=8)
 
 
 @pytest.mark.parametrize("idx", [3, 4])
 def test_rollout_contractive_twins_full_size(es, idx):
     """The launch configuration bench.py times - full population, fixed-length episodes, T = 1000, the shapes and
-    precision of configs[3] / [4] - on the contractive twin of the workload: 64 mirrored pairs (first, last and
+    precision of cfg3 / cfg4 - on the contractive twin of the workload: 64 mirrored pairs (first, last and
     random blocks) must meet the strict 2e-2 per episode, no episode sensitive, none excused.  This is the check
     that the step loop, the return accumulation, the passes over environment copies and the persistent grid's
     indexing are right at every step up to the last (paper Sec. 5.1 protocol, Sec. 5.2 fitness)."""
@@ -225,7 +225,7 @@ def test_rollout_contractive_twins_full_size(es, idx):
 
 
 def test_rollout_contractive_twin_sixteen_copies_two_action_tiles(es):
-    """configs[4]'s shapes with four episodes per environment copy - sixteen columns per pass, the K-split action layer with
+    """cfg4's shapes with four episodes per environment copy - sixteen columns per pass, the K-split action layer with
     two action tiles - on the contractive twin at the full horizon: strict 2e-2 per episode on 16 mirrored pairs."""
     w = replace(CONFIGS[4].contractive(), name="cfg4-contractive-k4-n256", pop=256, episodes=4)
     got, chaotic = _full_size_sampled(es, w, gen=0, n_blocks=2, probes=1)
@@ -235,7 +235,7 @@ def test_rollout_contractive_twin_sixteen_copies_two_action_tiles(es):
 
 @pytest.mark.parametrize("m", [1, 3, 4])
 def test_rollout_contractive_twin_other_depths_full_horizon(es, m):
-    """configs[3]'s shapes with one, three and four hidden layers (the paper's depth sweep, Sec. 5.1) on the contractive twin,
+    """cfg3's shapes with one, three and four hidden layers (the paper's depth sweep, Sec. 5.1) on the contractive twin,
     sixteen copies, T = 1000: every episode of a small population strictly within 2e-2."""
     w = replace(CONFIGS[3].contractive(), name=f"cfg3-contractive-m{m}-n8", pop=8, num_hidden=m)
     got, _ = _case(es, w, gen=0)
@@ -245,7 +245,7 @@ def test_rollout_contractive_twin_other_depths_full_horizon(es, m):
 
 @pytest.mark.parametrize("idx", [1, 2])
 def test_rollout_contractive_twins_fp32(es, idx):
-    """configs[1] / [2]'s twins, every episode, strict 1e-4 at T = 1000, none sensitive, none excused."""
+    """cfg1 / cfg2's twins, every episode, strict 1e-4 at T = 1000, none sensitive, none excused."""
     w = CONFIGS[idx].contractive()
     got, _ = _case(es, w, gen=0)
     assert np.all(got[1] == w.horizon)
@@ -255,7 +255,7 @@ def test_rollout_contractive_twins_fp32(es, idx):
 @pytest.mark.parametrize("idx", [3, 4])
 def test_rollout_bf16_configs_full_size_fixed_length(es, idx):
     """The original workloads under the fixed-length protocol, T = 1000, full population.  The closed loop of
-    configs[4] without its termination rule is chaotic (one bf16 ulp on a few operands moves the checker's own
+    cfg4 without its termination rule is chaotic (one bf16 ulp on a few operands moves the checker's own
     returns by several per cent), so there its episodes are held to the bounds derived from the checker's own
     spread; the strict comparison of this launch configuration at the full horizon is the contractive twin's
     (above), and here the strict tolerance is demanded at T = 16 as well, before trajectories have diverged."""
@@ -333,7 +333,7 @@ def test_register_resident_class_with_obs_norm_and_table(es):
     assert not chaotic
 
 
-# ---- register-resident binary32 variants (the narrow policies of configs[0..2]) ----
+# ---- register-resident binary32 variants (the narrow policies of cfg0 to cfg2) ----
 REG = Workload("reg", pop=6, envs=3, horizon=50, obs=17, hid=64, act=6, dtype=0, noise_dtype=0, seed=41)
 
 

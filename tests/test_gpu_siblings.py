@@ -111,7 +111,7 @@ def test_update_matches_checker(es, w):
 
 
 def test_update_ars_large_matrix_two_kernel_path(es):
-    """The shape of configs[4] (0.5 GB of bf16 noise, the chunked two-kernel stream) under ARS."""
+    """The shape of cfg4 (0.5 GB of bf16 noise, the chunked two-kernel stream) under ARS."""
     w = replace(CONFIGS[4], name="cfg4-ars", algorithm=ARS, num_elites=256, lr=0.02, sigma=0.03)
     ctx = es.EsContext(w)
     assert ctx.update_kernel.startswith("grad_partial")

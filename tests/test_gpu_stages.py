@@ -65,7 +65,7 @@ def test_sample_population_more_rows_than_a_grid_dimension(es):
 
 @pytest.mark.parametrize("idx", [3, 4])
 def test_sample_population_full_size_sampled_rows(es, idx):
-    """configs[3] (512 x 75264 bf16) and configs[4] (2048 x 133120 bf16) at full size: rows against the checker
+    """cfg3 (512 x 75264 bf16) and cfg4 (2048 x 133120 bf16) at full size: rows against the checker
     bit for bit, all rows finite."""
     w = CONFIGS[idx]
     ctx, noise = _sample(es, w, gen=1)
@@ -162,7 +162,7 @@ def test_update_grad_pointer_optional_and_rerun_identical(es):
 
 @pytest.mark.parametrize("idx", [3, 4])
 def test_update_full_size(es, idx):
-    """configs[3] (one-launch kernel, 512 rows x 75 016 parameters) and configs[4] (chunked stream, 2048 rows x
+    """cfg3 (one-launch kernel, 512 rows x 75 016 parameters) and cfg4 (chunked stream, 2048 rows x
     132 881 parameters) at full size: GPU-sampled noise (bit-equal to the checker's, see the sampling test),
     checker-side update over every parameter from the checker's own matrix."""
     w = CONFIGS[idx]

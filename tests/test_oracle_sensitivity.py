@@ -1,6 +1,6 @@
 """The sensitivity probe (one-ulp operand nudges, evaluated by the CPU checker alone) and the two
 regimes it tells apart: the contractive twins of the benchmark workloads damp a nudge far below the
-tolerance at the full horizon, the original configs[4] under the fixed-length protocol amplifies it."""
+tolerance at the full horizon, the original cfg4 under the fixed-length protocol amplifies it."""
 from dataclasses import replace
 
 import numpy as np
