@@ -256,7 +256,7 @@ template <class V, bool RELU, bool NORM>
 __global__ __launch_bounds__(V::NT) __attribute__((amdgpu_waves_per_eu(V::OCC * V::NW / 4, V::OCC * V::NW / 4)))
 void rollout_mfma_kernel(const MfmaArgs a) {
   extern __shared__ __align__(16) unsigned char lds[];
-  constexpr int KT1 = V::KT1, MT3 = V::MT3, MTE = V::MTE, KTA = V::KTA, PX = V::PX, PA = V::PA;
+  constexpr int KT1 = V::KT1, MT3 = V::MT3, MTE = V::MTE, KTA = V::KTA, PX = V::PX;
   constexpr int NW = V::NW, NT = V::NT, MT_H = V::MT_H;
   constexpr bool ENV_ALL = (V::ENV_ROWS == V::NOP);   // every wavefront's next-state tiles are inside the padded state
   constexpr int NC = V::NC;

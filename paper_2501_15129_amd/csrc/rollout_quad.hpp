@@ -24,7 +24,7 @@
 // (8.5 cycles per 4x4 instruction, measured) plus the vector work of the activations (5.8 cycles per instruction of a
 // lone wavefront).
 // Measured, whole rollout, T = 1000 unless noted: bf16 8-256-256-2, 128 individuals x 1 copy 1.23 ms (padded 16-column
-// kernel) -> 0.75 ms, x 4 copies 1.26 -> 0.97 ms; bf16 27-100-100-8, 128 x 5 copies, T = 400: 8.07 ms (LDS kernel) -> 0.36 ms.
+// kernel) -> 0.77 ms, x 4 copies 1.23 -> 1.01 ms; bf16 27-100-100-8, 128 x 5 copies, T = 400: 8.05 ms (LDS kernel) -> 0.35 ms.
 #pragma once
 
 #include <type_traits>
