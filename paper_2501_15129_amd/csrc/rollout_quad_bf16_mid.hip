@@ -2,7 +2,7 @@
 // or obs <= 128 with act <= 32 (state rows spread over the wavefronts).
 // tanh_near, because the LDS kernel that served these shapes is that accurate (error of the returns against binary64, rms and
 // geometric mean over 43 random shapes: 2.7e-5 and 5.0e-6 there, 6.0e-5 and 1.7e-5 with tanh_fast, 3.5e-5 and 6.1e-6 with
-// tanh_near; 27-100-100-8, 128 x 5 copies x 400 steps: 0.34 -> 0.36 ms).
+// tanh_near; 27-100-100-8, 128 x 5 copies x 400 steps: 0.335 -> 0.352 ms).
 #include "rollout_quad.hpp"
 
 namespace es {
