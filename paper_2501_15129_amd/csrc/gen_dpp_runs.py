@@ -5,7 +5,9 @@ Inline assembly needs its instruction text and operand numbers as literals, so t
 (accumulators, inputs per row) pair the kernels use are spelled out here instead of by hand."""
 from pathlib import Path
 
-DOT = [(q, n) for q in (1, 2, 4) for n in (3, 4, 5, 8, 16)]     # (accumulators, inputs per row)
+DOT = [(q, n) for q in (1, 2, 4) for n in (3, 4, 5, 8, 12, 16)]     # (accumulators, inputs per row)
+CHAIN = (3, 4, 5, 8, 12, 16)                                    # one accumulator, no partial sums
+ROTATE = (4, 8, 16)                                             # rotations of a row
 MAC = (3, 4, 6, 8, 16)                                          # accumulate-into runs (the action term)
 TAIL = ' row_mask:0xf bank_mask:0xf bound_ctrl:1\\n\\t"'
 
@@ -47,6 +49,20 @@ def mac_block(n):
     return f'    asm volatile("s_nop 1\\n\\t"\n{body}\n        : "+v"(acc)\n        : "v"(h),\n{operands(n)});\n'
 
 
+def chain_block(n):
+    """one accumulator: a dependent multiply-add issues as fast as an independent one, so partial sums would only cost their additions"""
+    lines = [ins("v_mul_f32_dpp" if j == 0 else "v_fmac_f32_dpp", 0, 1, 2 + j, j) for j in range(n)]
+    body = "      " + "\n      ".join(lines)
+    return f'    asm volatile("s_nop 1\\n\\t"\n{body}\n        : "=&v"(p)\n        : "v"(h),\n{operands(n)});\n'
+
+
+def rotate_block(n):
+    """the first rotation is none: a plain multiply, which is also one of the two wait states"""
+    lines = ['"v_mul_f32_e32 %0, %1, %2\\n\\t"'] + [f'"v_fmac_f32_dpp %0, %1, %{2 + j} row_ror:{j}{TAIL}' for j in range(1, n)]
+    body = "      " + "\n      ".join(lines)
+    return f'    asm volatile("s_nop 0\\n\\t"\n{body}\n        : "=&v"(p)\n        : "v"(h),\n{operands(n)});\n'
+
+
 def main():
     out = ["// Generated by gen_dpp_runs.py - do not edit.",
            "//",
@@ -81,6 +97,15 @@ def main():
     out.append('  else static_assert(N < 0, "no run of this length: add it to gen_dpp_runs.py");')
     out.append("  return acc;")
     out.append("}")
+    for name, doc, sizes, block in (
+            ("row_bcast_chain", "// sum_{j < N} w[j] * (lane j of h's row), in one accumulator", CHAIN, chain_block),
+            ("row_rotate_chain", "// sum_{j < N} w[j] * (lane (c - j) mod 16 of h's row) in column c, in one accumulator", ROTATE, rotate_block)):
+        out += ["", doc, "template <int N>", f"__device__ __forceinline__ float {name}(float h, const float (&w)[N]) {{", "  float p;"]
+        for k, n in enumerate(sizes):
+            out.append(f"  {'if' if k == 0 else 'else if'} constexpr (N == {n}) {{")
+            out.append(block(n).rstrip("\n"))
+            out.append("  }")
+        out += ['  else static_assert(N < 0, "no run of this length: add it to gen_dpp_runs.py");', "  return p;", "}"]
     Path(__file__).with_name("dpp_runs.inc").write_text("\n".join(out) + "\n")
 
 

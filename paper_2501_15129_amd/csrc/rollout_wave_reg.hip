@@ -1,7 +1,7 @@
 // Narrow policies in one wavefront per episode: choice of the variant, the exact shapes.
 #include <algorithm>
 
-#include "rollout_wave_reg.hpp"
+#include "rollout_wave_team.hpp"
 
 namespace es {
 
@@ -46,6 +46,14 @@ static void launch_fixed(int mode, dim3 grid, size_t lds, hipStream_t st, const 
     default: go(rollout_reg_kernel<CJ, NQ, NAR, 7, false, 2>); break;
   }
 }
+// Four wavefronts share an episode (rollout_wave_team.hpp) while every episode has a compute unit of its own; two episodes on a compute
+// unit only with four layers.  Per 200 steps, four wavefronts against one: 256 episodes of 17-64-64-6 84 us against 90, 512 episodes 108 against
+// 91; three layers of 64 97 against 145, 145 against 147; 30-40x4-6 124 against 212, 178 against 218, 640 episodes 241 against 219.
+static bool reg_team(const es_ctx* ctx) {
+  const Shape& s = ctx->shp;
+  return s.nh > 32 && s.m >= 2 && s.m <= 4 && (uint64_t)s.N * s.E <= (uint64_t)ctx->num_cus * (s.m == 4 ? 2u : 1u);
+}
+
 int launch_rollout_reg(es_ctx* ctx, uint32_t gen, const float* theta, const void* noise, const float* A,
                        const float* B, float* returns, int32_t* ep_len, float* fitness, void* /*ws*/,
                        hipStream_t st) {
@@ -63,12 +71,20 @@ int launch_rollout_reg(es_ctx* ctx, uint32_t gen, const float* theta, const void
   a.env_f32 = (c.dtype == 1 && c.env_dtype == 1) ? 1u : 0u;
   a.sigma = c.sigma; a.done_thresh = c.done_thresh; a.act_cost = c.act_cost;
   const dim3 grid(s.N * s.E);
-  const size_t lds = sizeof(float) * (size_t)std::max(s.nh * (s.no + 1u), std::max(s.m > 1u ? s.nh * (s.nh + 1u) : 0u, s.na * (s.nh + 1u)));      // one layer: at most 65 * 64 values
+  // the parameters of an individual pass through the LDS at once (one round of memory latency instead of one per layer) where the
+  // wavefronts of a CU have room for it, else one layer at a time: at most 65 * 64 values
+  const size_t whole = sizeof(float) * (size_t)s.D, per_cu = ((size_t)s.N * s.E + ctx->num_cus - 1) / ctx->num_cus;
+  a.whole = whole <= 48u * 1024u && whole * per_cu <= 128u * 1024u ? 1u : 0u;
+  const size_t lds = a.whole ? whole : sizeof(float) * (size_t)std::max(s.nh * (s.no + 1u), std::max(s.m > 1u ? s.nh * (s.nh + 1u) : 0u, s.na * (s.nh + 1u)));
   const int mode = (c.hidden_act == 1 ? 4 : 0) | (c.out_tanh ? 2 : 0) | (ctx->obs_mean ? 1 : 0);
   const int v = ctx->reg_variant;
   if (v < 0 || s.no > 64 || s.nh > 64 || s.na > 16 || s.m > 4)
     return fail(ctx, ES_EUNSUPPORTED, "es_rollout: no register-resident binary32 variant for this shape");
-  if (v == 0) launch_fixed<3, 2, 3>(mode, grid, lds, st, a);
+  int rc = ES_OK;
+  if (reg_team(ctx)) {
+    rc = c.dtype == 1 ? launch_team_bf16(ctx, grid, whole, st, a) : launch_team_f32(ctx, mode, grid, whole, st, a);
+    if (rc != ES_OK) return rc;
+  } else if (v == 0) launch_fixed<3, 2, 3>(mode, grid, lds, st, a);
   else if (v == 1) launch_fixed<5, 4, 6>(mode, grid, lds, st, a);
   else {
     const uint32_t cls = (uint32_t)(v - REG_EXACT);
@@ -76,7 +92,7 @@ int launch_rollout_reg(es_ctx* ctx, uint32_t gen, const float* theta, const void
     else if (s.m == 2) launch_reg_f32_two(cls, mode, grid, lds, st, a);
     else launch_reg_f32_deep(s.m, cls, mode, grid, lds, st, a);
   }
-  int rc = check_launch(ctx, "es_rollout (register-resident f32)");
+  rc = check_launch(ctx, "es_rollout (register-resident f32)");
   if (rc != ES_OK || s.E == 1u) return rc;
   return launch_fitness(ctx, returns, fitness, st);
 }

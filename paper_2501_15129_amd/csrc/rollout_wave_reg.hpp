@@ -21,13 +21,16 @@
 // benchmark shapes 11-32-3 and 17-64-6, whose activations and observation statistics are compile-time
 // variants too, and rounded up to a few classes for every other shape (padding has zero weights), where
 // the activations are chosen by branch-free selects.
-// Bound: one wavefront's instructions (32-256 episodes for 1024 SIMDs).  A lone wavefront is fed 8 bytes of code every 5.2
-// cycles, which is one DPP multiply-add, and no number of independent instructions hides that; so the count of instructions and
-// bytes of a step is what matters (18 KB per 10 steps of 17-64-64-6), and a taken branch, which costs 70 cycles, comes once in
-// four steps.  Splitting an episode over four wavefronts measured the same (two LDS hand-overs of 140 cycles per step).
-// 17-64-64-6, 256 episodes x 1000 steps: 465 -> 447 us; 11-40-40-3: 455 -> 425 us; three layers, which used to stream their
-// weights from the LDS: 17-64-64-64-6, 128 episodes x 400 steps: 4.2 -> 0.28 ms.
+// A layer of at most 32 units, which four rows would hold twice, is shared by the rows that hold the same inputs; the action layer of at most
+// eight actions is summed by sixteen columns, each over a part of its row's inputs (row_ror instead of row_newbcast).
+// Bound: one wavefront's instructions (32-256 episodes for 1024 SIMDs).  A lone wavefront issues a DPP multiply-add (8 bytes) every 4.5
+// cycles, a plain one (4 bytes) every 4, dependent or not; a transcendental takes 8, the two wait states before a DPP read 8, a taken
+// branch 70.  So the count of instructions and bytes of a step is what matters, and everything that ends a step comes once in four.
+// 11-32-32-3 (8 x 4 episodes, 100 steps, whole generation): 43.8 -> 36.2 us, some of it the staging (all layers in one round of loads); 17-64-64-6, 256
+// episodes x 1000 steps: 439 -> 391 us; 17-64-64-64-6, 128 episodes x 400 steps: 274 -> 266 us.
 #pragma once
+
+#include <type_traits>
 
 #include "es_internal.hpp"
 #include "rollout_stage.hpp"
@@ -51,6 +54,7 @@ struct RegArgs {
   uint32_t gen, k0, k1;
   uint32_t antithetic, noise_mode, hidden_relu, out_tanh;
   uint32_t env_f32;          // bf16 operands: keep the environment's products binary32
+  uint32_t whole;            // all parameters of an individual pass through the LDS at once
   float sigma, done_thresh, act_cost;
 };
 
@@ -91,7 +95,75 @@ __device__ __forceinline__ float row_total(float v) {
   v += dpp_zero<0x114, 0xF>(v);
   return v + dpp_zero<0x118, 0xF>(v);
 }
+// the value n columns away, (c - n) mod 16 of the row
+template <int N>
+__device__ __forceinline__ float dpp_rotate(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x120 + N, 0xF, 0xF, true));
+}
+// Columns after which the action vector repeats within a row: a column that adds up action c % P needs P of its row's sixteen
+// inputs, the columns P apart hold the other parts
+constexpr int action_period(int run) { return run <= 4 ? 4 : run <= 8 ? 8 : 16; }
 
+// Activations of the one- and four-wavefront kernels.  tanh(x + b) is 1 - 2 / (1 + 2^(c x + c b)), the bias in the multiply-add;
+// MODE < 0 chooses between the activations by selects (no branches).  NEAR: the tanh that is accurate near zero, for bf16 policies of one, three and
+// four layers, like the LDS kernel's, which served them (error of the returns against binary64, geometric mean of 50 random
+// shapes: 3.9e-6 there, 8.4e-6 with the short form, 3.7e-6 with this one; 0 to 6 % of the time)
+template <int MODE, bool NEAR>
+struct RegAct {
+  static constexpr bool FIXED = MODE >= 0, RELU = FIXED && (MODE & 4), OUT_TANH = FIXED && (MODE & 2);
+  float c;
+  // c in a scalar register: a multiplication is four bytes then, not eight
+  __device__ __forceinline__ RegAct() : c(2.88539008f) { asm volatile("" : "+s"(c)); }      // 2 log2(e), as in tanh_fast
+  __device__ __forceinline__ float squash(float t) const {
+    if (NEAR) return tanh_near(t);
+    return __fmaf_rn(-2.0f, __builtin_amdgcn_rcpf(__builtin_amdgcn_exp2f(t) + 1.0f), 1.0f);
+  }
+  // a bias, as ReLU and the linear output take it and as tanh does (the fixed modes drop the other)
+  struct Bias { float b, cb; };
+  __device__ __forceinline__ Bias bias(float b) const { return Bias{b, c * b}; }
+  __device__ __forceinline__ float tanh_of(float x, Bias b) const { return squash(__fmaf_rn(x, c, b.cb)); }
+  __device__ __forceinline__ float hidden(float x, Bias b, uint32_t relu) const {
+    if (FIXED) return RELU ? fmaxf(x + b.b, 0.f) : tanh_of(x, b);
+    const float z = fmaxf(x + b.b, 0.f), t = tanh_of(x, b);
+    return relu ? z : t;
+  }
+  __device__ __forceinline__ float out(float x, Bias b, uint32_t otanh) const {
+    if (FIXED) return OUT_TANH ? tanh_of(x, b) : x + b.b;
+    const float z = x + b.b, t = tanh_of(x, b);
+    return otanh ? t : z;
+  }
+  __device__ __forceinline__ float state(float x) const { return squash(x * c); }
+};
+
+// Steps until the horizon or until step(k) names lanes above the threshold; returns their number, with R as it was after the last of them.
+// A taken branch costs a lone wavefront 70 cycles and the test of a compare's mask 31 (it waits for the compare), so both come once
+// in a turn of four steps.  Nothing outside the registers depends on the steps a turn makes beyond an episode's end; R is kept for each.
+template <class Step>
+__device__ __forceinline__ uint32_t run_episode(uint32_t T, float& R, Step&& step) {
+  // (the share of a step is added within it, where its instructions fill waits, not all four behind the last)
+  auto booked = [](float& r) { asm volatile("" : "+v"(r)); return r; };
+  uint32_t left = T, stop;
+  unsigned long long m0, m1, m2, m3;
+  float r0, r1, r2;
+  do {
+    m0 = step(std::integral_constant<int, 0>{});
+    r0 = booked(R);
+    m1 = step(std::integral_constant<int, 1>{});
+    r1 = booked(R);
+    m2 = step(std::integral_constant<int, 2>{});
+    r2 = booked(R);
+    m3 = step(std::integral_constant<int, 3>{});
+    booked(R);
+    const unsigned long long m = (m0 | m1) | (m2 | m3);
+    asm volatile("s_cmp_lt_u32 %1, 5\n\ts_cselect_b32 %0, 1, 0" : "=s"(stop) : "s"(left) : "scc");      // (scalar: the compiler would make it a vector compare)
+    stop |= (uint32_t)m | (uint32_t)(m >> 32);
+    left -= 4u;
+  } while (stop == 0u);
+  left += 4u;
+  const uint32_t n = min(left, m0 != 0ull ? 1u : m1 != 0ull ? 2u : m2 != 0ull ? 3u : 4u);
+  R = n == 1u ? r0 : n == 2u ? r1 : n == 3u ? r2 : R;
+  return T - left + n;
+}
 
 // The perturbed parameters of one individual (one binary32 rounding each, then bf16 where they are operands in bf16), a range
 // of consecutive ones at a time into LDS, in coalesced order; the loads of eight iterations are in flight together.
@@ -156,8 +228,7 @@ template <int CJ, int NQ, int NAR, int MODE, bool BF16, int M>
 __global__ __launch_bounds__(64) void rollout_reg_kernel(const RegArgs a) {
   static_assert(NQ == 1 || NQ == 2 || NQ == 4, "rows of hidden units");
   constexpr bool FIXED = MODE >= 0;
-  constexpr int UNROLL = 4;
-  constexpr bool RELU = FIXED && (MODE & 4), OUT_TANH = FIXED && (MODE & 2), NORM = !FIXED || (MODE & 1);
+  constexpr bool NORM = !FIXED || (MODE & 1);
   extern __shared__ float sp[];      // the individual's perturbed parameters, once
   const int u = threadIdx.x;
   const uint32_t i = blockIdx.x / a.E, e = blockIdx.x % a.E;
@@ -167,8 +238,10 @@ __global__ __launch_bounds__(64) void rollout_reg_kernel(const RegArgs a) {
   const int lr = u >> 4, lc = u & 15;
   const int ks = 4 * lc + lr;                    // the state element of this lane
   const bool sval = lc < CJ && ks < no;
-  const int hu = NQ == 1 ? lc : u;               // the hidden unit of this lane
-  const bool hid = hu < nh;
+  // Units of a hidden layer, by lane.  NQ = 4: unit u in lane u; NQ = 1: unit c in column c of every row.  NQ = 2: two rows hold the same
+  // sixteen, alternately rows r and r + 2 (after layers 1, 3) and the rows of a pair (after layers 2, 4): a layer of a pair of rows that
+  // hold the same inputs is shared by them, each sums one half of the outputs, and one row stage adds the two halves of the inputs.
+  auto tile_of = [&](int layer) { return NQ == 4 ? lr : NQ == 1 ? 0 : (layer & 1) ? lr & 1 : lr >> 1; };      // of hidden layer 1, 2, ..
   auto opnd = [](float v) { return BF16 ? bf16_round(v) : v; };      // a value as an operand of a product
   // ... of one of the ENVIRONMENT's products: rounded like the policy's unless the environment stays binary32 (a select,
   // not a branch: the flag is read into a vector register the compiler cannot prove uniform)
@@ -176,81 +249,93 @@ __global__ __launch_bounds__(64) void rollout_reg_kernel(const RegArgs a) {
   if (BF16) asm volatile("" : "+v"(envf_l));
   auto opnd_env = [&](float v) { return BF16 ? (envf_l ? v : bf16_round(v)) : v; };
 
-  // ---- this lane's weights ----
-  // first layer: partial sums of the units lc, lc + 16, ... over the inputs of row lr: w1[CJ q + j] = W1[lc + 16 q][4 j + lr]
-  // second layer and action layer: the same over the 16 hidden units of row lr: w2[16 q + j] = W2[lc + 16 q][16 lr + j],
-  //   w3[j] = W3[lc][16 lr + j] (with one row of hidden units every row holds all of them: input j)
-  // environment: partial sums of the four state elements of column lc: ar[CJ r + j] = A[4 lc + r][4 j + lr];
-  //   action term of this lane's own element: br[c] = B[ks][c]
-  float w1[NQ * CJ], w2[M > 1 ? M - 1 : 1][NQ * 16], w3[16], ar[4 * CJ], br[NAR], b1, b2[M > 1 ? M - 1 : 1], b3;
-  // (one layer's window, at most 16.6 KB, leaves room for nine wavefronts per CU)
-  const ParamStage ps = param_stage(a, row, scale);
-  ps.stage<64, BF16>(sp, a.oW1, (uint32_t)(nh * no + nh));
-#pragma unroll
-  for (int qq = 0; qq < NQ; ++qq)
-#pragma unroll
-    for (int j = 0; j < CJ; ++j) {
-      const int unit = lc + 16 * qq, k = 4 * j + lr;
-      w1[CJ * qq + j] = (unit < nh && k < no) ? sp[unit * no + k] : 0.f;
-    }
-  b1 = hid ? sp[nh * no + hu] : 0.f;
-#pragma unroll
-  for (int l = 0; l < M - 1; ++l) {
-    ps.stage<64, BF16>(sp, a.oW2 + (uint32_t)l * (uint32_t)(nh * nh + nh), (uint32_t)(nh * nh + nh));
-#pragma unroll
-    for (int qq = 0; qq < NQ; ++qq)
-#pragma unroll
-      for (int j = 0; j < 16; ++j) {
-        const int unit = lc + 16 * qq, k = (NQ == 1 ? 0 : 16 * lr) + j;
-        w2[l][16 * qq + j] = (unit < nh && k < nh) ? sp[unit * nh + k] : 0.f;
-      }
-    b2[l] = hid ? sp[nh * nh + hu] : 0.f;
-  }
-  ps.stage<64, BF16>(sp, a.oW3, (uint32_t)(na * nh + na));
-#pragma unroll
-  for (int j = 0; j < 16; ++j) {
-    const int k = (NQ == 1 ? 0 : 16 * lr) + j;
-    w3[j] = (lc < na && k < nh) ? sp[lc * nh + k] : 0.f;
-  }
-  b3 = lc < na ? sp[na * nh + lc] : 0.f;            // in every row: the action vector is kept once per row
+  // ---- environment matrices and statistics, requested first (masked elements read the matrix's first entry) ----
+  // partial sums of the four state elements of column lc: ar[CJ r + j] = A[4 lc + r][4 j + lr]; action term of this lane's own
+  // element: br[c] = B[ks][c]
+  float ar[4 * CJ], br[NAR];
 #pragma unroll
   for (int r = 0; r < 4; ++r)
 #pragma unroll
     for (int j = 0; j < CJ; ++j) {
       const int el = 4 * lc + r, k = 4 * j + lr;
-      ar[CJ * r + j] = (lc < CJ && el < no && k < no) ? opnd_env(a.A[el * no + k]) : 0.f;
+      const bool ok = lc < CJ && el < no && k < no;
+      const float v = a.A[ok ? el * no + k : 0];
+      ar[CJ * r + j] = ok ? opnd_env(v) : 0.f;
     }
 #pragma unroll
-  for (int c = 0; c < NAR; ++c) br[c] = (sval && c < na) ? opnd_env(a.B[ks * na + c]) : 0.f;
-
+  for (int c = 0; c < NAR; ++c) {
+    const bool ok = sval && c < na;
+    const float v = a.B[ok ? ks * na + c : 0];
+    br[c] = ok ? opnd_env(v) : 0.f;
+  }
   // frozen observation statistics of this lane's state element (identity when none are set: (s - 0) * 1 = s exactly)
   const bool stats = a.obs_mean != nullptr;
   const float mu = (NORM && stats && sval) ? a.obs_mean[ks] : 0.f;
   const float iv = (NORM && stats && sval) ? a.obs_inv[ks] : 1.f;
+  float s = sval ? reset_value((uint32_t)ks, e, a.gen, a.k0, a.k1) : 0.f;
+
+  // ---- this lane's weights ----
+  // first layer: partial sums of the units lc, lc + 16, ... over the inputs of row lr: w1[CJ q + j] = W1[lc + 16 q][4 j + lr]
+  // further layers, NQ = 4 and 1: the same over the hidden units of row lr: w2[16 q + j] = W2[lc + 16 q][16 lr + j]; NQ = 2: of the one tile of
+  //   outputs this row has after the layer
+  // action layer: column lc adds up action lc % P over units lc, lc - 1, .., lc - P + 1 (mod 16) of its row (rows that hold the same: one of them)
+  constexpr int P = action_period(NAR), Q2 = NQ == 4 ? 4 : 1;
+  float w1[NQ * CJ], w2[M > 1 ? M - 1 : 1][Q2 * 16], w3[P], b1, b2[M > 1 ? M - 1 : 1], b3;
+  // all layers through the LDS at once, or one layer's window after the other (at most 16.6 KB: room for nine wavefronts per CU)
+  const ParamStage ps = param_stage(a, row, scale);
+  if (a.whole) ps.stage<64, BF16>(sp, 0u, a.D);
+  auto window = [&](uint32_t off, uint32_t count) -> const float* {
+    if (a.whole) return sp + off;
+    ps.stage<64, BF16>(sp, off, count);
+    return sp;
+  };
+  const float* wp = window(a.oW1, (uint32_t)(nh * no + nh));
+  auto pick = [&](bool ok, int idx) { const float v = wp[ok ? idx : 0]; return ok ? v : 0.f; };
+#pragma unroll
+  for (int qq = 0; qq < NQ; ++qq)
+#pragma unroll
+    for (int j = 0; j < CJ; ++j) {
+      const int unit = lc + 16 * qq, k = 4 * j + lr;
+      w1[CJ * qq + j] = pick(unit < nh && k < no, unit * no + k);
+    }
+  { const int unit = 16 * tile_of(1) + lc; b1 = pick(unit < nh, nh * no + unit); }
+#pragma unroll
+  for (int l = 0; l < M - 1; ++l) {
+    wp = window(a.oW2 + (uint32_t)l * (uint32_t)(nh * nh + nh), (uint32_t)(nh * nh + nh));
+    const int own = 16 * tile_of(l + 2) + lc;
+#pragma unroll
+    for (int qq = 0; qq < Q2; ++qq)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const int unit = NQ == 4 ? lc + 16 * qq : own, k = 16 * tile_of(l + 1) + j;
+        w2[l][16 * qq + j] = pick(unit < nh && k < nh, unit * nh + k);
+      }
+    b2[l] = pick(own < nh, nh * nh + own);
+  }
+  wp = window(a.oW3, (uint32_t)(na * nh + na));
+  const int ac = lc % P;
+  const bool sole = NQ != 2 || ((M & 1) ? lr < 2 : (lr & 1) == 0);      // the first row that holds these units
+#pragma unroll
+  for (int j = 0; j < P; ++j) {
+    const int k = 16 * tile_of(M) + ((lc - j) & 15);
+    w3[j] = pick(sole && ac < na && k < nh, ac * nh + k);
+  }
+  b3 = pick(ac < na, na * nh + ac);
+
   // run-time activation choices as per-lane values the compiler cannot prove uniform: selects, not branches
   uint32_t relu_l = a.hidden_relu, otanh_l = a.out_tanh;
   if (!FIXED) asm volatile("" : "+v"(relu_l), "+v"(otanh_l));
-  float s = sval ? reset_value((uint32_t)ks, e, a.gen, a.k0, a.k1) : 0.f;
   float R = 0.f;                      // per-lane share of the return
-  const float ninv_no = -1.0f / (float)no, nq_cost = -0.25f * a.act_cost;
+  // (every action is held 4 * 16 / P times)
+  const float ninv_no = -1.0f / (float)no, nq_cost = -(float)P / 64.0f * a.act_cost;
+  const RegAct<MODE, BF16 && M != 2> act{};
+  const auto c1 = act.bias(b1), c3 = act.bias(b3);
+  typename RegAct<MODE, BF16 && M != 2>::Bias c2[M > 1 ? M - 1 : 1];
+#pragma unroll
+  for (int l = 0; l < M - 1; ++l) c2[l] = act.bias(b2[l]);
 
-  // c of tanh(x) = 1 - 2 / (1 + 2^(c x)) in a scalar register: the multiplication is four bytes then, not eight
-  float tanh_c = 2.88539008f;      // 2 log2(e), as in tanh_fast
-  asm volatile("" : "+s"(tanh_c));
-  // bf16 policies of one, three and four layers: the tanh that is accurate near zero, like the LDS kernel's, which served them
-  // (error of the returns against binary64, geometric mean of 50 random shapes: 3.9e-6 there, 8.4e-6 with the short form, 3.7e-6
-  // with this one; 0 to 6 % of the time)
-  auto tanh_s = [&](float x) {
-    if (BF16 && M != 2) return tanh_near(x * tanh_c);
-    return __fmaf_rn(-2.0f, __builtin_amdgcn_rcpf(__builtin_amdgcn_exp2f(x * tanh_c) + 1.0f), 1.0f);
-  };
-  auto hidden = [&](float l) {
-    if (FIXED) return RELU ? fmaxf(l, 0.f) : tanh_s(l);
-    const float t = tanh_s(l);
-    return relu_l ? fmaxf(l, 0.f) : t;
-  };
-  // one step; true: the episode is over
-  auto step = [&]() {
+  // one step; the lanes whose state is above the threshold
+  auto step = [&](auto) {
     // h1 = act(W1 s + b1)
     const float xp = opnd(NORM ? (s - mu) * iv : s);      // the policy's input (paper App. B: fixed normalisation statistics)
     float p[NQ];
@@ -259,27 +344,29 @@ __global__ __launch_bounds__(64) void rollout_reg_kernel(const RegArgs a) {
     if constexpr (NQ == 4) l1 = rows_transpose_add(p[0], p[1], p[2], p[3]);
     else if constexpr (NQ == 2) l1 = rows_transpose_add(p[0], p[1]);
     else l1 = rows_add(p[0]);
-    float h2 = opnd(hidden(l1 + b1));      // the last hidden layer so far
+    float h = opnd(act.hidden(l1, c1, relu_l));      // the last hidden layer so far
     // further hidden layers: h = act(W h + b)
 #pragma unroll
     for (int l = 0; l < M - 1; ++l) {
-      row_bcast_dot<NQ, 16>(p, h2, w2[l]);
       float l2;
-      if constexpr (NQ == 4) l2 = rows_transpose_add(p[0], p[1], p[2], p[3]);
-      else if constexpr (NQ == 2) l2 = swap16_add(p[0], p[1]);      // the units' own rows 0 and 1 hold all of their inputs
-      else l2 = p[0];                                               // every row holds all inputs
-      h2 = opnd(hidden(l2 + b2[l]));
+      if constexpr (NQ == 4) {
+        row_bcast_dot<4, 16>(p, h, w2[l]);
+        l2 = rows_transpose_add(p[0], p[1], p[2], p[3]);
+      } else {
+        l2 = row_bcast_chain<16>(h, w2[l]);
+        if (NQ == 2) l2 = (l & 1) ? swap32_add(l2, l2) : swap16_add(l2, l2);      // the other half of the inputs: in the row's partner of the layer before
+      }
+      h = opnd(act.hidden(l2, c2[l], relu_l));
     }
-    // a = tanh(W3 h2 + b3): column c of every row ends up with unit c's total, one tanh serves all units
-    float pa[1];
-    row_bcast_dot<1, 16>(pa, h2, w3);
-    float pv = NQ == 1 ? pa[0] : rows_add(pa[0]);
-    pv = pv + b3;
-    float tv;
-    if (FIXED) tv = OUT_TANH ? tanh_s(pv) : pv;      // columns >= act: weights and bias are zero
-    else { const float tt = tanh_s(pv); tv = otanh_l ? tt : pv; }
-    // reward from the pre-step state, 1 - |s|^2 / obs - cost |a|^2: a sum over all 64 lanes (the action vector is held
-    // once per row, hence the quarter); this lane's share, the lanes are added after the last step
+    // a = tanh(W3 h + b3): every row holds every action, P columns apart; one tanh serves all of them
+    float pv = row_rotate_chain<P>(h, w3);
+    if (NQ != 1) pv = rows_add(pv);
+    else if (P <= 8) pv += 0.0f;      // (the wait states before a DPP read are counted from instructions the compiler sees)
+    if (P == 4) pv += dpp_rotate<4>(pv);
+    if (P <= 8) pv += dpp_rotate<8>(pv);
+    const float tv = act.out(pv, c3, otanh_l);      // actions >= act: weights and bias are zero
+    // reward from the pre-step state, 1 - |s|^2 / obs - cost |a|^2: a sum over all 64 lanes; this lane's share, the lanes are added after the
+    // last step
     R += __fmaf_rn(ninv_no * s, s, nq_cost * (tv * tv));
     // s' = tanh(A s + B a): partial sums of the four elements of this column over the inputs of this row, rows added
     // and moved to their element's lane; the action term straight from the row's action vector
@@ -287,25 +374,10 @@ __global__ __launch_bounds__(64) void rollout_reg_kernel(const RegArgs a) {
     row_bcast_dot<4, CJ>(ev, opnd_env(s), ar);
     float pre = rows_transpose_add(ev[0], ev[1], ev[2], ev[3]);
     pre = row_bcast_mac<NAR>(pre, opnd_env(tv), br);
-    s = tanh_s(pre);                                  // lanes without a state element: zero weights, tanh(0) = 0
-    // max |s| > threshold: some lane exceeds it
-    return __ballot(fabsf(s) > a.done_thresh) != 0ull;
+    s = act.state(pre);                               // lanes without a state element: zero weights, tanh(0) = 0
+    return __ballot(fabsf(s) > a.done_thresh);
   };
-  // A taken branch costs a lone wavefront 70 cycles, a branch not taken 5: UNROLL steps per turn
-  uint32_t len = 0u;
-  for (uint32_t turns = a.T / (uint32_t)UNROLL; turns != 0u; --turns) {
-#pragma unroll
-    for (int k = 0; k < UNROLL; ++k) {
-      ++len;
-      asm volatile("" : "+s"(len));      // (one register, counted here: the exits would each need their own count otherwise)
-      if (__builtin_expect(step(), 0)) goto end;
-    }
-  }
-  for (uint32_t rest = a.T % (uint32_t)UNROLL; rest != 0u; --rest) {
-    ++len;
-    if (__builtin_expect(step(), 0)) break;
-  }
-end:
+  const uint32_t len = run_episode(a.T, R, step);
   R = (float)len + row_total(rows_add(R));      // ends in lane 15
   if (u == 15) {
     a.returns[(size_t)i * a.E + e] = R;
