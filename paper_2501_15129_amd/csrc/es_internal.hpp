@@ -14,7 +14,7 @@ enum RolloutKind : int {
   ROLLOUT_MFMA_REG = 1,   // one workgroup per individual; bf16 weights resident in registers, MFMA
   ROLLOUT_WAVE_REG = 2,   // one wavefront per (individual, env); binary32 weights resident in registers
   ROLLOUT_MFMA_F32 = 3,   // one workgroup per individual; binary32 weights resident in registers, fp32 MFMA
-  ROLLOUT_QUAD = 4,       // passes of four copies on the 4x4 MFMA shapes; weights resident in registers
+  ROLLOUT_QUAD = 4,       // passes of four copies on the 4x4 MFMA shapes (narrow policies: or of sixteen); weights resident in registers
 };
 
 struct Shape {
