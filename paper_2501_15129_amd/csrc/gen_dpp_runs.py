@@ -43,6 +43,14 @@ def dot_block(q, n):
     return f'    asm volatile("s_nop 1\\n\\t"\n{body}\n        : {outs}\n        : "v"(h),\n{operands(q * n)});\n'
 
 
+def dot_add_block(q, n):
+    """as dot_block, added to o"""
+    lines = [" ".join(ins("v_fmac_f32_dpp", a, q, q + 1 + n * a + j, j) for a in range(q)) for j in range(n)]
+    outs = ", ".join(f'"+v"(o[{a}])' for a in range(q))
+    body = "      " + "\n      ".join(lines)
+    return f'    asm volatile("s_nop 1\\n\\t"\n{body}\n        : {outs}\n        : "v"(h),\n{operands(q * n)});\n'
+
+
 def mac_block(n):
     lines = [ins("v_fmac_f32_dpp", 0, 1, 2 + j, j) for j in range(n)]
     body = "      " + "\n      ".join(lines)
@@ -83,6 +91,11 @@ def main():
         out.append("  }")
         first = False
     out.append('  else static_assert(Q < 0, "no run of this shape: add it to gen_dpp_runs.py");')
+    out.append("}")
+    out.append("")
+    out.append("// o[a] += sum_{j < 16} w[16 a + j] * (lane j of h's row), a < 2")
+    out.append("__device__ __forceinline__ void row_bcast_dot_add(float (&o)[2], float h, const float (&w)[32]) {")
+    out.append(dot_add_block(2, 16).rstrip("\n"))
     out.append("}")
     out.append("")
     out.append("// acc + sum_{j < N} w[j] * (lane j of h's row)")
