@@ -93,6 +93,12 @@ template <> struct Oper<true> {
     const uint32_t u = q ? recv : r.x, w = q ? r.y : recv;           // units 0/1 and 2/3 of the quad, copies 2q and 2q + 1
     return V4{__builtin_amdgcn_perm(dpp_u<0xB1>(u), u, sel), __builtin_amdgcn_perm(dpp_u<0xB1>(w), w, sel)};
   }
+  // two copies: unit per lane -> copy x & 1 per lane, four units packed (lanes 2 and 3 of a quad, whose rows nobody reads, repeat two units)
+  static __device__ __forceinline__ V4 transpose2(float a, float b, bool, uint32_t sel) {
+    const uint32_t r = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+    const uint32_t u = __builtin_amdgcn_perm(dpp_u<0xB1>(r), r, sel);      // units 0/1 in lanes 0 and 1, 2/3 in lanes 2 and 3
+    return V4{u, dpp_u<0xEE>(u)};                                          // quad_perm [2, 3, 2, 3]
+  }
   // one copy: unit per lane -> four units of the lane's quad
   static __device__ __forceinline__ V4 gather(float v) { return pack_bf16x4(dpp_f<0x00>(v), dpp_f<0x55>(v), dpp_f<0xAA>(v), dpp_f<0xFF>(v)); }
   // action rows R b .. of copy x in lane 4 b + x -> four rows of the copy in every (4 / R)-th block
@@ -181,7 +187,7 @@ struct QuadShape {
   static constexpr int PH = HID + O::PAD_H;
   static constexpr int HB = 4 * PH * ES;                                 // one exchange buffer
   // the action: one or two rows of one copy per lane (ROWS_COPY), or one row per lane for all copies
-  static constexpr bool ROWS_COPY = NC == 4 ? (NW > 1 || !BF16) : (NW == 1 && !BF16);
+  static constexpr bool ROWS_COPY = NC > 1 ? (NW > 1 || !BF16) : (NW == 1 && !BF16);
   static constexpr int RPL = NA / 16;                                    // rows per lane of the former
   static constexpr int PP = NC == 1 ? 64 : NA + 4;                       // pitch (floats) of a copy's action partials
   static constexpr int PB = 4 * (BF16 ? 2 : 1) * NW * NC * PP;
@@ -209,6 +215,7 @@ struct QuadShape {
   static constexpr int NP = HALVES ? 2 * NW : NW;                        // partial sums of an action row
   static constexpr int WREGS = VR * (2 * KG + (M - 1) * HG + W3N + KGA);
   static constexpr int OCC = WREGS + 72 <= 168 ? 3 : WREGS + 72 <= 256 ? 2 : 1;
+  static constexpr bool PLACED = NW == 2 && OCC > 1;                     // may be launched with four wavefronts, two of which leave (wavefront_place)
   // first K group of portion k of A s: in the first activation, after the first exchange, in the second activation, after
   // the action's exchange, with the action's tanh
   static constexpr int env_at(int k) {
@@ -219,11 +226,30 @@ struct QuadShape {
   static_assert(!(GROUPED && NA > 16), "grouped action layer: sixteen rows");
   static_assert(!SPREAD || 64 * NW >= 4 * KG, "the wavefronts must cover the padded state");
   static_assert(KG % GR == 0 && HG % GR == 0 && LDS_BYTES <= 160 * 1024, "staging rounds, LDS budget");
-  static_assert(WREGS <= 490 && (NC == 1 || NC == 4), "register budget, copies");
+  static_assert(WREGS <= 490 && (NC == 1 || NC == 4 || (NC == 2 && HALVES && !SPREAD)), "register budget, copies");
 };
 
+// Two wavefronts, two workgroups on a CU: the hardware starts a workgroup one SIMD after the last one's start, so that the second would put a wavefront
+// beside one of the first and leave a SIMD idle.  Such workgroups are launched with four wavefronts, one per SIMD, of which two stay: those of
+// SIMDs 0 and 1 in the workgroup whose LDS starts at 0, of SIMDs 2 and 3 in the other.  Only the speed depends on it: of any four the two with the
+// smallest keys stay.  Returns the place among those that stay; NW or more: not one of them.
+template <int NW>
+__device__ __forceinline__ int wavefront_place(uint32_t* slots) {
+  if (NW != 2 || blockDim.x == 64u * NW) return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  constexpr int HW_SIMD_ID = 4 | (4 << 6) | (1 << 11), LDS_BASE = 6 | (0 << 6) | (11 << 11);      // hardware registers: HW_ID bits 4..5, LDS_ALLOC bits 0..11
+  const uint32_t i = threadIdx.x >> 6, simd = (uint32_t)__builtin_amdgcn_s_getreg(HW_SIMD_ID), half = __builtin_amdgcn_s_getreg(LDS_BASE) != 0 ? 1u : 0u;
+  const uint32_t key = 4u * ((simd >> 1) ^ half) + i;
+  if ((threadIdx.x & 63u) == 0u) slots[i] = key;
+  __syncthreads();
+  int place = 0;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) place += slots[k] < key ? 1 : 0;
+  __syncthreads();
+  return __builtin_amdgcn_readfirstlane(place);
+}
+
 template <class S>
-__global__ __launch_bounds__(S::NT) __attribute__((amdgpu_waves_per_eu(S::OCC, S::OCC)))
+__global__ __launch_bounds__(S::PLACED ? 256 : S::NT) __attribute__((amdgpu_waves_per_eu(S::OCC, S::OCC)))
 void rollout_quad_kernel(const QuadArgs a) {
   using namespace quad;
   using O = typename S::O;
@@ -232,8 +258,12 @@ void rollout_quad_kernel(const QuadArgs a) {
   constexpr bool BF16 = S::BF16, NORM = S::NORM, SPREAD = S::SPREAD;
   constexpr int NW = S::NW, NT = S::NT, KG = S::KG, M = S::M, HID = S::HID, HG = S::HG, KGA = S::KGA, NR = S::NR, GR = S::GR, COLS = S::COLS;
   extern __shared__ __align__(16) unsigned char lds[];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int w = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = threadIdx.x & 63;
+  const int w = NW == 1 ? 0 : S::PLACED ? wavefront_place<NW>(reinterpret_cast<uint32_t*>(lds)) : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  if (S::PLACED && w >= NW) return;
+  const int tid = S::PLACED ? 64 * w + lane : (int)threadIdx.x;
+  int threads = S::PLACED ? NT : (int)blockDim.x;
+  if constexpr (S::PLACED) asm volatile("" : "+s"(threads));      // (kept from the compiler, which would unroll the staging loops: 25 us of instruction misses)
   const int blk = lane >> 2, x = lane & 3;
   const bool p = (x & 1) != 0, q = (x & 2) != 0;
   const uint32_t psel = p ? 0x03020706u : 0x05040100u;
@@ -250,13 +280,13 @@ void rollout_quad_kernel(const QuadArgs a) {
   V4 Ae[KG], Be[KGA];
   static_for<0, KG / GR>([&](auto rc) {
     constexpr int r = decltype(rc)::value;
-    stage_cols<COLS, false>(win, S::PWIN, S::ENV_ROWS, no, no, COLS * r, a.A, NoiseRow{}, 0.0f, 0u);
+    stage_cols<COLS, false>(win, S::PWIN, S::ENV_ROWS, no, no, COLS * r, a.A, NoiseRow{}, 0.0f, 0u, tid, threads);
     stage_sync();
 #pragma unroll
     for (int g = 0; g < GR; ++g) Ae[GR * r + g] = win_group(erow, S::PWIN, g);
     stage_sync();
   });
-  stage_cols<4 * KGA, false>(win, S::PWIN, S::ENV_ROWS, no, na, 0, a.B, NoiseRow{}, 0.0f, 0u);
+  stage_cols<4 * KGA, false>(win, S::PWIN, S::ENV_ROWS, no, na, 0, a.B, NoiseRow{}, 0.0f, 0u, tid, threads);
   stage_sync();
 #pragma unroll
   for (int g = 0; g < KGA; ++g) Be[g] = win_group(erow, S::PWIN, g);
@@ -303,7 +333,7 @@ void rollout_quad_kernel(const QuadArgs a) {
     }
     static_for<0, KG / GR>([&](auto rc) {
       constexpr int r = decltype(rc)::value;
-      stage_cols<COLS, true>(win, S::PWIN, HID, nh, no, COLS * r, a.theta, nz, scale, a.oW1);
+      stage_cols<COLS, true>(win, S::PWIN, HID, nh, no, COLS * r, a.theta, nz, scale, a.oW1, tid, threads);
       stage_sync();
 #pragma unroll
       for (int g = 0; g < GR; ++g) W1[GR * r + g] = win_group(unit, S::PWIN, g);
@@ -313,14 +343,14 @@ void rollout_quad_kernel(const QuadArgs a) {
       constexpr int l = decltype(lc)::value;
       static_for<0, HG / GR>([&](auto rc) {
         constexpr int r = decltype(rc)::value;
-        stage_cols<COLS, true>(win, S::PWIN, HID, nh, nh, COLS * r, a.theta, nz, scale, a.oW2 + (uint32_t)l * (uint32_t)(nh * nh + nh));
+        stage_cols<COLS, true>(win, S::PWIN, HID, nh, nh, COLS * r, a.theta, nz, scale, a.oW2 + (uint32_t)l * (uint32_t)(nh * nh + nh), tid, threads);
         stage_sync();
 #pragma unroll
         for (int g = 0; g < GR; ++g) Wh[l][GR * r + g] = win_group(unit, S::PWIN, g);
         stage_sync();
       });
     });
-    stage_cols<HID, true>(win, S::PW3, S::NA, na, nh, 0, a.theta, nz, scale, a.oW3);
+    stage_cols<HID, true>(win, S::PW3, S::NA, na, nh, 0, a.theta, nz, scale, a.oW3, tid, threads);
     stage_sync();
     if constexpr (S::HALVES) {   // lane = action row, and a half of the wavefront's K groups in either half of the lanes
 #pragma unroll
@@ -385,6 +415,7 @@ void rollout_quad_kernel(const QuadArgs a) {
       // one row (unit) per lane, a register per copy -> operand
       auto operand = [&](const float (&v)[NC]) {
         if constexpr (NC == 1) return O::gather(v[0]);
+        else if constexpr (NC == 2) return O::transpose2(v[0], v[1], p, psel);
         else return O::transpose(f32x4{v[0], v[1], v[2], v[3]}, p, q, psel);
       };
       auto publish = [&] {       // s -> operand (own registers, or the exchange buffer)
@@ -535,7 +566,7 @@ void rollout_quad_kernel(const QuadArgs a) {
           }
           sync();
           float pv[S::NP][RPL];
-          const float* src = pb + (S::ROWS_COPY ? x * S::PP + RPL * blk : lane);
+          const float* src = pb + (S::ROWS_COPY ? (x & (NC - 1)) * S::PP + RPL * blk : lane);
 #pragma unroll
           for (int ww = 0; ww < S::NP; ++ww) {
             if constexpr (S::ROWS_COPY && RPL == 2) { const f32x2 v2 = *reinterpret_cast<const f32x2*>(src + ww * NC * S::PP); pv[ww][0] = v2.x; pv[ww][1] = v2.y; }
@@ -687,7 +718,9 @@ int launch_quad_shape(es_ctx* ctx, QuadArgs a, float* fitness, hipStream_t st) {
   a.split = quad_split(a.N, (a.E + (uint32_t)S::NC - 1u) / (uint32_t)S::NC, slots);
   a.fitness = a.split == 1u ? fitness : nullptr;
   const uint32_t grid = std::min<uint32_t>(a.N * a.split, slots);
-  hipLaunchKernelGGL(rollout_quad_kernel<S>, dim3(grid), dim3(S::NT), S::LDS_BYTES, st, a);
+  const uint32_t cus = (uint32_t)std::max(1, ctx->num_cus);
+  const bool place = S::PLACED && grid > cus && grid <= 2u * cus;
+  hipLaunchKernelGGL(rollout_quad_kernel<S>, dim3(grid), dim3(place ? 256 : S::NT), S::LDS_BYTES, st, a);
   int rc = check_launch(ctx, "es_rollout (passes of four copies)");
   if (rc != ES_OK || a.split == 1u) return rc;
   return launch_fitness(ctx, a.returns, fitness, st);
@@ -707,9 +740,17 @@ int launch_quad_options(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStrea
 }
 // obs <= 64: the width class (in binary32, where a group of four costs four instructions twice a step, one more class;
 // observation statistics only in the widest) and the number of copies of a pass
+// Copies of a pass: as few as the chip can take side by side, one wavefront per SIMD, since the activations of a copy are on the chain of a step.
+// Per 100 steps of bf16 27-100-100-8, four copies a pass / as chosen: 128 individuals x 2 copies 97 / 75 us (one), 128 x 3 97 / 84 (one), 128 x 5 100 / 87
+// (two), 512 x 2 127 / 85 (two; 42 us of it wavefront_place), 8-256-256-2 64 x 8 129 / 118 (two).
 template <bool BF16, int NW, int KG, int M, bool WITH_NORM, bool NEAR>
 int launch_quad_copies(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st) {
-  return a.E == 1 ? launch_quad_options<BF16, NW, KG, M, 1, WITH_NORM, NEAR>(ctx, a, fitness, st) : launch_quad_options<BF16, NW, KG, M, 4, WITH_NORM, NEAR>(ctx, a, fitness, st);
+  auto apart = [&](uint32_t nc) { return (uint64_t)a.N * ((a.E + nc - 1u) / nc) * NW <= 4u * (uint64_t)ctx->num_cus; };
+  if (a.E == 1u || apart(1u)) return launch_quad_options<BF16, NW, KG, M, 1, WITH_NORM, NEAR>(ctx, a, fitness, st);
+  if constexpr (BF16 && M <= 2) {
+    if (a.E == 2u || apart(2u)) return launch_quad_options<BF16, NW, KG, M, 2, WITH_NORM, NEAR>(ctx, a, fitness, st);
+  }
+  return launch_quad_options<BF16, NW, KG, M, 4, WITH_NORM, NEAR>(ctx, a, fitness, st);
 }
 template <bool BF16, int NW, int M, bool NEAR>
 int launch_quad_obs64(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st) {

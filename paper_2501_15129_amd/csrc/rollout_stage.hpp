@@ -53,21 +53,22 @@ __device__ __forceinline__ void put1(float* dst, float v) { *dst = v; }
 
 // Fill dst[r * pitch + c] for r < rows_p, c < COLS with the source value of matrix element (r, kbase + c) when
 // r < rows and kbase + c < cols, and zero elsewhere.
+// By `step` threads, this one being `tid` of them.
 // PERTURB: value = fma(scale, noise[idx], theta[idx]) with idx = off + r * cols + (kbase + c).
 // The loads of STAGE_BATCH iterations are issued together and unconditionally (a masked-out element reads the
 // matrix's first entries instead, which are always there), and only then consumed: a load inside the bounds test
 // would be waited for in its own iteration, and the round would cost one memory latency per iteration.
 template <int COLS, bool PERTURB, class Elem>
 __device__ __forceinline__ void stage_cols(Elem* dst, int pitch, int rows_p, int rows, int cols, int kbase,
-                                           const float* __restrict__ src, const NoiseRow nz, float scale, uint32_t off) {
+                                           const float* __restrict__ src, const NoiseRow nz, float scale, uint32_t off,
+                                           const int tid = (int)threadIdx.x, const int step = (int)blockDim.x) {
   constexpr int U = STAGE_BATCH;
-  const int step = (int)blockDim.x;
   if (((cols | (int)off | kbase) & 3) == 0) {
     // four consecutive columns per thread: 16-byte parameter loads, 8/16-byte noise loads, vector LDS stores
     constexpr int C4 = COLS / 4;
     const int total = rows_p * C4;
     auto batch = [&](auto fetch) {
-      for (int q0 = threadIdx.x; q0 < total; q0 += U * step) {
+      for (int q0 = tid; q0 < total; q0 += U * step) {
         f32x4 tv[U];
         decltype(fetch(0u)) ev[U];
         bool ok[U];
@@ -100,7 +101,7 @@ __device__ __forceinline__ void stage_cols(Elem* dst, int pitch, int rows_p, int
     // unrolled: its body is two hundred instructions, and the staging code should stay in the instruction cache
     if (PERTURB && nz.mode >= 2u) {
 #pragma unroll 1
-      for (int q = threadIdx.x; q < total; q += step) {
+      for (int q = tid; q < total; q += step) {
         const int r = q / C4, c = (q % C4) * 4, k = kbase + c;
         f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
         if (r < rows && k < cols) {
@@ -124,7 +125,7 @@ __device__ __forceinline__ void stage_cols(Elem* dst, int pitch, int rows_p, int
   // rows that are not multiples of four long: one column per thread
   const int total = rows_p * COLS;
   auto batch = [&](auto fetch) {
-    for (int q0 = threadIdx.x; q0 < total; q0 += U * step) {
+    for (int q0 = tid; q0 < total; q0 += U * step) {
       float tv[U];
       decltype(fetch(0u)) ev[U];
       bool ok[U];
@@ -152,7 +153,7 @@ __device__ __forceinline__ void stage_cols(Elem* dst, int pitch, int rows_p, int
     // one counter block gives four consecutive parameters: per row, the aligned groups of four that cover its columns
     constexpr int G = COLS / 4 + 1;
 #pragma unroll 1
-    for (int q = threadIdx.x; q < rows_p * G; q += step) {
+    for (int q = tid; q < rows_p * G; q += step) {
       const int r = q / G;
       const uint32_t first = off + (uint32_t)r * (uint32_t)cols + (uint32_t)kbase, g0 = (first & ~3u) + 4u * (uint32_t)(q % G);
       const int k0 = (int)(g0 - first);
