@@ -23,8 +23,9 @@
 // Bound: the dependent chain of a step when a few individuals are evaluated; with a full chip, matrix-core issue
 // (8.5 cycles per 4x4 instruction, measured) plus the vector work of the activations (5.8 cycles per instruction of a
 // lone wavefront).
-// Measured, whole rollout, T = 1000 unless noted: bf16 8-256-256-2, 128 individuals x 1 copy 1.23 ms (padded 16-column
-// kernel) -> 0.77 ms, x 4 copies 1.23 -> 1.01 ms; bf16 27-100-100-8, 128 x 5 copies, T = 400: 8.05 ms (LDS kernel) -> 0.35 ms.
+// Measured, whole rollout, T = 1000 unless noted: bf16 8-256-256-2, 128 individuals x 1 copy 1.23 ms (padded 16-column kernel) -> 0.77 ms -> 0.74 with
+// the books and the two branches of a step's end behind the loop; bf16 27-100-100-8, 128 x 5 copies, T = 400: 8.05 ms (LDS kernel) -> 0.34 ms -> 0.27 with
+// passes of two copies on SIMDs of their own.
 #pragma once
 
 #include <type_traits>
@@ -456,9 +457,12 @@ void rollout_quad_kernel(const QuadArgs a) {
       }
 
       const f32x4 zero4 = f32x4{0.f, 0.f, 0.f, 0.f};
-      // (one taken branch per step, the loop's own: each costs a lone wavefront some seventy cycles of instruction fetch)
-      uint32_t t = 0u;
+      // One branch per step, the loop's own: a taken one costs a lone wavefront some seventy cycles of instruction fetch, and its condition is one scalar
+      // (the end of a copy, or of the horizon); what follows from it stands behind the loop, which is entered again while copies run.
+      uint32_t t = 0u, stop, seen = 0u;      // seen: SPREAD, copies ended by any row so far
+      unsigned long long over[NC];
       while (true) {
+      do {
 #pragma unroll
         for (int c = 0; c < NC; ++c) { pin_sgpr(ninv[c]); pin_sgpr(thr[c]); if (!S::ROWS_COPY) pin_sgpr(ncost[c]); }
         // (two wait states must lie between instructions on one accumulator: two accumulators alternate)
@@ -623,7 +627,7 @@ void rollout_quad_kernel(const QuadArgs a) {
 #pragma unroll
         for (int c = 0; c < NC; ++c) s[c] = tanh_b<S::NEAR>(accE[0][c] + accE[1][c], 0.0f);       // padded rows: tanh(0) = 0
         // ---- termination: max |s| > threshold ends a copy after this step ----
-        unsigned long long over[NC], any = 0ull;
+        unsigned long long any = 0ull;
 #pragma unroll
         for (int c = 0; c < NC; ++c) { over[c] = __ballot(fabsf(s[c]) > thr[c]); any |= over[c]; }
         if constexpr (SPREAD) {
@@ -635,7 +639,6 @@ void rollout_quad_kernel(const QuadArgs a) {
           }
         }
         publish();
-        uint32_t seen = 0u;                // SPREAD: copies ended by any row so far
         if constexpr (SPREAD) {
           sync();
           fetch_state();
@@ -645,25 +648,27 @@ void rollout_quad_kernel(const QuadArgs a) {
           seen = uniform(f) & alive;
         }
         ++t;
-        if (__builtin_expect((SPREAD ? seen != 0u : any != 0ull) || t == a.T, 0)) {
-          uint32_t ended = seen;
-          if constexpr (!SPREAD) {
+        asm volatile("s_cmp_eq_u32 %1, %2\n\ts_cselect_b32 %0, 1, 0" : "=s"(stop) : "s"(t), "s"(a.T) : "scc");      // (scalar: the compiler makes masks of it)
+        stop |= SPREAD ? seen : (uint32_t)any | (uint32_t)(any >> 32);
+      } while (stop == 0u);
+        // ---- some copy ended, or all with the horizon ----
+        uint32_t ended = seen;
+        if constexpr (!SPREAD) {
 #pragma unroll
-            for (int c = 0; c < NC; ++c) ended |= over[c] != 0ull ? 1u << c : 0u;
-            ended = uniform(ended & alive);
-          }
-#pragma unroll
-          for (int c = 0; c < NC; ++c) {
-            const bool end = (ended >> c & 1u) != 0u;
-            len[c] = (int)uniform(end ? t : (uint32_t)len[c]);
-            ninv[c] = uniform(end ? 0.0f : ninv[c]);
-            ncost[c] = uniform(end ? 0.0f : ncost[c]);
-            thr[c] = uniform(end ? __builtin_inff() : thr[c]);
-          }
-          alive &= ~ended;
-          if (((alive >> x) & 1u) == 0u) xcost = 0.0f;
-          if (alive == 0u || t == a.T) break;
+          for (int c = 0; c < NC; ++c) ended |= over[c] != 0ull ? 1u << c : 0u;
+          ended = uniform(ended & alive);
         }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+          const bool end = (ended >> c & 1u) != 0u;
+          len[c] = (int)uniform(end ? t : (uint32_t)len[c]);
+          ninv[c] = uniform(end ? 0.0f : ninv[c]);
+          ncost[c] = uniform(end ? 0.0f : ncost[c]);
+          thr[c] = uniform(end ? __builtin_inff() : thr[c]);
+        }
+        alive &= ~ended;
+        if (((alive >> x) & 1u) == 0u) xcost = 0.0f;
+        if (alive == 0u || t == a.T) break;
       }
       // ---- outputs of this pass: return = length + the lanes' shares ----
       const uint32_t cnt = min((uint32_t)NC, a.E - (uint32_t)NC * pass);
