@@ -14,7 +14,8 @@ MICRO_LIB = HERE / "libes_microbench.so"
 # (the longest compilations first)
 SOURCES = ["rollout_quad_f32_mid.hip", "rollout_mfma.hip", "rollout_quad_bf16_mid4.hip", "rollout_quad_bf16_deep4.hip", "rollout_quad_f32_wide.hip",
            "rollout_quad_bf16_mid3.hip", "rollout_quad_bf16_deep3.hip", "rollout_quad_bf16_wide.hip", "rollout_quad_bf16_mid.hip",
-           "rollout_wave_reg_deep.hip", "rollout_wave_team_f32.hip", "rollout_wave_team_bf16.hip", "rollout_single_mid.hip", "rollout_single_wide.hip", "rollout_cols_f32_64.hip", "rollout_cols_f32_48.hip", "rollout_cols_f32_small.hip", "rollout_cols_bf16.hip",
+           "rollout_wave_reg_deep.hip", "rollout_wave_team_f32.hip", "rollout_wave_team_bf16.hip", "rollout_quad_obs256.hip", "rollout_quad_obs192.hip", "rollout_quad_obs128.hip",
+           "rollout_single_mid.hip", "rollout_single_wide.hip", "rollout_cols_f32_64.hip", "rollout_cols_f32_48.hip", "rollout_cols_f32_small.hip", "rollout_cols_bf16.hip",
            "rollout_quad_narrow.hip", "rollout_wave_reg_bf16.hip", "rollout_wave_reg_f32.hip",
            "rollout_mfma_f32.hip", "rollout_wave_reg.hip", "api.hip", "sample.hip", "rank.hip", "update.hip", "rollout_wave.hip",
            "rollout_quad.hip"]

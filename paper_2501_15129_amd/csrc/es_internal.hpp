@@ -104,6 +104,9 @@ int launch_rollout_mfma_f32(es_ctx* ctx, uint32_t gen, const float* theta, const
 int launch_rollout_quad(es_ctx* ctx, uint32_t gen, const float* theta, const void* noise,
                         const float* A, const float* B, float* returns, int32_t* ep_len,
                         float* fitness, void* ws, hipStream_t st);
+// bf16, two layers, 65 .. 256 observations, up to 32 actions and four copies (launch_rollout_mfma)
+int launch_rollout_quad_spread(es_ctx* ctx, uint32_t gen, const float* theta, const void* noise, const float* A, const float* B, float* returns,
+                               int32_t* ep_len, float* fitness, hipStream_t st);
 bool quad_fits(const es_config& cfg, uint32_t copies, int cus);   // copies = episodes evaluated per individual
 std::string quad_variant_name(const es_config& cfg);
 bool mfma_f32_fits(const es_config& cfg);

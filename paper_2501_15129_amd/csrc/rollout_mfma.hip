@@ -81,7 +81,7 @@ constexpr int PH = NHP + 8;       // LDS pitch (bf16 elements) of a hidden activ
 constexpr int KC = 2;             // K tiles staged per round
 constexpr int PW = 32 * KC + 8;   // LDS pitch of the staging window
 
-template <int KT1_, int MT3_, int MTE_, int KTAR_, int NC_, int NW_, int OCC_ = 1, int ME_ = 0, bool ENVF_ = false, bool NEAR_ = false>
+template <int KT1_, int MT3_, int MTE_, int KTAR_, int NW_, int OCC_ = 1, int ME_ = 0, bool ENVF_ = false, bool NEAR_ = false>
 struct Variant {
   static constexpr bool NEAR = NEAR_;          // the tanh that is accurate near zero
   static constexpr bool ENVF = ENVF_;          // the environment's products A s + B a stay binary32 (fp32 16x16x4 MFMAs, its own
@@ -93,7 +93,7 @@ struct Variant {
   static constexpr int NT = 64 * NW;          // threads per workgroup
   static constexpr int MT_H = NHP / (16 * NW);   // 16-row tiles of a wide layer per wavefront
   static constexpr int ENV_ROWS = 16 * NW * MTE_;   // padded rows of the next-state vector covered by the workgroup
-  static constexpr int NC = NC_;              // environment copies per pass: 16, or 4 with column compaction
+  static constexpr int NC = 16;               // environment copies per pass
   static constexpr int KT1 = KT1_;            // K tiles over the (padded) observation width
   static constexpr int MT3 = MT3_;            // 16-row tiles of the action layer
   static constexpr int MTE = MTE_;            // 16-row tiles of the next-state vector per wavefront
@@ -129,38 +129,26 @@ struct Variant {
   static constexpr int OFF_X0P = OFF_XP + 2 * NC * PX;
   static constexpr int OFF_MU = OFF_X0P + 2 * NC * PX;
   static constexpr int OFF_IV = OFF_MU + 4 * NOP;
-  // passes of four copies with the action layer split along K (FUSE3): the second state buffer (steps alternate)
-  // and the binary32 partial sums of the action layer [wavefront][copy][32 action rows]
-  static constexpr bool FUSE3 = NC_ == 4;
-  static constexpr int OFF_X1 = OFF_IV + 4 * NOP;
-  static constexpr int OFF_P3 = OFF_X1 + (FUSE3 ? 2 * NC * PX : 0);
+  // binary32 partial sums of the action layer, which is split along K: [wavefront][copy][PP3 rows]
+  static constexpr int OFF_P3 = OFF_IV + 4 * NOP;
   // binary32 environment: the state as binary32 [copy][state index] (pitch PXF floats: 16-byte reads of 16 lanes hit
   // distinct banks), working buffer and cached initial value
   static constexpr int KPL = NOP / 4;          // state elements per lane group of the fp32 MFMA's K dimension
   static constexpr int PXF = NOP + 4;
-  // passes of sixteen copies (KSPLIT16): the same K split of the action layer, at any depth; every lane keeps its four tiles of
-  // the last hidden layer for its own column, so they feed the MFMA with no lane exchange at all.
-  // Partials [wavefront][copy][PP3 rows].
-  static constexpr bool KSPLIT16 = NC_ == 16;
   static constexpr int PP3 = 16 * MT3_ + 4;    // pitch (floats) of a copy's partial rows: 16-byte accesses of 16 lanes spread over the banks
-  static constexpr int OFF_XF = OFF_P3 + (FUSE3 ? 4 * NW * NC * 32 : KSPLIT16 ? 4 * NW * 16 * PP3 : 0);
+  static constexpr int OFF_XF = OFF_P3 + 4 * NW * NC * PP3;
   static constexpr int OFF_X0F = OFF_XF + (ENVF ? 4 * NC * PXF : 0);
-  // With all of A in registers the step loop has under a hundred working registers left: B and this wavefront's slice
-  // of the action-layer weights then stay in LDS and are fetched where they are used (a dozen reads per step).
-  static constexpr bool SMALL_LDS = FUSE3 && KTAR_ >= KT1_ && KT1_ >= 8;
   static constexpr int OFF_BL = OFF_X0F + (ENVF ? 4 * NC * PXF : 0);      // B [ENV_ROWS][PA] bf16
-  // ... as with four hidden layers, which leave four registers too few for everything
-  static constexpr bool B_LDS = SMALL_LDS || ME_ == 2;
+  // four hidden layers leave four registers too few for everything: B then stays in LDS
+  static constexpr bool B_LDS = ME_ == 2;
   static constexpr int LDS_BYTES = OFF_BL + (B_LDS ? 2 * ENV_ROWS * PA : 0);
-  static_assert(!ENVF || (NC == 16 && ME == 0 && MT3 == 1 && KT1 <= 2), "binary32 environment: passes of 16 copies, two hidden layers, obs <= 64, act <= 16");
+  static_assert(!ENVF || (ME == 0 && MT3 == 1 && KT1 <= 2), "binary32 environment: passes of 16 copies, two hidden layers, obs <= 64, act <= 16");
   static_assert(ENV_ROWS >= NOP, "the wavefronts must cover the padded state");
   static_assert(ENV_ROWS <= 256, "staging window rows");
   static_assert(NW == 4, "one wavefront per SIMD (two per SIMD, each with half of the rows, measured slower at every shape)");
   static_assert(MT_H >= 1 && MT_H <= 4, "wide-layer tiles per wavefront");
   static_assert(NAP >= 16 * MT3 && KTA <= KC, "action K padding");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS budget");
-  static_assert(NC == 4 || NC == 16, "columns per pass");
-  static_assert(NC == 16 || ME == 0, "passes of four copies: two hidden layers");
   static_assert(ME <= 0 || (OCC == 1 && KTAL == 0), "deeper policies need the whole register file of the CU");
   static_assert(ME >= 0 || KTAL == 0, "the single-layer variant keeps all of A in registers");
   static_assert(MT3 <= 2 && MT3 <= 4, "action tiles: one wavefront each, partial layout holds two");
@@ -203,40 +191,6 @@ __device__ __forceinline__ f32x4 hidden4(f32x4 v) {
   return tanh4<NEAR>(v);
 }
 
-// Column compaction for passes of 4 environment copies: the MFMA result tile has 16 columns
-// of which only 0..3 are real.  Lanes of bank q (columns 4q..4q+3) fetch tile q's values of
-// columns 0..3 with a row shift, so that the tanh epilogue runs once per lane, not once per tile.
-template <int CTRL, int BANK>
-__device__ __forceinline__ float dpp_take(float keep, float from) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, keep), __builtin_bit_cast(int, from),
-                                                                CTRL, 0xF, BANK, false));
-}
-template <int NT>
-__device__ __forceinline__ f32x4 compact4(const f32x4 (&t)[NT]) {
-  f32x4 v = t[0];
-  // (register by register within each step: a register's next move is then four instructions away)
-#pragma unroll
-  for (int r = 0; r < 4 && NT > 1; ++r) v[r] = dpp_take<0x114, 0x2>(v[r], t[NT > 1 ? 1 : 0][r]);   // row_shr:4  -> columns 4..7
-#pragma unroll
-  for (int r = 0; r < 4 && NT > 2; ++r) v[r] = dpp_take<0x118, 0x4>(v[r], t[NT > 2 ? 2 : 0][r]);   // row_shr:8  -> columns 8..11
-#pragma unroll
-  for (int r = 0; r < 4 && NT > 3; ++r) v[r] = dpp_take<0x11C, 0x8>(v[r], t[NT > 3 ? 3 : 0][r]);   // row_shr:12 -> columns 12..15
-  return v;
-}
-
-// Sum over the four banks of a 16-lane row (lanes c, c+4, c+8, c+12), result in lanes 0..3.
-template <int CTRL>
-__device__ __forceinline__ float dpp_shl(float v) {   // lane i <- lane i + n within the row, 0 past the end
-  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
-}
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_shl_u(uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true);
-}
-__device__ __forceinline__ float row_bank_sum(float v) {
-  v = v + dpp_shl<0x104>(v);
-  return v + dpp_shl<0x108>(v);
-}
 // Sum over the four 16-lane rows of the wavefront (lanes l, l+16, l+32, l+48), result in
 // every row, by the row-swap instructions of gfx950 (vector ALU speed, no LDS round trip).
 __device__ __forceinline__ float rows_sum(float v) {
@@ -273,8 +227,6 @@ void rollout_mfma_kernel(const MfmaArgs a) {
   if constexpr (!ENV_ALL && V::OCC == 2) w = (w + ((__builtin_amdgcn_s_getreg(LDS_BASE_REG) != 0) ? NW - 1 : 0)) % NW;
   const bool env_wave = ENV_ALL || 16 * w * MTE < V::NOP;      // has next-state tiles
   const int g = lane >> 4, n = lane & 15;
-  const int col = n & (NC - 1);      // environment copy (column) this lane reads and keeps books for
-  const int q = n >> 2;              // NC == 4: which tile this lane finishes after compaction
   uint16_t* stage = reinterpret_cast<uint16_t*>(lds);
   float* b1s = reinterpret_cast<float*>(lds + V::OFF_B1);
   float* b2s = reinterpret_cast<float*>(lds + V::OFF_B2);
@@ -341,20 +293,11 @@ void rollout_mfma_kernel(const MfmaArgs a) {
   } else if constexpr (!ENVF) {
     stage_cols<32 * KC, false>(stage, PW, V::ENV_ROWS, no, na, 0, a.B, NoiseRow{}, 0.0f, 0u);
     __syncthreads();
+    // K slot j < 4 of lane group g stands for action row 4g + j, slot j >= 4 for row 16 + 4g + (j - 4) of the second
+    // action tile (padding when there is one tile) - the rows whose sums the lane holds after the action layer: the
+    // action goes from those registers into the MFMA
 #pragma unroll
-    for (int t = 0; t < MTE; ++t)
-#pragma unroll
-      for (int kt = 0; kt < KTA; ++kt)
-        Br[t][kt] = lds_tile(lds, 2 * ((16 * (w * MTE + t) + n) * PW + 32 * kt + 8 * g));
-    if constexpr (V::KSPLIT16) {
-      // K slot j < 4 of lane group g stands for action row 4g + j, slot j >= 4 for row 16 + 4g + (j - 4) of the second
-      // action tile (padding when there is one tile) - the rows whose sums the lane holds after the action layer: the
-      // action goes from those registers into the MFMA
-#pragma unroll
-      for (int t = 0; t < MTE; ++t) {
-        Br[t][0] = b_slots(lds + 2 * ((16 * (w * MTE + t) + n) * PW + 4 * g));
-      }
-    }
+    for (int t = 0; t < MTE; ++t) Br[t][0] = b_slots(lds + 2 * ((16 * (w * MTE + t) + n) * PW + 4 * g));
     __syncthreads();
   }
 
@@ -454,11 +397,11 @@ void rollout_mfma_kernel(const MfmaArgs a) {
       if constexpr (ME > 0) stage_deeper(std::integral_constant<int, 0>());
       if constexpr (ME > 1) stage_deeper(std::integral_constant<int, 1>());
 
-      // FUSE3: this wavefront's K slice (its own 64 hidden units) of the action-layer weights, as MFMA A operands.  The K
+      // This wavefront's K slice (its own 64 hidden units) of the action-layer weights, as MFMA A operands.  The K
       // order inside a tile follows the order in which the lane holds h2 after the layer-2 epilogue: slots 0..3 = units
       // 4g..4g+3 of the even 16-unit tile, slots 4..7 = the same rows of the odd tile (any K order is as good as another
       // as long as both operands agree), so h2 goes from the epilogue's registers into the MFMA with no exchange.
-      bf16x8 W3k[(V::FUSE3 || V::KSPLIT16) ? MT3 : 1][2];
+      bf16x8 W3k[MT3][2];
       auto w3k_tile = [&](int mt, int kk) {
         const unsigned char* src = lds + V::OFF_W3 + 2 * ((16 * mt + n) * PH + 64 * w + 32 * kk + 4 * g);
         const u32x2 lo = *reinterpret_cast<const u32x2*>(src), hi = *reinterpret_cast<const u32x2*>(src + 2 * 16);
@@ -466,7 +409,7 @@ void rollout_mfma_kernel(const MfmaArgs a) {
       };
       // ... held in registers where the file has room for them; fetched from LDS at their use otherwise (all of A in
       // registers, two workgroups per CU, more than two hidden layers)
-      constexpr bool W3K_REGS = (V::FUSE3 && !V::SMALL_LDS) || (V::KSPLIT16 && ME < 2);
+      constexpr bool W3K_REGS = ME < 2;
       if constexpr (W3K_REGS) {
 #pragma unroll
         for (int mt = 0; mt < MT3; ++mt)
@@ -522,7 +465,7 @@ void rollout_mfma_kernel(const MfmaArgs a) {
         }
         __syncthreads();
 
-        const uint32_t e = cb * (uint32_t)NC + (uint32_t)col;
+        const uint32_t e = cb * (uint32_t)NC + (uint32_t)n;
         uint32_t alive_cols = (1u << min((uint32_t)NC, a.E - cb * (uint32_t)NC)) - 1u;      // columns still running, the same in all wavefronts
         bool add = false;        // the previous step counts for this lane's column
         float Rn = 0.0f;
@@ -542,10 +485,10 @@ void rollout_mfma_kernel(const MfmaArgs a) {
         // lanes that write a partial (one per column) write it to its place, the others to the scratch: no branch
         float* const ss_out = reinterpret_cast<float*>(lds + (lane < NC ? V::OFF_SSP + 4 * (lane * NW + w) : V::OFF_SCR + 4 * tid));
         // shares -> the wavefront's partial of |s_t|^2: while the layer-1 stream waits for its first tiles
-        auto books_norm = [&] { *ss_out = rows_sum(NC == 4 ? row_bank_sum(ssp) : ssp); };
+        auto books_norm = [&] { *ss_out = rows_sum(ssp); };
         // the reward of step t - 1: between the instructions of the stream's second stage
         auto books_reward = [&] {
-          const float aa = rows_sum(NC == 4 ? part + dpp_shl<0x104>(part) : part);      // four copies: rows 8g..8g+7 of a column are in lanes c, c + 4
+          const float aa = rows_sum(part);
           const float r = __fmaf_rn(-ss_cur, inv_no, 1.0f) - a.act_cost * aa;
           Rn += add ? r : 0.0f;
 #pragma unroll
@@ -562,9 +505,9 @@ void rollout_mfma_kernel(const MfmaArgs a) {
         // (rare) these columns end with t steps, all of them after the last step
         auto end_columns = [&](uint32_t seen, uint32_t t) {
           const uint32_t ended = t == a.T ? alive_cols : seen;
-          Ln = (ended >> col & 1u) ? (int32_t)t : Ln;
+          Ln = (ended >> n & 1u) ? (int32_t)t : Ln;
           alive_cols &= ~ended;
-          add = (alive_cols >> col & 1u) != 0u;
+          add = (alive_cols >> n & 1u) != 0u;
           stop = a.T;
         };
         *ss_out = 0.0f;           // (wavefronts without next-state tiles write no partial)
@@ -573,7 +516,6 @@ void rollout_mfma_kernel(const MfmaArgs a) {
           if (__builtin_expect(over != 0ull, 0)) {
             uint32_t m = (uint32_t)(over | over >> 32);
             m |= m >> 16;
-            if (NC == 4) { m |= m >> 8; m |= m >> 4; }
             if (lane == 0) flags[w] |= m;
           }
         };
@@ -583,10 +525,10 @@ void rollout_mfma_kernel(const MfmaArgs a) {
         unsigned long long prof_acc[12] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
         unsigned long long prof_last = __builtin_readcyclecounter();
 #endif
-        // KSPLIT16, after the last hidden layer: it stays in registers - the lane's values of tiles 0, 1 and of tiles 2, 3 are
+        // After the last hidden layer: it stays in registers - the lane's values of tiles 0, 1 and of tiles 2, 3 are
         // the two K tiles of this wavefront's slice of the action layer - and only the binary32 partial sums cross the LDS
         auto last_hidden_ksplit = [&](const f32x4 (&accs)[MT_H]) {
-          static_assert(!V::KSPLIT16 || MT_H == 4, "four hidden tiles per wavefront");
+          static_assert(MT_H == 4, "four hidden tiles per wavefront");
           if constexpr (!W3K_REGS) {      // requested ahead of the activation, which hides the latency
 #pragma unroll
             for (int mt = 0; mt < MT3; ++mt)
@@ -610,212 +552,6 @@ void rollout_mfma_kernel(const MfmaArgs a) {
           for (int mt = 0; mt < MT3; ++mt)
             *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(lds + V::OFF_P3) + (w * 16 + n) * V::PP3 + 16 * mt + 4 * g) = p3[mt];
         };
-        if constexpr (V::FUSE3) {
-        // Passes of four copies (FUSE3): the action layer is split along K.  Every wavefront multiplies
-        // the 64 units of h2 it has just produced - still in its registers - with its slice of the action-layer weights;
-        // only the binary32 partial sums [wavefront][copy][action row] cross the LDS, and every wavefront adds them in the
-        // same order.  h2 itself is never exchanged: three workgroup barriers per step instead of four, and no phase in
-        // which two wavefronts wait for the other two.  The state has two buffers (steps alternate) so that a wavefront
-        // may still read s_t while another already writes s_{t+1}.
-        float* p3s = reinterpret_cast<float*>(lds + V::OFF_P3);
-        const int qq = q & 1;                                  // this lane adds up action rows 8g + 4qq .. + 3 of column col
-        static_assert(V::NC != 4 || MT3 == 2, "32 action rows");
-        // A x (independent of the chain of layers) is issued in four portions of KP K tiles: between the vector instructions of the
-        // two activations, and on both sides of the first two barriers, where the wavefront would wait for the others and for the LDS
-        // (obs 244: 1.12 -> 1.04 ms; half of it used to lengthen the second layer's stream).
-        constexpr int KP = KT1 / 4;
-        static_assert(KT1 % 4 == 0, "portions of A x");
-        auto env_mfma = [&](int ka, int tt, bf16x8 xt) {
-          if (ENV_ALL || 16 * (w * MTE + tt) < V::NOP) {
-            if (ka < KTAR) { accE[tt] = mfma16(Ar[tt][ka < KTAR ? ka : 0], xt, accE[tt]); }
-            else accE[tt] = mfma16(lds_tile(lds, V::OFF_AL + 2 * ((16 * (w * MTE + tt) + n) * PAL + 32 * (ka - KTAR) + 8 * g)), xt, accE[tt]);
-          }
-        };
-        auto bar = [] { __builtin_amdgcn_sched_barrier(0); };
-        // a portion between vector instructions
-        auto mix = [&] {
-#pragma unroll
-          for (int r = 0; r < KP * MTE; ++r) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
-          }
-        };
-        for (uint32_t t = 0; t <= a.T; ++t) {
-          const int off_x = (t & 1u) ? V::OFF_X1 : V::OFF_X, off_xn = (t & 1u) ? V::OFF_X : V::OFF_X1;
-          // ---- phase A: h1 = act(W1 x + b1); books of the previous step ----
-          bf16x8 xk[2][KP], bxr[3];      // state tiles: of the portions of A x, and the ring of the layer-1 stream
-          auto xload = [&](int kt) { return lds_tile(lds, off_x + 2 * (col * PX + 32 * kt + 8 * g)); };
-          auto portion_load = [&](int p) {
-#pragma unroll
-            for (int k = 0; k < KP; ++k) xk[p & 1][k] = xload(p * KP + k);
-          };
-          auto portion = [&](int p, int from, int to) {      // instructions [from, to) of portion p
-#pragma unroll
-            for (int j = from; j < to; ++j) env_mfma(p * KP + j / MTE, j % MTE, xk[p & 1][j / MTE]);
-          };
-          auto xfetch = [&](int kt) {
-            if (NORM || kt >= KP) bxr[kt % 3] = NORM ? lds_tile(lds, V::OFF_XP + 2 * (col * PX + 32 * kt + 8 * g)) : xload(kt);
-            if (kt < KP) xk[0][kt < KP ? kt : 0] = xload(kt);
-          };
-#pragma unroll
-          for (int kt = 0; kt < 2; ++kt) xfetch(kt);
-          u32x4 fl;
-          uint32_t seen = 0u;
-          bar();
-          books_norm();
-          bar();
-#pragma unroll
-          for (int kt = 0; kt < KT1; ++kt) {
-            if (kt + 2 < KT1) xfetch(kt + 2);
-#pragma unroll
-            for (int tt = 0; tt < MT_H; ++tt) {
-              if (V::OCC == 1) pin_agpr(W1r[tt][kt]);
-              acc[tt] = mfma16(W1r[tt][kt], (!NORM && kt < KP) ? xk[0][kt < KP ? kt : 0] : bxr[kt % 3], acc[tt]);
-            }
-            if (kt == 0) fl = *reinterpret_cast<const u32x4*>(flags);
-            if (kt == 1) books_reward();
-            if (kt == 2) seen = flagged(fl);
-            if (kt == KT1 - 1) portion_load(1);
-            bar();
-          }
-          PSTAMP(0);
-          if (__builtin_expect((seen | ((t ^ stop) - 1u) >> 31) != 0u, 0)) {      // (t == stop, in scalar arithmetic) identical in all four wavefronts
-            end_columns(seen, t);
-            if (alive_cols == 0u) break;
-          }
-          PSTAMP(1);
-          bar();
-#pragma unroll
-          for (int tt = 0; tt < MTE; ++tt) accE[tt] = f32x4{0.f, 0.f, 0.f, 0.f};
-          portion(0, 0, KP * MTE);
-          {
-            const f32x4 h = hidden4<RELU, V::NEAR>(compact4<MT_H>(acc));
-            if (q < MT_H)
-              *reinterpret_cast<u32x2*>(lds + V::OFF_H1 + 2 * (col * PH + 16 * (w * MT_H + q) + 4 * g)) = pack_bf16x4(h.x, h.y, h.z, h.w);
-          }
-          mix();
-          bar();
-          PSTAMP(2);
-          // ---- phase B: h2 = act(W2 h1 + b2); then this wavefront's K slice of W3 h2 ----
-          portion(1, 0, KP * MTE / 2);
-          bar();
-#pragma unroll
-          for (int tt = 0; tt < MT_H; ++tt) acc[tt] = *reinterpret_cast<const f32x4*>(b2s + 16 * (w * MT_H + tt) + 4 * g);
-          __syncthreads();
-          PSTAMP(3);
-          {
-            bf16x8 bh[3];
-            auto fetch = [&](int kt) { bh[kt % 3] = lds_tile(lds, V::OFF_H1 + 2 * (col * PH + 32 * kt + 8 * g)); };
-            fetch(0);
-            fetch(1);
-            const f32x4 sp4 = *reinterpret_cast<const f32x4*>(lds + V::OFF_SSP + 4 * NW * col);
-            bar();
-            portion(1, KP * MTE / 2, KP * MTE);
-            bar();
-#pragma unroll
-            for (int kt = 0; kt < KT_H; ++kt) {
-              if (kt + 2 < KT_H) fetch(kt + 2);
-#pragma unroll
-              for (int tt = 0; tt < MT_H; ++tt) { pin_agpr(W2r[tt][kt]); acc[tt] = mfma16(W2r[tt][kt], bh[kt % 3], acc[tt]); }
-              if (kt == 2) norm_total(sp4);
-              if (kt == KT_H - 2) portion_load(2);
-              bar();
-            }
-          }
-          PSTAMP(4);
-          {
-            if constexpr (V::SMALL_LDS) {      // fetched here, ahead of the activation that hides the latency
-#pragma unroll
-              for (int mt = 0; mt < MT3; ++mt)
-#pragma unroll
-                for (int kk = 0; kk < 2; ++kk) W3k[mt][kk] = w3k_tile(mt, kk);
-            }
-            portion_load(3);
-            portion(2, 0, KP * MTE);
-            // h2 of this wavefront's 64 units stays in registers: lane (g, 4q + c) holds units 4g..4g+3 of tile q for copy c
-            const f32x4 h = hidden4<RELU, V::NEAR>(compact4<MT_H>(acc));
-            const u32x2 hp = pack_bf16x4(h.x, h.y, h.z, h.w);
-            // the lanes of the four real columns (n < 4) collect the other three tiles of their copy from the lanes to their right
-            const uint32_t s4x = dpp_shl_u<0x104>(hp.x), s4y = dpp_shl_u<0x104>(hp.y);
-            const uint32_t s8x = dpp_shl_u<0x108>(hp.x), s8y = dpp_shl_u<0x108>(hp.y);
-            const uint32_t scx = dpp_shl_u<0x10C>(hp.x), scy = dpp_shl_u<0x10C>(hp.y);
-            const bf16x8 bk0 = __builtin_bit_cast(bf16x8, u32x4{hp.x, hp.y, s4x, s4y});     // K tile of the wavefront's tiles 0, 1
-            const bf16x8 bk1 = __builtin_bit_cast(bf16x8, u32x4{s8x, s8y, scx, scy});       // ... and of tiles 2, 3
-            mix();
-            bar();
-            f32x4 p3[MT3];
-#pragma unroll
-            for (int mt = 0; mt < MT3; ++mt) p3[mt] = mfma16(W3k[mt][0], bk0, f32x4{0.f, 0.f, 0.f, 0.f});
-#pragma unroll
-            for (int mt = 0; mt < MT3; ++mt) p3[mt] = mfma16(W3k[mt][1], bk1, p3[mt]);
-            bar();
-            portion(3, 0, KP * MTE / 2);
-            bar();
-#pragma unroll
-            for (int mt = 0; mt < MT3; ++mt)
-              if (n < NC) *reinterpret_cast<f32x4*>(p3s + (w * NC + n) * 32 + 16 * mt + 4 * g) = p3[mt];
-          }
-          PSTAMP(5);
-          __syncthreads();
-          PSTAMP(6);
-          // ---- phase D: a = tanh(sum of the partials + b3); s' = tanh(A x + B a); norms for the reward and the termination test ----
-          const int r0 = 8 * g + 4 * qq;
-          f32x4 pv[NW];
-#pragma unroll
-          for (int ww = 0; ww < NW; ++ww) pv[ww] = *reinterpret_cast<const f32x4*>(p3s + (ww * NC + col) * 32 + r0);
-          const f32x4 b3v = *reinterpret_cast<const f32x4*>(b3s + r0);
-          bf16x8 ba, brt[MTE];
-          if constexpr (V::SMALL_LDS) {
-#pragma unroll
-            for (int tt = 0; tt < MTE; ++tt) brt[tt] = lds_tile(lds, V::OFF_BL + 2 * ((16 * (w * MTE + tt) + n) * V::PA + 8 * g));
-          } else {
-#pragma unroll
-            for (int tt = 0; tt < MTE; ++tt) brt[tt] = Br[tt][0];
-          }
-          bar();
-          portion(3, KP * MTE / 2, KP * MTE);
-          bar();
-          {
-            f32x4 v = b3v;
-#pragma unroll
-            for (int ww = 0; ww < NW; ++ww) v += pv[ww];
-            {      // branch-free: a select costs four instructions, the branch cost six register moves on the chain
-              const f32x4 tv = tanh4<V::NEAR>(v);
-              const bool squash = a.out_tanh != 0u;
-              v = f32x4{squash ? tv.x : v.x, squash ? tv.y : v.y, squash ? tv.z : v.z, squash ? tv.w : v.w};
-            }
-            part = v.x * v.x;
-            part = __fmaf_rn(v.y, v.y, part); part = __fmaf_rn(v.z, v.z, part); part = __fmaf_rn(v.w, v.w, part);
-            const u32x2 ap = pack_bf16x4(v.x, v.y, v.z, v.w);
-            const uint32_t a4x = dpp_shl_u<0x104>(ap.x), a4y = dpp_shl_u<0x104>(ap.y);
-            ba = __builtin_bit_cast(bf16x8, u32x4{ap.x, ap.y, a4x, a4y});      // action rows 8g..8g+7 of column n (n < 4)
-          }
-#pragma unroll
-          for (int tt = 0; tt < MTE; ++tt) accE[tt] = mfma16(brt[tt], ba, accE[tt]);
-          PSTAMP(7);
-          {
-            const int tile = w * MTE + q;
-            const bool valid = q < MTE && (ENV_ALL || 16 * tile < V::NOP);
-            const f32x4 sn = tanh4<V::NEAR>(compact4<MTE>(accE));
-            if (valid) {
-              *reinterpret_cast<u32x2*>(lds + off_xn + 2 * (col * PX + 16 * tile + 4 * g)) = pack_bf16x4(sn.x, sn.y, sn.z, sn.w);
-              if (NORM) {
-                const f32x4 xn = (sn - *reinterpret_cast<const f32x4*>(mus + 16 * tile + 4 * g)) * *reinterpret_cast<const f32x4*>(ivs + 16 * tile + 4 * g);
-                *reinterpret_cast<u32x2*>(lds + V::OFF_XP + 2 * (col * PX + 16 * tile + 4 * g)) = pack_bf16x4(xn.x, xn.y, xn.z, xn.w);
-              }
-            }
-            ssp = sn.x * sn.x;
-            ssp = __fmaf_rn(sn.y, sn.y, ssp); ssp = __fmaf_rn(sn.z, sn.z, ssp); ssp = __fmaf_rn(sn.w, sn.w, ssp);
-            if (MTE < 4 || !ENV_ALL) ssp = valid ? ssp : 0.0f;
-            flag_ended(exceeds(sn, a.done_thresh));      // (lanes without a tile of their own hold copies of a tile, or zeros)
-          }
-#pragma unroll
-          for (int tt = 0; tt < MT_H; ++tt) acc[tt] = *reinterpret_cast<const f32x4*>(b1s + 16 * (w * MT_H + tt) + 4 * g);
-          PSTAMP(9);
-          __syncthreads();
-          PSTAMP(10);
-        }
-        } else {
         // Two workgroups on a CU: the wavefronts of a SIMD compete for its issue slots, and left alone they fall into step, vector phase on vector
         // phase.  The short serial part of a step (sums of the partials, environment, first layer: few instructions and two hand-overs) goes before the
         // long ones, the first activation before the second layer's stream: whoever is late catches up, and the other's products and tanh fill
@@ -835,11 +571,11 @@ void rollout_mfma_kernel(const MfmaArgs a) {
           }
           // W1 stream: the B operand (state tiles) runs two stages ahead of the MFMAs
           bf16x8 bx[KA1 > 0 ? KA1 : 1], bxr[3];     // tiles < KA1 are kept for A x below; the rest pass through a ring
-          auto xload = [&](int kt) { return lds_tile(lds, V::OFF_X + 2 * (col * PX + 32 * kt + 8 * g)); };
+          auto xload = [&](int kt) { return lds_tile(lds, V::OFF_X + 2 * (n * PX + 32 * kt + 8 * g)); };
           // with observation statistics the policy reads the normalised state and A x the raw one
           auto xfetch = [&](int kt) {
             if (NORM) {
-              bxr[kt % 3] = lds_tile(lds, V::OFF_XP + 2 * (col * PX + 32 * kt + 8 * g));
+              bxr[kt % 3] = lds_tile(lds, V::OFF_XP + 2 * (n * PX + 32 * kt + 8 * g));
               if (kt < KA1) bx[kt < KA1 ? kt : 0] = xload(kt);
             } else if (kt < KA1) {
               bx[kt < KA1 ? kt : 0] = xload(kt);
@@ -921,21 +657,21 @@ void rollout_mfma_kernel(const MfmaArgs a) {
             bf16x8 bh[3], at[3 * (PS > 0 ? PS : 1)], bx2[KT1 - KA1 > 0 ? KT1 - KA1 : 1];
             // operands of stage kt are fetched two stages ahead: h1 tile, LDS-resident A tiles, state tiles
             auto fetch = [&](int kt) {
-              bh[kt % 3] = lds_tile(lds, V::OFF_H1 + 2 * (col * PH + 32 * kt + 8 * g));
+              bh[kt % 3] = lds_tile(lds, V::OFF_H1 + 2 * (n * PH + 32 * kt + 8 * g));
 #pragma unroll
               for (int r = 0; r < PS; ++r) {
                 const int j = kt * PS + r;
                 if (j < NT2) {
                   const int ka = KA1 + j / MTE, tt = j % MTE;
                   if (ka >= KTAR) at[(kt % 3) * PS + r] = lds_tile(lds, V::OFF_AL + 2 * ((16 * (w * MTE + tt) + n) * PAL + 32 * (ka - KTAR) + 8 * g));
-                  if (tt == 0 || r == 0) bx2[ka - KA1] = lds_tile(lds, V::OFF_X + 2 * (col * PX + 32 * ka + 8 * g));
+                  if (tt == 0 || r == 0) bx2[ka - KA1] = lds_tile(lds, V::OFF_X + 2 * (n * PX + 32 * ka + 8 * g));
                 }
               }
             };
             prio(P0{});
             fetch(0);
             fetch(1);
-            const f32x4 sp4 = *reinterpret_cast<const f32x4*>(lds + V::OFF_SSP + 4 * NW * col);
+            const f32x4 sp4 = *reinterpret_cast<const f32x4*>(lds + V::OFF_SSP + 4 * NW * n);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int kt = 0; kt < KT_H; ++kt) {
@@ -975,12 +711,12 @@ void rollout_mfma_kernel(const MfmaArgs a) {
             for (int tt = 0; tt < MT_H; ++tt) acc[tt] = *reinterpret_cast<const f32x4*>(bxs + j * NHP + 16 * (w * MT_H + tt) + 4 * g);
             __syncthreads();
             bf16x8 bh[3];
-            bh[0] = lds_tile(lds, off_in + 2 * (col * PH + 8 * g));
-            bh[1] = lds_tile(lds, off_in + 2 * (col * PH + 32 + 8 * g));
+            bh[0] = lds_tile(lds, off_in + 2 * (n * PH + 8 * g));
+            bh[1] = lds_tile(lds, off_in + 2 * (n * PH + 32 + 8 * g));
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int kt = 0; kt < KT_H; ++kt) {
-              if (kt + 2 < KT_H) bh[(kt + 2) % 3] = lds_tile(lds, off_in + 2 * (col * PH + 32 * (kt + 2) + 8 * g));
+              if (kt + 2 < KT_H) bh[(kt + 2) % 3] = lds_tile(lds, off_in + 2 * (n * PH + 32 * (kt + 2) + 8 * g));
 #pragma unroll
               for (int tt = 0; tt < MT_H; ++tt) {
                 if (j == 0) pin_agpr(Wxr[j][tt][kt]);      // the first extra layer shares the accumulation half with layer 2
@@ -1004,7 +740,7 @@ void rollout_mfma_kernel(const MfmaArgs a) {
           __syncthreads();
           PSTAMP(6);
           prio(P3{});
-          if constexpr (ME < 0) norm_total(*reinterpret_cast<const f32x4*>(lds + V::OFF_SSP + 4 * NW * col));
+          if constexpr (ME < 0) norm_total(*reinterpret_cast<const f32x4*>(lds + V::OFF_SSP + 4 * NW * n));
           if (env_wave) {          // the others have no next-state tile
           // ---- phase C: a = tanh(sum of the partials + b3) ----
           bf16x8 ba16;             // the action as a B operand, from registers
@@ -1082,7 +818,6 @@ void rollout_mfma_kernel(const MfmaArgs a) {
           __syncthreads();
           PSTAMP(10);
         }
-        }
 #ifdef ES_PHASE_PROF
         if (blockIdx.x == 0 && lane == 0 && a.prof)
           for (int k = 0; k < 12; ++k) a.prof[w * 16 + k] += prof_acc[k];
@@ -1109,26 +844,23 @@ constexpr int env_tiles(int nop, int nw) { return (nop / 16 + nw - 1) / nw > 0 ?
 // individuals) share a CU and hide each other's LDS round trips and barriers (1.5x at obs 27).
 // (Passes of sixteen copies: A stays in LDS - with two workgroups per CU the register file has no four registers to spare
 // for its tile, and a spilled tile would be reloaded from scratch memory every step.)
-template <int NC, int NW> using V32 = Variant<1, 1, env_tiles(32, NW), NC == 16 ? 0 : 1, NC, NW, 2>;   // obs <= 32,  act <= 16
-template <int NC, int NW> using V64 = Variant<2, 1, env_tiles(64, NW), 2, NC, NW>;      // obs <= 64,  act <= 16
+template <int NW> using V32 = Variant<1, 1, env_tiles(32, NW), 0, NW, 2>;   // obs <= 32,  act <= 16
+template <int NW> using V64 = Variant<2, 1, env_tiles(64, NW), 2, NW>;      // obs <= 64,  act <= 16
 // the same two shapes with the environment's products in binary32 (es_config.env_dtype = 1)
-template <int NC, int NW> using V32F = Variant<1, 1, env_tiles(32, NW), 1, NC, NW, 2, 0, true>;
-template <int NC, int NW> using V64F = Variant<2, 1, env_tiles(64, NW), 2, NC, NW, 1, 0, true>;
-template <int NC, int NW> using V128 = Variant<4, 2, env_tiles(128, NW), 4, NC, NW>;    // obs <= 128, act <= 32
+template <int NW> using V32F = Variant<1, 1, env_tiles(32, NW), 1, NW, 2, 0, true>;
+template <int NW> using V64F = Variant<2, 1, env_tiles(64, NW), 2, NW, 1, 0, true>;
+template <int NW> using V128 = Variant<4, 2, env_tiles(128, NW), 4, NW>;    // obs <= 128, act <= 32
 // Deeper policies (m = 3, 4 hidden layers) of the two narrow-observation shapes: one workgroup per CU, the
 // extra 256 x 256 layers take the registers the second workgroup would have used.
 // (fewer than 128 units: tanh_near, as in rollout_quad_bf16_mid.hip; 27 random shapes, three and four layers: rms error 2.2e-5 on
 // the LDS kernel, 3.3e-5 with tanh_fast, 2.1e-5 with tanh_near, which costs 8 %)
-template <int NC, int NW, int ME, bool NEAR> using V32D = Variant<1, 1, env_tiles(32, NW), 1, NC, NW, 1, ME, false, NEAR>;
-template <int NC, int NW, int ME, bool NEAR> using V64D = Variant<2, 1, env_tiles(64, NW), 2, NC, NW, 1, ME, false, NEAR>;
+template <int NW, int ME, bool NEAR> using V32D = Variant<1, 1, env_tiles(32, NW), 1, NW, 1, ME, false, NEAR>;
+template <int NW, int ME, bool NEAR> using V64D = Variant<2, 1, env_tiles(64, NW), 2, NW, 1, ME, false, NEAR>;
 // A single hidden layer (m = 1) of the same two shapes: the second layer's phase and weights drop out.
-template <int NC, int NW> using V32S = Variant<1, 1, env_tiles(32, NW), 1, NC, NW, 2, -1>;
-template <int NC, int NW> using V64S = Variant<2, 1, env_tiles(64, NW), 2, NC, NW, 1, -1>;
-// obs <= 256, act <= 32.  KTAR of the eight K tiles of the environment matrix A sit in registers, the rest in LDS: all eight in
-// passes of four copies (512 individuals x 4 x 300 steps at obs 244: 1.04 ms), four of them in passes of sixteen, whose working
-// set is larger.
-template <int NC, int NW, int KTAR> using V256K = Variant<8, 2, env_tiles(256, NW), KTAR, NC, NW>;
-template <int NC, int NW> using V256 = V256K<NC, NW, 4>;
+template <int NW> using V32S = Variant<1, 1, env_tiles(32, NW), 1, NW, 2, -1>;
+template <int NW> using V64S = Variant<2, 1, env_tiles(64, NW), 2, NW, 1, -1>;
+// obs <= 256, act <= 32: four of the eight K tiles of the environment matrix A sit in registers, the rest in LDS
+template <int NW> using V256 = Variant<8, 2, env_tiles(256, NW), 4, NW>;
 
 struct VariantInfo { int max_obs, max_act; const char* name; };
 static const VariantInfo kVariants[] = {
@@ -1166,7 +898,7 @@ static int launch_variant_act(es_ctx* ctx, const MfmaArgs& a, uint32_t units, hi
   // Two workgroups per CU: priorities by phase.  They make the two equally fast, which is wrong where the last round leaves one of them an
   // individual more (a remainder of up to half the grid): without them the older one, which has it, is ahead anyway.  27-256-256-8 x 16 copies x 60
   // steps, without / with: 512 individuals 156 / 144 us, 600 220 / 233, 768 222 / 234, 800 277 / 254, 1200 328 / 355, 1600 446 / 474, 2048 552 / 504.
-  if constexpr (V::OCC == 2 && V::NC == 16 && !ORDERED) {
+  if constexpr (V::OCC == 2 && !ORDERED) {
     const uint32_t rest = units % grid;
     if (per_cu == 2 && (rest == 0u || 2u * rest > grid)) return launch_variant_act<V, RELU, NORM, true>(ctx, a, units, st);
   }
@@ -1194,44 +926,44 @@ int launch_rollout_mfma(es_ctx* ctx, uint32_t gen, const float* theta, const voi
   a.antithetic = c.antithetic; a.out_tanh = c.out_tanh; a.noise_mode = nv.mode;
   a.sigma = c.sigma; a.done_thresh = c.done_thresh; a.act_cost = c.act_cost;
   a.prof = static_cast<unsigned long long*>(ws);
-  if ((int)V256<16, 4>::LDS_BYTES > ctx->lds_limit)
+  if ((int)V256<4>::LDS_BYTES > ctx->lds_limit)
     return fail(ctx, ES_EUNSUPPORTED, "es_rollout: this device's LDS is too small for the register-resident kernel");
   const uint32_t units = s.N;      // one work item per individual
-  const bool narrow = s.E <= 4;     // passes of 4 environment copies with column compaction
 #ifdef ES_DEV_FAST   // tuning builds only: one variant, seconds to compile
   if (c.env_dtype == 1 && ctx->mfma_variant == 0 && ctx->cfg.hidden_act == 0 && !ctx->obs_mean)
-    return launch_variant_act<V32F<16, 4>, false, false>(ctx, a, units, st);
-  if (ctx->mfma_variant == 3 && narrow && s.m == 2 && ctx->cfg.hidden_act == 0 && !ctx->obs_mean)
-    return launch_variant_act<V256K<4, 4, 8>, false, false>(ctx, a, units, st);
-  if (ctx->mfma_variant == 0 && !narrow && s.m == 2 && ctx->cfg.hidden_act == 0 && !ctx->obs_mean)
-    return launch_variant_act<V32<16, 4>, false, false>(ctx, a, units, st);
+    return launch_variant_act<V32F<4>, false, false>(ctx, a, units, st);
+  if (ctx->mfma_variant == 0 && s.m == 2 && ctx->cfg.hidden_act == 0 && !ctx->obs_mean)
+    return launch_variant_act<V32<4>, false, false>(ctx, a, units, st);
   return fail(ctx, ES_EUNSUPPORTED, "tuning build: variant not compiled");
 #else
   if (c.env_dtype == 1) {          // binary32 environment: passes of 16 copies whatever E is
-    if (ctx->mfma_variant == 0) return launch_variant<V32F<16, 4>>(ctx, a, units, st);
-    if (ctx->mfma_variant == 1) return launch_variant<V64F<16, 4>>(ctx, a, units, st);
+    if (ctx->mfma_variant == 0) return launch_variant<V32F<4>>(ctx, a, units, st);
+    if (ctx->mfma_variant == 1) return launch_variant<V64F<4>>(ctx, a, units, st);
     return fail(ctx, ES_EUNSUPPORTED, "es_rollout: no register-resident variant with a binary32 environment for this shape");
   }
   // (obs <= 64 with up to four copies: rollout_quad.hpp)
   if (s.m == 1) {
-    if (ctx->mfma_variant == 0) return launch_variant<V32S<16, 4>>(ctx, a, units, st);
-    if (ctx->mfma_variant == 1) return launch_variant<V64S<16, 4>>(ctx, a, units, st);
+    if (ctx->mfma_variant == 0) return launch_variant<V32S<4>>(ctx, a, units, st);
+    if (ctx->mfma_variant == 1) return launch_variant<V64S<4>>(ctx, a, units, st);
   } else if (s.m == 3) {
-    if (ctx->mfma_variant == 0) return s.nh < 128 ? launch_variant<V32D<16, 4, 1, true>>(ctx, a, units, st) : launch_variant<V32D<16, 4, 1, false>>(ctx, a, units, st);
-    if (ctx->mfma_variant == 1) return s.nh < 128 ? launch_variant<V64D<16, 4, 1, true>>(ctx, a, units, st) : launch_variant<V64D<16, 4, 1, false>>(ctx, a, units, st);
+    if (ctx->mfma_variant == 0) return s.nh < 128 ? launch_variant<V32D<4, 1, true>>(ctx, a, units, st) : launch_variant<V32D<4, 1, false>>(ctx, a, units, st);
+    if (ctx->mfma_variant == 1) return s.nh < 128 ? launch_variant<V64D<4, 1, true>>(ctx, a, units, st) : launch_variant<V64D<4, 1, false>>(ctx, a, units, st);
   } else if (s.m == 4) {
-    if (ctx->mfma_variant == 0) return s.nh < 128 ? launch_variant<V32D<16, 4, 2, true>>(ctx, a, units, st) : launch_variant<V32D<16, 4, 2, false>>(ctx, a, units, st);
-    if (ctx->mfma_variant == 1) return s.nh < 128 ? launch_variant<V64D<16, 4, 2, true>>(ctx, a, units, st) : launch_variant<V64D<16, 4, 2, false>>(ctx, a, units, st);
+    if (ctx->mfma_variant == 0) return s.nh < 128 ? launch_variant<V32D<4, 2, true>>(ctx, a, units, st) : launch_variant<V32D<4, 2, false>>(ctx, a, units, st);
+    if (ctx->mfma_variant == 1) return s.nh < 128 ? launch_variant<V64D<4, 2, true>>(ctx, a, units, st) : launch_variant<V64D<4, 2, false>>(ctx, a, units, st);
   }
   if (s.m != 2) return fail(ctx, ES_EUNSUPPORTED, "es_rollout: no register-resident variant for this depth");
+  // 65 to 256 observations: up to four copies, or passes of four that fit the chip at once, in the four-copy kernel.  Per 100 steps of obs-256-256-17, up to
+  // sixteen columns a pass here (or, before, four of them) / there: four copies of 1024 individuals obs 128 649 / 556 us, 244 777 / 700 (a step 3 730 / 3 320
+  // cycles), one copy 645 / 470 and 774 / 620; obs 244 64 x 16 copies 256 / 207, 128 x 8 266 / 207, 40 x 24 471 / 204; more passes of five copies and more:
+  // 256 x 6 277 us here, 1024 x 8 986 (four each: 200 and 700).
+  if (ctx->mfma_variant >= 2 && (s.E <= 4 || (uint64_t)s.N * ((s.E + 3) / 4) <= (uint64_t)ctx->num_cus))
+    return launch_rollout_quad_spread(ctx, gen, theta, noise, A, B, returns, ep_len, fitness, st);
   switch (ctx->mfma_variant) {
-    case 0: return launch_variant<V32<16, 4>>(ctx, a, units, st);
-    case 1: return launch_variant<V64<16, 4>>(ctx, a, units, st);
-    case 2: return narrow ? launch_variant<V128<4, 4>>(ctx, a, units, st) : launch_variant<V128<16, 4>>(ctx, a, units, st);
-    case 3: {
-      if (!narrow) return launch_variant<V256<16, 4>>(ctx, a, units, st);
-      return launch_variant<V256K<4, 4, 8>>(ctx, a, units, st);
-    }
+    case 0: return launch_variant<V32<4>>(ctx, a, units, st);
+    case 1: return launch_variant<V64<4>>(ctx, a, units, st);
+    case 2: return launch_variant<V128<4>>(ctx, a, units, st);
+    case 3: return launch_variant<V256<4>>(ctx, a, units, st);
     default: return fail(ctx, ES_EUNSUPPORTED, "es_rollout: no register-resident variant for this shape");
   }
 #endif

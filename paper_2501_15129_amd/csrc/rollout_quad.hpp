@@ -25,7 +25,7 @@
 // lone wavefront).
 // Measured, whole rollout, T = 1000 unless noted: bf16 8-256-256-2, 128 individuals x 1 copy 1.23 ms (padded 16-column kernel) -> 0.77 ms -> 0.74 with
 // the books and the two branches of a step's end behind the loop; bf16 27-100-100-8, 128 x 5 copies, T = 400: 8.05 ms (LDS kernel) -> 0.34 ms -> 0.27 with
-// passes of two copies on SIMDs of their own.
+// passes of two copies on SIMDs of their own; 244-256-256-17, 1024 x 4 copies, T = 1000: 6.3 ms (16-column kernel with compacted columns) -> 5.7.
 #pragma once
 
 #include <type_traits>
@@ -221,13 +221,17 @@ struct QuadShape {
   // the action's exchange, with the action's tanh
   static constexpr int env_at(int k) {
     constexpr bool two = M > 1;
+    if (SPREAD && two) {      // (244-256-256-17: 3 470 cycles a step with the split below, 3 330 with more of it behind the barriers)
+      constexpr int at[6] = {0, KG / 8, KG * 3 / 8, KG / 2, KG * 7 / 8, KG};
+      return at[k];
+    }
     constexpr int at[6] = {0, KG * 3 / 8, NW > 1 && two ? KG / 2 : KG * 3 / 8, two ? KG * 13 / 16 : (NW > 1 && two ? KG / 2 : KG * 3 / 8), NW > 1 ? KG * 15 / 16 : (two ? KG * 13 / 16 : KG * 3 / 8), KG};
     return at[k];
   }
   static_assert(!(GROUPED && NA > 16), "grouped action layer: sixteen rows");
   static_assert(!SPREAD || 64 * NW >= 4 * KG, "the wavefronts must cover the padded state");
   static_assert(KG % GR == 0 && HG % GR == 0 && LDS_BYTES <= 160 * 1024, "staging rounds, LDS budget");
-  static_assert(WREGS <= 490 && (NC == 1 || NC == 4 || (NC == 2 && HALVES && !SPREAD)), "register budget, copies");
+  static_assert(WREGS <= 490 && (NC == 1 || NC == 4 || (NC == 2 && HALVES)), "register budget, copies");
 };
 
 // Two wavefronts, two workgroups on a CU: the hardware starts a workgroup one SIMD after the last one's start, so that the second would put a wavefront
@@ -464,7 +468,11 @@ void rollout_quad_kernel(const QuadArgs a) {
       while (true) {
       do {
 #pragma unroll
-        for (int c = 0; c < NC; ++c) { pin_sgpr(ninv[c]); pin_sgpr(thr[c]); if (!S::ROWS_COPY) pin_sgpr(ncost[c]); }
+        for (int c = 0; c < NC; ++c)
+          if constexpr (NC > 1 || !SPREAD) {      // (one copy with spread rows: constants, which the compiler keeps where it likes)
+            pin_sgpr(ninv[c]); pin_sgpr(thr[c]);
+            if (!S::ROWS_COPY) pin_sgpr(ncost[c]);
+          }
         // (two wait states must lie between instructions on one accumulator: two accumulators alternate)
         f32x4 accE[2] = {zero4, zero4};
         // A s is off the chain of dependent layers: its K groups are issued in five portions, between the vector
@@ -785,5 +793,8 @@ int launch_quad_bf16_deep4(es_ctx* ctx, const QuadArgs& a, float* fitness, hipSt
 int launch_quad_f32_mid(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st);      // two wavefronts, one to three layers
 int launch_quad_f32_wide(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st);     // four wavefronts, one or two layers
 int launch_quad_narrow(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st);       // one wavefront, two layers
+int launch_quad_obs128(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st);       // four wavefronts, bf16, two layers, obs <= 128, act <= 32
+int launch_quad_obs192(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st);       // ... <= 192
+int launch_quad_obs256(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st);       // ... <= 256
 
 }  // namespace es
