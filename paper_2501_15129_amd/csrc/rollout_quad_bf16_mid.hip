@@ -10,7 +10,9 @@ namespace es {
 int launch_quad_bf16_mid(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st) {
   const bool one = ctx->shp.m == 1;
   if (a.no <= 64 && a.na <= 16) return one ? launch_quad_obs64<true, 2, 1, true>(ctx, a, fitness, st) : launch_quad_obs64<true, 2, 2, true>(ctx, a, fitness, st);
-  return one ? launch_quad_options<true, 2, 32, 1, 4, true, true>(ctx, a, fitness, st) : launch_quad_options<true, 2, 32, 2, 4, true, true>(ctx, a, fitness, st);
+  // (per 200 steps, four copies a pass / as many as the chip has room for: 70-100-100-17 64 x 4 copies 237 / 194 us, 512 x 1 247 / 198, 512 x 2 242 / 208,
+  // 128-128-128-32 64 x 16 223 / 205, 1024 x 4 458 / 455, one layer 64 x 4 179 / 135)
+  return one ? launch_quad_copies<true, 2, 32, 1, true, true>(ctx, a, fitness, st) : launch_quad_copies<true, 2, 32, 2, true, true>(ctx, a, fitness, st);
 }
 
 }  // namespace es
