@@ -755,12 +755,13 @@ int launch_quad_options(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStrea
 // observation statistics only in the widest) and the number of copies of a pass
 // Copies of a pass: as few as the chip can take side by side, one wavefront per SIMD, since the activations of a copy are on the chain of a step.
 // Per 100 steps of bf16 27-100-100-8, four copies a pass / as chosen: 128 individuals x 2 copies 97 / 75 us (one), 128 x 3 97 / 84 (one), 128 x 5 100 / 87
-// (two), 512 x 2 127 / 85 (two; 42 us of it wavefront_place), 8-256-256-2 64 x 8 129 / 118 (two).
+// (two), 512 x 2 127 / 85 (two; 42 us of it wavefront_place), 8-256-256-2 64 x 8 129 / 118 (two); three layers per 200 steps, 27-100x3-6 128 x 4
+// 321 / 270 (two), 8-256x3-6 512 x 2 614 / 535 (two).  (Four layers split the action layer by lane groups, which needs all four rows or one.)
 template <bool BF16, int NW, int KG, int M, bool WITH_NORM, bool NEAR>
 int launch_quad_copies(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st) {
   auto apart = [&](uint32_t nc) { return (uint64_t)a.N * ((a.E + nc - 1u) / nc) * NW <= 4u * (uint64_t)ctx->num_cus; };
   if (a.E == 1u || apart(1u)) return launch_quad_options<BF16, NW, KG, M, 1, WITH_NORM, NEAR>(ctx, a, fitness, st);
-  if constexpr (BF16 && M <= 2) {
+  if constexpr (BF16 && M <= 3) {
     if (a.E == 2u || apart(2u)) return launch_quad_options<BF16, NW, KG, M, 2, WITH_NORM, NEAR>(ctx, a, fitness, st);
   }
   return launch_quad_options<BF16, NW, KG, M, 4, WITH_NORM, NEAR>(ctx, a, fitness, st);

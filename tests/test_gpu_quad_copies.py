@@ -19,6 +19,7 @@ pytestmark = pytest.mark.gpu
     (20, 4, dict(hid=100, obs=128, act=32)), (300, 1, dict(hid=65, obs=65, act=3, done_thresh=0.5)), (100, 6, dict(hid=128, obs=90, act=17, hidden_act=1)), (200, 3, dict(hid=100, obs=127, num_hidden=1, done_thresh=0.5)),
     # 129 to 256 units: two copies, four
     (40, 7, dict()), (40, 8, dict(obs=50, hidden_act=1, done_thresh=0.5)), (300, 2, dict(num_hidden=1, hid=200)), (70, 4, dict()), (70, 3, dict(hid=150, obs=40, done_thresh=0.5)),
+    (100, 3, dict(num_hidden=3, hid=100, obs=50, done_thresh=0.5)), (300, 4, dict(num_hidden=3)), (300, 3, dict(num_hidden=3, hid=90, hidden_act=1)),
     (70, 4, dict(num_hidden=3)), (70, 4, dict(num_hidden=4, hidden_act=1)), (70, 4, dict(num_hidden=3, hid=90, done_thresh=0.5)), (70, 3, dict(num_hidden=4, hid=90))], ids=str)
 def test_bf16(es, pop, envs, kw):  # noqa: F811
     w = replace(B, name=f"copies-{pop}x{envs}", horizon=14, **{"pop": pop, "envs": envs, "seed": 411 + pop + envs, **kw})
