@@ -205,7 +205,11 @@ struct QuadShape {
   static constexpr int WIN_ROWS = HID > ENV_ROWS ? HID : ENV_ROWS;
   static constexpr int WIN_BYTES = WIN_ROWS * PWIN * ES > NA * PW3 * ES ? WIN_ROWS * PWIN * ES : NA * PW3 * ES;
   static constexpr int OFF_BIAS = RUN_BYTES > WIN_BYTES ? RUN_BYTES : WIN_BYTES;    // [M][HID] hidden, then [NA] action biases, binary32
-  static constexpr int LDS_BYTES = (OFF_BIAS + 4 * (M * HID + 64) + 15) / 16 * 16;
+  // More than 128 observations: the initial states of the last pass, [copy][thread] binary32; most individuals of a workgroup start from the same ones
+  // (244-256-256-17, 4096 x 4 copies: 8 steps 750 -> 735 us, 200 steps 4980 -> 4936; up to 128 observations 3 % slower)
+  static constexpr bool KEEP_S0 = SPREAD && KG > 32;
+  static constexpr int OFF_S0 = OFF_BIAS + 4 * (M * HID + 64);
+  static constexpr int LDS_BYTES = (OFF_S0 + (KEEP_S0 ? 4 * NC * NT : 0) + 15) / 16 * 16;
   // registers of a lane's weights, and the wavefronts per SIMD that leaves room for
   static constexpr int VR = BF16 ? 2 : 4;
   // action layer, the wavefront's sixteen K groups: GROUPED (binary32; four layers, for the registers) four K values per instruction in groups of four
@@ -303,6 +307,8 @@ void rollout_quad_kernel(const QuadArgs a) {
   const float inv_no = 1.0f / (float)no;
   const bool squash = a.out_tanh != 0u;
   const uint32_t items = a.N * a.split;
+  uint32_t s0_pass = ~0u;                              // KEEP_S0: the pass whose initial states are kept
+  float* s0s = reinterpret_cast<float*>(lds + S::OFF_S0);
 
   for (uint32_t item = blockIdx.x; item < items; item += gridDim.x) {
     const uint32_t i = item / a.split, pass0 = item - i * a.split;
@@ -408,9 +414,15 @@ void rollout_quad_kernel(const QuadArgs a) {
         ncost[c] = uniform(on && w == 0 ? -a.act_cost : 0.0f);
         thr[c] = uniform(on ? a.done_thresh : __builtin_inff());
         len[c] = (int)a.T;
-        s[c] = 0.0f;
-        if (on && erow < no) s[c] = reset_value((uint32_t)erow, e, a.gen, a.k0, a.k1);
+        if (!S::KEEP_S0 || s0_pass != pass) {
+          s[c] = 0.0f;
+          if (on && erow < no) s[c] = reset_value((uint32_t)erow, e, a.gen, a.k0, a.k1);
+          if constexpr (S::KEEP_S0) s0s[c * NT + tid] = s[c];
+        } else {
+          s[c] = s0s[c * NT + tid];      // (written by this thread)
+        }
       }
+      if constexpr (S::KEEP_S0) s0_pass = pass;
       float xcost = (w == 0 && ((alive >> x) & 1u)) ? -a.act_cost : 0.0f;      // -cost of this lane's copy (ROWS_COPY)
       float Rs[NC];              // per-lane shares of the returns: rows of the state (and action rows, where row = lane)
       float Rx = 0.0f;           // ... of copy x: action rows (ROWS_COPY)
