@@ -17,6 +17,7 @@ pytestmark = pytest.mark.gpu
     (130, 3, dict(hid=100, obs=70, act=17, done_thresh=0.5)), (514, 1, dict(hid=100)), (270, 1, dict(hid=80, num_hidden=1)), (256, 2, dict(hid=128, episodes=2)),
     # ... state rows spread over the wavefronts: one copy, two, four
     (20, 4, dict(hid=100, obs=128, act=32)), (300, 1, dict(hid=65, obs=65, act=3, done_thresh=0.5)), (100, 6, dict(hid=128, obs=90, act=17, hidden_act=1)), (200, 3, dict(hid=100, obs=127, num_hidden=1, done_thresh=0.5)),
+    (300, 4, dict(hid=100, obs=128, act=32)), (300, 3, dict(hid=128, obs=65, act=5, num_hidden=1, done_thresh=0.5)), (514, 1, dict(hid=90, obs=100)),
     # 129 to 256 units: two copies, four
     (40, 7, dict()), (40, 8, dict(obs=50, hidden_act=1, done_thresh=0.5)), (300, 2, dict(num_hidden=1, hid=200)), (70, 4, dict()), (70, 3, dict(hid=150, obs=40, done_thresh=0.5)),
     (100, 3, dict(num_hidden=3, hid=100, obs=50, done_thresh=0.5)), (300, 4, dict(num_hidden=3)), (300, 3, dict(num_hidden=3, hid=90, hidden_act=1)),
@@ -26,7 +27,7 @@ def test_bf16(es, pop, envs, kw):  # noqa: F811
     assert "quad_bf16" in _case(es, w).rollout_kernel
 
 
-@pytest.mark.parametrize("pop,envs,kw", [(100, 7, dict(hid=100)), (10, 4, dict(hid=100, obs=70, act=17)), (90, 6, dict(hid=80, obs=128, act=30, num_hidden=1)), (40, 8, dict(hidden_act=1, obs=40)), (130, 8, dict(hid=100, obs=40)), (66, 13, dict(hid=120, obs=100, act=20)), (70, 4, dict(num_hidden=3))], ids=str)
+@pytest.mark.parametrize("pop,envs,kw", [(100, 7, dict(hid=100)), (10, 4, dict(hid=100, obs=70, act=17)), (90, 6, dict(hid=80, obs=128, act=30, num_hidden=1)), (300, 4, dict(hid=90, obs=100, act=20)), (40, 8, dict(hidden_act=1, obs=40)), (130, 8, dict(hid=100, obs=40)), (66, 13, dict(hid=120, obs=100, act=20)), (70, 4, dict(num_hidden=3))], ids=str)
 def test_bf16_statistics(es, pop, envs, kw):  # noqa: F811
     _case(es, replace(B, name=f"copies-norm-{pop}x{envs}", horizon=10, pop=pop, envs=envs, **kw), norm=True)
 

@@ -25,3 +25,12 @@ def test_wide_observations(es, obs, act, pop, envs, kw):  # noqa: F811
 def test_statistics(es, obs, act, pop, envs, kw):  # noqa: F811
     w = replace(B, name=f"wideobs-norm-{obs}-{pop}x{envs}", horizon=10, obs=obs, act=act, pop=pop, envs=envs, hid=256, **kw)
     assert _case(es, w, norm=True).rollout_kernel in NAMES
+
+
+@pytest.mark.parametrize("obs,act,pop,envs,kw,norm", [(100, 17, 130, 9, dict(), False), (128, 32, 90, 16, dict(hidden_act=1), False), (65, 3, 130, 5, dict(done_thresh=0.5), True),
+                                                      (244, 17, 130, 9, dict(), False), (200, 32, 70, 18, dict(done_thresh=0.5), False), (256, 20, 130, 6, dict(hidden_act=1), True)], ids=str)
+def test_sixteen_columns(es, obs, act, pop, envs, kw, norm):  # noqa: F811
+    """more than four copies, and more passes of four than compute units: the 16-column kernel of the same widths"""
+    assert pop * ((envs + 3) // 4) > 256
+    w = replace(B, name=f"wideobs-16-{obs}-{pop}x{envs}", horizon=8, obs=obs, act=act, pop=pop, envs=envs, hid=256, seed=711 + obs, **kw)
+    assert _case(es, w, norm=norm).rollout_kernel in NAMES
