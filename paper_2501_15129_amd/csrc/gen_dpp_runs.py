@@ -10,6 +10,8 @@ CHAIN = (3, 4, 5, 8, 12, 16)                                    # one accumulato
 ROTATE = (4, 8, 16)                                             # rotations of a row
 MAC = (3, 4, 6, 8, 16)                                          # accumulate-into runs (the action term)
 TAIL = ' row_mask:0xf bank_mask:0xf bound_ctrl:1\\n\\t"'
+# ends a run whose accumulators a row swap may read at once: the compiler keeps one of the two wait states behind inline assembly
+SWAP = '\n      "s_nop 0\\n\\t"'
 
 
 def ins(op, acc, h, w, j):
@@ -21,7 +23,7 @@ def operands(n, per=10):
     return ",\n".join("          " + ", ".join(items[a:a + per]) for a in range(0, n, per))
 
 
-def dot_block(q, n):
+def dot_block(q, n, swapped=False):
     """q accumulators x n inputs: o[a] = sum_j w[n a + j] * bcast_j(h); with one accumulator the sum is split into
     up to four interleaved partial sums."""
     lines = []
@@ -39,7 +41,7 @@ def dot_block(q, n):
     for j in range(n):
         lines.append(" ".join(ins("v_mul_f32_dpp" if j == 0 else "v_fmac_f32_dpp", a, q, q + 1 + n * a + j, j) for a in range(q)))
     outs = ", ".join(f'"=&v"(o[{a}])' for a in range(q))
-    body = "      " + "\n      ".join(lines)
+    body = "      " + "\n      ".join(lines) + (SWAP if swapped else "")
     return f'    asm volatile("s_nop 1\\n\\t"\n{body}\n        : {outs}\n        : "v"(h),\n{operands(q * n)});\n'
 
 
@@ -47,7 +49,7 @@ def dot_add_block(q, n):
     """as dot_block, added to o"""
     lines = [" ".join(ins("v_fmac_f32_dpp", a, q, q + 1 + n * a + j, j) for a in range(q)) for j in range(n)]
     outs = ", ".join(f'"+v"(o[{a}])' for a in range(q))
-    body = "      " + "\n      ".join(lines)
+    body = "      " + "\n      ".join(lines) + SWAP
     return f'    asm volatile("s_nop 1\\n\\t"\n{body}\n        : {outs}\n        : "v"(h),\n{operands(q * n)});\n'
 
 
@@ -78,16 +80,23 @@ def main():
            "// broadcast within each row by the DPP modifier, fused into the multiply-add - one instruction per multiply-add,",
            "// no scalar hop.  The compiler folds a DPP move into v_mul / v_add but not into v_fmac, hence inline assembly.",
            "// Its hazard checks do not look inside inline assembly: a vector ALU write of `h` must be two wait states away",
-           "// from the first DPP read, hence the s_nop that leads every run.  A run starts with multiplies (no zeroed",
+           "// from the first DPP read, hence the s_nop that leads every run.  The same distance lies before a row swap (v_permlane16_swap,",
+           "// v_permlane32_swap): behind inline assembly the compiler leaves one wait state, so a run of two accumulators, which are swapped with one",
+           "// another as they are, ends with the other.  Of four accumulators the pair that is swapped first ends one instruction earlier; a single one is",
+           "// copied before it is swapped with itself, and the copy's distance is the compiler's.  tests/test_wait_states.py reads the distances out",
+           "// of the built code.  A run starts with multiplies (no zeroed",
            "// accumulators) and interleaves its accumulators, so that consecutive instructions never depend on each other.",
            "",
-           "// o[a] = sum_{j < N} w[N a + j] * (lane j of h's row), a < Q",
-           "template <int Q, int N>",
+           "// o[a] = sum_{j < N} w[N a + j] * (lane j of h's row), a < Q.  SWAPPED: the two accumulators may be swapped with one another next",
+           "template <int Q, int N, bool SWAPPED = Q == 2>",
            "__device__ __forceinline__ void row_bcast_dot(float (&o)[Q], float h, const float (&w)[Q * N]) {"]
     first = True
     for q, n in DOT:
         out.append(f"  {'if' if first else 'else if'} constexpr (Q == {q} && N == {n}) {{")
-        out.append(dot_block(q, n).rstrip("\n"))
+        if q == 2:
+            out += ["    if constexpr (SWAPPED) {", dot_block(q, n, True).rstrip("\n"), "    } else {", dot_block(q, n).rstrip("\n"), "    }"]
+        else:
+            out.append(dot_block(q, n).rstrip("\n"))
         out.append("  }")
         first = False
     out.append('  else static_assert(Q < 0, "no run of this shape: add it to gen_dpp_runs.py");')

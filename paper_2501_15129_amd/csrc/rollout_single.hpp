@@ -134,7 +134,7 @@ void rollout_single_kernel(const QuadArgs a, const uint32_t hidden_relu) {
     auto bar = [] { __builtin_amdgcn_sched_barrier(0); };
     const float xp = NORM ? (s - mu) * iv : s;
     float ev[4], p[2];
-    auto env_front = [&] { row_bcast_dot<2, CJ>(reinterpret_cast<float(&)[2]>(ev[0]), s, reinterpret_cast<const float(&)[2 * CJ]>(ar[0])); };
+    auto env_front = [&] { row_bcast_dot<2, CJ, false>(reinterpret_cast<float(&)[2]>(ev[0]), s, reinterpret_cast<const float(&)[2 * CJ]>(ar[0])); };
     auto env_back = [&] { row_bcast_dot<2, CJ>(reinterpret_cast<float(&)[2]>(ev[2]), s, reinterpret_cast<const float(&)[2 * CJ]>(ar[2 * CJ])); };
     row_bcast_dot<2, CJ>(p, xp, w1);
     float h = act.hidden(rows_transpose_add(p[0], p[1]), cb[0], relu_l);
