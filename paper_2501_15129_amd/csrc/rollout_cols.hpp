@@ -66,6 +66,10 @@ __device__ __forceinline__ void stage_all(Elem* sp, const float* __restrict__ th
   __syncthreads();
 }
 
+// LDS of an individual's parameters
+template <class Elem>
+constexpr uint32_t param_bytes(uint32_t count) { return ((uint32_t)sizeof(Elem) * count + 15u) / 16u * 16u; }
+
 }  // namespace cols
 
 // KS: groups of four state elements (class of ceil(obs / 4)); HT: tiles of sixteen hidden units; NAK: groups of four actions.
@@ -194,7 +198,10 @@ void rollout_cols_kernel(const QuadArgs a) {
   auto hidden = [&](f32x4 v) { return S::RELU ? f32x4{relu(v.x), relu(v.y), relu(v.z), relu(v.w)} : squash(v); };
   const f32x4 zero4 = f32x4{0.f, 0.f, 0.f, 0.f};
   const uint32_t npass = (a.E + 15u) / 16u;
-  const float inv_no = 1.0f / (float)no;
+  const float ninv = -1.0f / (float)no, ncost = -a.act_cost;
+  // A copy that has ended goes on with the others and may run into infinities, so its share of the return is put aside when it ends (not multiplied
+  // by zero from then on): one per lane, behind the parameters
+  float* ends = reinterpret_cast<float*>(lds + param_bytes<Elem>(a.ob3 + a.na));
   uint32_t squash_l = a.out_tanh;      // (a select, not a branch)
   asm volatile("" : "+v"(squash_l));
 
@@ -204,7 +211,7 @@ void rollout_cols_kernel(const QuadArgs a) {
     const bool on = e < a.E;
     uint32_t alive = cnt == 16u ? 0xFFFFu : (1u << cnt) - 1u;      // copies still running (uniform)
     uint32_t len = a.T;
-    float ninv = on ? -inv_no : 0.0f, ncost = on ? -a.act_cost : 0.0f, thr = on ? a.done_thresh : __builtin_inff(), R = 0.0f;      // of this lane's copy, while it runs
+    float thr = on ? a.done_thresh : __builtin_inff(), R = 0.0f;      // of this lane's copy, while it runs
     f32x4 s[OT];
 #pragma unroll
     for (int t = 0; t < OT; ++t)
@@ -291,12 +298,13 @@ void rollout_cols_kernel(const QuadArgs a) {
       ++t;
       if (__builtin_expect(over != 0ull || t == a.T, 0)) {
         uint32_t m = (uint32_t)(over | over >> 32);
-        m = (m | m >> 16) & alive;
-        if (m >> n & 1u) { len = t; ninv = 0.0f; ncost = 0.0f; thr = __builtin_inff(); }
+        m = t == a.T ? alive : (m | m >> 16) & alive;
+        if (m >> n & 1u) { len = t; thr = __builtin_inff(); ends[lane] = R; }
         alive &= ~m;
-        if (alive == 0u || t == a.T) break;
+        if (alive == 0u) break;
       }
     }
+    R = ends[lane];      // (written by this lane)
     // ---- outputs: return = length + the shares of the four lanes of a copy ----
     R += __shfl_xor(R, 16, 64);
     R += __shfl_xor(R, 32, 64);
@@ -312,7 +320,7 @@ void rollout_cols_kernel(const QuadArgs a) {
 
 template <class S>
 int launch_cols_shape(es_ctx* ctx, QuadArgs a, float* fitness, hipStream_t st) {
-  const size_t lds = ((S::BF16 ? sizeof(uint16_t) : sizeof(float)) * (a.ob3 + a.na) + 15u) / 16u * 16u;      // at most 38 KB
+  const size_t lds = cols::param_bytes<std::conditional_t<S::BF16, uint16_t, float>>(a.ob3 + a.na) + 64u * sizeof(float);      // at most 38 KB
   const uint32_t npass = (a.E + 15u) / 16u, per_cu = (uint32_t)std::max<size_t>(1, std::min<size_t>(4 * S::OCC, (size_t)ctx->lds_limit / lds));
   a.split = quad_split(a.N, npass, (uint32_t)std::max(1, ctx->num_cus) * per_cu);
   a.fitness = a.split == 1u ? fitness : nullptr;

@@ -201,7 +201,9 @@ struct QuadShape {
   static constexpr int OFF_XP = OFF_X + XB;
   static constexpr int OFF_FLAG = OFF_XP + (NORM ? XB : 0);
   static constexpr int OFF_RED = OFF_FLAG + 16;
-  static constexpr int RUN_BYTES = OFF_RED + 4 * 4 * NW;
+  // [copy][thread]: a lane's share of the return of a copy that has ended
+  static constexpr int OFF_END = OFF_RED + 4 * 4 * NW;
+  static constexpr int RUN_BYTES = OFF_END + (NC > 1 ? 4 * NC * NT : 0);
   static constexpr int WIN_ROWS = HID > ENV_ROWS ? HID : ENV_ROWS;
   static constexpr int WIN_BYTES = WIN_ROWS * PWIN * ES > NA * PW3 * ES ? WIN_ROWS * PWIN * ES : NA * PW3 * ES;
   static constexpr int OFF_BIAS = RUN_BYTES > WIN_BYTES ? RUN_BYTES : WIN_BYTES;    // [M][HID] hidden, then [NA] action biases, binary32
@@ -405,6 +407,7 @@ void rollout_quad_kernel(const QuadArgs a) {
       int len[NC];
       float s[NC];               // state row of this lane, one register per copy (binary32)
       const bool mine = SPREAD || w == 0;      // the wavefront that adds up the state's share of the reward
+      float* ends = reinterpret_cast<float*>(lds + S::OFF_END);
 #pragma unroll
       for (int c = 0; c < NC; ++c) {
         const uint32_t e = (uint32_t)NC * pass + (uint32_t)c;
@@ -678,9 +681,12 @@ void rollout_quad_kernel(const QuadArgs a) {
           for (int c = 0; c < NC; ++c) ended |= over[c] != 0ull ? 1u << c : 0u;
           ended = uniform(ended & alive);
         }
+        if (t == a.T) ended = alive;
+        // (a copy that has ended goes on with the others and may run into infinities, so its share is put aside here: a factor of zero does not keep them out)
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
           const bool end = (ended >> c & 1u) != 0u;
+          if (NC > 1 && end) ends[c * NT + tid] = Rs[c] + (x == c ? Rx : 0.0f);
           len[c] = (int)uniform(end ? t : (uint32_t)len[c]);
           ninv[c] = uniform(end ? 0.0f : ninv[c]);
           ncost[c] = uniform(end ? 0.0f : ncost[c]);
@@ -688,13 +694,13 @@ void rollout_quad_kernel(const QuadArgs a) {
         }
         alive &= ~ended;
         if (((alive >> x) & 1u) == 0u) xcost = 0.0f;
-        if (alive == 0u || t == a.T) break;
+        if (alive == 0u) break;
       }
       // ---- outputs of this pass: return = length + the lanes' shares ----
       const uint32_t cnt = min((uint32_t)NC, a.E - (uint32_t)NC * pass);
       float R[NC];
 #pragma unroll
-      for (int c = 0; c < NC; ++c) R[c] = wave_sum(Rs[c] + (NC == 1 || x == c ? Rx : 0.0f));
+      for (int c = 0; c < NC; ++c) R[c] = wave_sum(NC == 1 ? Rs[0] + Rx : ends[c * NT + tid]);      // (written by this thread)
       if constexpr (SPREAD) {
         float* red = reinterpret_cast<float*>(lds + S::OFF_RED);
         if (lane == 0) {
