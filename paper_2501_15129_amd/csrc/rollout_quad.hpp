@@ -206,12 +206,9 @@ struct QuadShape {
   static constexpr int RUN_BYTES = OFF_END + (NC > 1 ? 4 * NC * NT : 0);
   static constexpr int WIN_ROWS = HID > ENV_ROWS ? HID : ENV_ROWS;
   static constexpr int WIN_BYTES = WIN_ROWS * PWIN * ES > NA * PW3 * ES ? WIN_ROWS * PWIN * ES : NA * PW3 * ES;
-  static constexpr int OFF_BIAS = RUN_BYTES > WIN_BYTES ? RUN_BYTES : WIN_BYTES;    // [M][HID] hidden, then [NA] action biases, binary32
   // More than 128 observations: the initial states of the last pass, [copy][thread] binary32; most individuals of a workgroup start from the same ones
   // (244-256-256-17, 4096 x 4 copies: 8 steps 750 -> 735 us, 200 steps 4980 -> 4936; up to 128 observations 3 % slower)
   static constexpr bool KEEP_S0 = SPREAD && KG > 32;
-  static constexpr int OFF_S0 = OFF_BIAS + 4 * (M * HID + 64);
-  static constexpr int LDS_BYTES = (OFF_S0 + (KEEP_S0 ? 4 * NC * NT : 0) + 15) / 16 * 16;
   // registers of a lane's weights, and the wavefronts per SIMD that leaves room for
   static constexpr int VR = BF16 ? 2 : 4;
   // action layer, the wavefront's sixteen K groups: GROUPED (binary32; four layers, for the registers) four K values per instruction in groups of four
@@ -222,6 +219,18 @@ struct QuadShape {
   static constexpr int NP = HALVES ? 2 * NW : NW;                        // partial sums of an action row
   static constexpr int WREGS = VR * (2 * KG + (M - 1) * HG + W3N + KGA);
   static constexpr int OCC = WREGS + 72 <= 168 ? 3 : WREGS + 72 <= 256 ? 2 : 1;
+  // Four wavefronts, up to two workgroups on a CU: two staging windows, so that a round's loads are requested while other wavefronts still read the round
+  // before (one barrier a round).  Three workgroups would not fit the LDS: one layer, 1000 x 4 copies of 27-256-8, 200 steps 237 us, two windows 289
+  static constexpr bool TWO_WIN = NW == 4 && OCC < 3;
+  static constexpr int OFF_S0 = RUN_BYTES > (TWO_WIN ? 2 : 1) * WIN_BYTES ? RUN_BYTES : (TWO_WIN ? 2 : 1) * WIN_BYTES;
+  static constexpr int LDS_BYTES = (OFF_S0 + (KEEP_S0 ? 4 * NC * NT : 0) + 15) / 16 * 16;
+  // Registers beside the weights while they are staged.  Where they are short, a batch of loads, or what the compiler derives from the lane's number once for
+  // all individuals, is spilled, and the reloads are waited for one after the other between the loads: FRESH computes the lane's number anew
+  // (lane_now), BATCH halves a batch where a second workgroup fills the waits.  4096 x 4 copies, 2 steps, neither / FRESH / both: 244-256-256-17 (96 registers) 567 / 560 / 692 us, 100-256-256-17 (224)
+  // 388 / 416 / 521; 512 x 2 of 27-256-256-8 (72) 42 / 52 / 35
+  static constexpr int SLACK = (OCC == 3 ? 168 : OCC == 2 ? 256 : 512) - WREGS;
+  static constexpr bool FRESH = SLACK <= 96;
+  static constexpr int BATCH = OCC == 2 && SLACK < 80 ? STAGE_BATCH / 2 : STAGE_BATCH;
   static constexpr bool PLACED = NW == 2 && OCC > 1;                     // may be launched with four wavefronts, two of which leave (wavefront_place)
   // first K group of portion k of A s: in the first activation, after the first exchange, in the second activation, after
   // the action's exchange, with the action's tanh
@@ -282,25 +291,36 @@ void rollout_quad_kernel(const QuadArgs a) {
   const int unit = 64 * w + lane;                      // this lane's unit of every hidden layer
   const int erow = SPREAD ? unit : lane;               // ... and its row of the state
   Elem* win = reinterpret_cast<Elem*>(lds);
-  float* biass = reinterpret_cast<float*>(lds + S::OFF_BIAS);
   auto sync = [] { if constexpr (NW > 1) __syncthreads(); };
   auto stage_sync = [] { __syncthreads(); };
-  auto win_group = [&](int row, int pitch, int g) { return *reinterpret_cast<const V4*>(win + row * pitch + 4 * g); };
+  auto window = [&](int round) { return win + (S::TWO_WIN && (round & 1) ? S::WIN_BYTES / S::ES : 0); };
+  auto window_read = [&] { if constexpr (!S::TWO_WIN) stage_sync(); };
+  auto win_group = [&](int round, int row, int pitch, int g) { return *reinterpret_cast<const V4*>(window(round) + row * pitch + 4 * g); };
+
+  // FRESH: the lane and thread number, computed where they are needed.  What the compiler derives from the ones above and keeps from one individual to
+  // the next does not fit the registers beside the weights there, and its reloads are waited for one after the other
+  auto lane_now = [&] {
+    if constexpr (!S::FRESH) return lane;
+    int zero = 0;
+    asm volatile("" : "+v"(zero));
+    return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, (uint32_t)zero));
+  };
+  auto tid_now = [&] { return S::FRESH ? 64 * w + lane_now() : tid; };
 
   // ---- environment matrices -> registers: Ae[g] = A[erow][4g .. 4g+3], Be[g] = B[erow][4g .. 4g+3] ----
   V4 Ae[KG], Be[KGA];
   static_for<0, KG / GR>([&](auto rc) {
     constexpr int r = decltype(rc)::value;
-    stage_cols<COLS, false>(win, S::PWIN, S::ENV_ROWS, no, no, COLS * r, a.A, NoiseRow{}, 0.0f, 0u, tid, threads);
+    stage_cols<COLS, false>(window(r), S::PWIN, S::ENV_ROWS, no, no, COLS * r, a.A, NoiseRow{}, 0.0f, 0u, tid, threads);
     stage_sync();
 #pragma unroll
-    for (int g = 0; g < GR; ++g) Ae[GR * r + g] = win_group(erow, S::PWIN, g);
-    stage_sync();
+    for (int g = 0; g < GR; ++g) Ae[GR * r + g] = win_group(r, erow, S::PWIN, g);
+    window_read();
   });
-  stage_cols<4 * KGA, false>(win, S::PWIN, S::ENV_ROWS, no, na, 0, a.B, NoiseRow{}, 0.0f, 0u, tid, threads);
+  stage_cols<4 * KGA, false>(window(KG / GR), S::PWIN, S::ENV_ROWS, no, na, 0, a.B, NoiseRow{}, 0.0f, 0u, tid, threads);
   stage_sync();
 #pragma unroll
-  for (int g = 0; g < KGA; ++g) Be[g] = win_group(erow, S::PWIN, g);
+  for (int g = 0; g < KGA; ++g) Be[g] = win_group(KG / GR, erow, S::PWIN, g);
   float mu = 0.f, iv = 0.f;                            // observation statistics of this row (padded rows: scale 0)
   if (NORM && erow < no) { mu = a.obs_mean[erow]; iv = a.obs_inv[erow]; }
 
@@ -324,78 +344,74 @@ void rollout_quad_kernel(const QuadArgs a) {
 
     // ---- perturbed parameters -> LDS window -> registers ----
     V4 W1[KG], Wh[M > 1 ? M - 1 : 1][M > 1 ? HG : 1], W3[S::W3N];
+    // A lane's own biases, requested together before anything else (a load behind a bounds test would be waited for by itself: three latencies an
+    // individual).  hb: as the activation takes them, c b for tanh, b for ReLU; b3: of this lane's action rows
+    constexpr int RPL = S::RPL, NB = M + RPL;
+    const int lane_i = lane_now(), unit_i = 64 * w + lane_i;
+    float hb[M], b3[RPL];
+    uint32_t bix[NB];
+    bool bok[NB];
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+      const int c = S::ROWS_COPY ? RPL * (lane_i >> 2) + k - M : (k == M ? lane_i : S::NA);
+      bok[k] = k < M ? unit_i < nh : c < na;
+      bix[k] = !bok[k] ? 0u : k < M ? (k == 0 ? a.ob1 : a.ob2 + (uint32_t)(k - 1) * (uint32_t)(nh * nh + nh)) + (uint32_t)unit_i : a.ob3 + (uint32_t)c;
+    }
+    row_values<NB>(a.theta, nz, scale, bix, [&](int k, float v) {
+      if (BF16) v = bf16_round(v);
+      if (!bok[k]) v = 0.0f;
+      if (k < M) hb[k < M ? k : 0] = S::RELU ? v : TANH_C * v;
+      else b3[k < M ? 0 : k - M] = v;
+    });
     stage_sync();                // the previous individual's last reads of LDS are done
-    for (int u = tid; u < M * HID; u += NT) {
-      const int l = u / HID, uu = u - l * HID;
-      float v = 0.0f;
-      if (uu < nh) {
-        const uint32_t ix = (l == 0 ? a.ob1 : a.ob2 + (uint32_t)(l - 1) * (uint32_t)(nh * nh + nh)) + (uint32_t)uu;
-        v = __fmaf_rn(scale, row_noise(nz, ix), a.theta[ix]);
-        if (BF16) v = bf16_round(v);
-      }
-      biass[u] = v;
-    }
-    for (int c = tid; c < 64; c += NT) {
-      float v = 0.0f;
-      if (c < na) {
-        const uint32_t ix = a.ob3 + (uint32_t)c;
-        v = __fmaf_rn(scale, row_noise(nz, ix), a.theta[ix]);
-        if (BF16) v = bf16_round(v);
-      }
-      biass[M * HID + c] = v;
-    }
     static_for<0, KG / GR>([&](auto rc) {
       constexpr int r = decltype(rc)::value;
-      stage_cols<COLS, true>(win, S::PWIN, HID, nh, no, COLS * r, a.theta, nz, scale, a.oW1, tid, threads);
+      stage_cols<COLS, true, S::BATCH>(window(r), S::PWIN, HID, nh, no, COLS * r, a.theta, nz, scale, a.oW1, tid_now(), threads);
       stage_sync();
+      const int u = tid_now();
 #pragma unroll
-      for (int g = 0; g < GR; ++g) W1[GR * r + g] = win_group(unit, S::PWIN, g);
-      stage_sync();
+      for (int g = 0; g < GR; ++g) W1[GR * r + g] = win_group(r, u, S::PWIN, g);
+      window_read();
     });
     static_for<0, M - 1>([&](auto lc) {
       constexpr int l = decltype(lc)::value;
       static_for<0, HG / GR>([&](auto rc) {
-        constexpr int r = decltype(rc)::value;
-        stage_cols<COLS, true>(win, S::PWIN, HID, nh, nh, COLS * r, a.theta, nz, scale, a.oW2 + (uint32_t)l * (uint32_t)(nh * nh + nh), tid, threads);
+        constexpr int r = decltype(rc)::value, round = KG / GR + l * (HG / GR) + r;
+        stage_cols<COLS, true, S::BATCH>(window(round), S::PWIN, HID, nh, nh, COLS * r, a.theta, nz, scale, a.oW2 + (uint32_t)l * (uint32_t)(nh * nh + nh), tid_now(), threads);
         stage_sync();
+        const int u = tid_now();
 #pragma unroll
-        for (int g = 0; g < GR; ++g) Wh[l][GR * r + g] = win_group(unit, S::PWIN, g);
-        stage_sync();
+        for (int g = 0; g < GR; ++g) Wh[l][GR * r + g] = win_group(round, u, S::PWIN, g);
+        window_read();
       });
     });
-    stage_cols<HID, true>(win, S::PW3, S::NA, na, nh, 0, a.theta, nz, scale, a.oW3, tid, threads);
+    constexpr int last = KG / GR + (M - 1) * (HG / GR);
+    stage_cols<HID, true, S::BATCH>(window(last), S::PW3, S::NA, na, nh, 0, a.theta, nz, scale, a.oW3, tid_now(), threads);
     stage_sync();
+    const int lw = lane_now();
     if constexpr (S::HALVES) {   // lane = action row, and a half of the wavefront's K groups in either half of the lanes
 #pragma unroll
       for (int g = 0; g < S::W3N; ++g) {
         W3[g] = O::zero();
-        if ((lane & 31) < S::NA) W3[g] = win_group(lane & 31, S::PW3, 16 * w + 8 * (lane >> 5) + g);
+        if ((lw & 31) < S::NA) W3[g] = win_group(last, lw & 31, S::PW3, 16 * w + 8 * (lw >> 5) + g);
       }
     } else if constexpr (!S::GROUPED) { // lane = action row; K group g of this wavefront's 64 units
 #pragma unroll
       for (int g = 0; g < S::W3N; ++g) {
         W3[g] = O::zero();
-        if (lane < S::NA) W3[g] = win_group(lane, S::PW3, 16 * w + g);
+        if (lw < S::NA) W3[g] = win_group(last, lw, S::PW3, 16 * w + g);
       }
     } else {                     // lane (group gq of 16 lanes, n) = action row n; units 64 w + 16 gq ..
 #pragma unroll
-      for (int g = 0; g < S::W3N; ++g) W3[g] = win_group(lane & 15, S::PW3, 16 * w + 4 * (lane >> 4) + g);
+      for (int g = 0; g < S::W3N; ++g) W3[g] = win_group(last, lw & 15, S::PW3, 16 * w + 4 * (lw >> 4) + g);
     }
     stage_sync();
-    // biases as the activation takes them: c b for tanh, b for ReLU
-    float hb[M];
-#pragma unroll
-    for (int l = 0; l < M; ++l) { const float b = biass[l * HID + unit]; hb[l] = S::RELU ? b : TANH_C * b; }
-    constexpr int RPL = S::RPL;
-    float b3[RPL];                // biases of this lane's action rows
-#pragma unroll
-    for (int r = 0; r < RPL; ++r) b3[r] = biass[M * HID + (S::ROWS_COPY ? RPL * blk + r : (r == 0 ? lane : 63))];
     float sel_c[NC];             // binary32: columns of the selector that sums the four lane groups and transposes
 #pragma unroll
     for (int c = 0; c < NC; ++c) sel_c[c] = (NC == 1 || x == c) ? 1.0f : 0.0f;
     float* part = reinterpret_cast<float*>(lds + S::OFF_P);
     if constexpr (NW > 1) {      // action partials past the rows that are written read as zero
-      for (int k = tid; k < (S::P_TWICE ? 2 : 1) * S::NP * NC * S::PP; k += NT) part[k] = 0.0f;
+      for (int k = tid_now(); k < (S::P_TWICE ? 2 : 1) * S::NP * NC * S::PP; k += NT) part[k] = 0.0f;
       stage_sync();
     }
 
@@ -405,6 +421,7 @@ void rollout_quad_kernel(const QuadArgs a) {
       uint32_t alive = 0u;       // bit c: copy c of this pass still runs (uniform)
       float ninv[NC], ncost[NC], thr[NC];   // per copy while it runs: -1 / obs, -cost, threshold; 0, 0, +inf after its end
       int len[NC];
+      const int tid_p = tid_now(), erow_p = SPREAD ? tid_p : tid_p - 64 * w;
       float s[NC];               // state row of this lane, one register per copy (binary32)
       const bool mine = SPREAD || w == 0;      // the wavefront that adds up the state's share of the reward
       float* ends = reinterpret_cast<float*>(lds + S::OFF_END);
@@ -419,10 +436,10 @@ void rollout_quad_kernel(const QuadArgs a) {
         len[c] = (int)a.T;
         if (!S::KEEP_S0 || s0_pass != pass) {
           s[c] = 0.0f;
-          if (on && erow < no) s[c] = reset_value((uint32_t)erow, e, a.gen, a.k0, a.k1);
-          if constexpr (S::KEEP_S0) s0s[c * NT + tid] = s[c];
+          if (on && erow_p < no) s[c] = reset_value((uint32_t)erow_p, e, a.gen, a.k0, a.k1);
+          if constexpr (S::KEEP_S0) s0s[c * NT + tid_p] = s[c];
         } else {
-          s[c] = s0s[c * NT + tid];      // (written by this thread)
+          s[c] = s0s[c * NT + tid_p];      // (written by this thread)
         }
       }
       if constexpr (S::KEEP_S0) s0_pass = pass;
@@ -686,7 +703,7 @@ void rollout_quad_kernel(const QuadArgs a) {
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
           const bool end = (ended >> c & 1u) != 0u;
-          if (NC > 1 && end) ends[c * NT + tid] = Rs[c] + (x == c ? Rx : 0.0f);
+          if (NC > 1 && end) ends[c * NT + tid_now()] = Rs[c] + (x == c ? Rx : 0.0f);
           len[c] = (int)uniform(end ? t : (uint32_t)len[c]);
           ninv[c] = uniform(end ? 0.0f : ninv[c]);
           ncost[c] = uniform(end ? 0.0f : ncost[c]);
@@ -700,7 +717,7 @@ void rollout_quad_kernel(const QuadArgs a) {
       const uint32_t cnt = min((uint32_t)NC, a.E - (uint32_t)NC * pass);
       float R[NC];
 #pragma unroll
-      for (int c = 0; c < NC; ++c) R[c] = wave_sum(NC == 1 ? Rs[0] + Rx : ends[c * NT + tid]);      // (written by this thread)
+      for (int c = 0; c < NC; ++c) R[c] = wave_sum(NC == 1 ? Rs[0] + Rx : ends[c * NT + tid_now()]);      // (written by this thread)
       if constexpr (SPREAD) {
         float* red = reinterpret_cast<float*>(lds + S::OFF_RED);
         if (lane == 0) {

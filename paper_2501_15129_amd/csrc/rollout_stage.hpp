@@ -51,18 +51,33 @@ __device__ __forceinline__ void put4(float* dst, f32x4 v) { *reinterpret_cast<f3
 __device__ __forceinline__ void put1(uint16_t* dst, float v) { *dst = (uint16_t)bf16_bits(v); }
 __device__ __forceinline__ void put1(float* dst, float v) { *dst = v; }
 
+// put(k, value of parameter ix[k]), k < N: perturbed, the loads of all of them in flight together (each index is that of a parameter).
+template <int N, class Put>
+__device__ __forceinline__ void row_values(const float* __restrict__ theta, const NoiseRow nz, float scale, const uint32_t (&ix)[N], Put&& put) {
+  auto batch = [&](auto fetch) {
+    float tv[N];
+    decltype(fetch(0u)) ev[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) { tv[k] = theta[ix[k]]; ev[k] = fetch(ix[k]); }
+#pragma unroll
+    for (int k = 0; k < N; ++k) put(k, __fmaf_rn(scale, widen1(ev[k]), tv[k]));
+  };
+  if (nz.mode >= 2u) batch([&](uint32_t idx) { return noise_regen1(nz.row, idx, nz.gen, nz.k0, nz.k1, nz.mode == 3u); });
+  else if (nz.mode == 1u) batch([&](uint32_t idx) { return static_cast<const uint16_t*>(nz.ptr)[idx]; });
+  else batch([&](uint32_t idx) { return static_cast<const float*>(nz.ptr)[idx]; });
+}
+
 // Fill dst[r * pitch + c] for r < rows_p, c < COLS with the source value of matrix element (r, kbase + c) when
 // r < rows and kbase + c < cols, and zero elsewhere.
 // By `step` threads, this one being `tid` of them.
 // PERTURB: value = fma(scale, noise[idx], theta[idx]) with idx = off + r * cols + (kbase + c).
-// The loads of STAGE_BATCH iterations are issued together and unconditionally (a masked-out element reads the
+// The loads of U iterations are issued together and unconditionally (a masked-out element reads the
 // matrix's first entries instead, which are always there), and only then consumed: a load inside the bounds test
 // would be waited for in its own iteration, and the round would cost one memory latency per iteration.
-template <int COLS, bool PERTURB, class Elem>
+template <int COLS, bool PERTURB, int U = STAGE_BATCH, class Elem>
 __device__ __forceinline__ void stage_cols(Elem* dst, int pitch, int rows_p, int rows, int cols, int kbase,
                                            const float* __restrict__ src, const NoiseRow nz, float scale, uint32_t off,
                                            const int tid = (int)threadIdx.x, const int step = (int)blockDim.x) {
-  constexpr int U = STAGE_BATCH;
   if (((cols | (int)off | kbase) & 3) == 0) {
     // four consecutive columns per thread: 16-byte parameter loads, 8/16-byte noise loads, vector LDS stores
     constexpr int C4 = COLS / 4;
