@@ -18,7 +18,7 @@
 // SIMD do not overlap their DPP multiply-adds (10.7 cycles a pair), so beyond that one wavefront per episode is faster.
 // Bound: 660 cycles of issue per step of 17-64-64-6 and the hand-over, 820 to 890 in all (the barrier takes 100 to 200 of them: four wavefronts that
 // leave it together fetch their code together; the spread is that of the code's alignment in 32-byte windows).
-// Whole rollout, against one wavefront per episode: 256 episodes x 1000 steps of 17-64-64-6 391 -> 362 us (439 before either was tuned),
+// Whole rollout, against one wavefront per episode: 256 episodes x 1000 steps of 17-64-64-6 391 -> 374 us (439 before either was tuned),
 // 128 episodes x 400 steps of three layers 266 -> 187 us.
 #pragma once
 
@@ -128,12 +128,10 @@ __global__ __launch_bounds__(256) void rollout_team_kernel(const RegArgs a) {
     constexpr int BUF = PAIRS == 1 ? decltype(k)::value & 1 : 0;      // the buffer of the first hand-over: a step makes one or two
     const float xp = opnd(NORM ? (s - mu) * iv : s), se = opnd_env(s);
     float ev[4], h = 0.f, pre = 0.f;
-    // A s: four accumulators in two runs, whose swaps have their distance without a wait state of the runs' own.  With two layers the runs have one all the
-    // same: it moves the code behind them (256 episodes x 1000 steps of 17-64-64-6 375 -> 362 us; three layers, 128 x 400 steps, would go from 187 to 191).
-    constexpr bool PADDED = M == 2;
-    auto env_front = [&] { row_bcast_dot<2, CJ, PADDED>(reinterpret_cast<float(&)[2]>(ev[0]), se, reinterpret_cast<const float(&)[2 * CJ]>(ar[0])); };
+    // (A s: four accumulators in two runs, whose swaps have their distance without a wait state of the runs' own)
+    auto env_front = [&] { row_bcast_dot<2, CJ, false>(reinterpret_cast<float(&)[2]>(ev[0]), se, reinterpret_cast<const float(&)[2 * CJ]>(ar[0])); };
     auto env_back = [&] {
-      row_bcast_dot<2, CJ, PADDED>(reinterpret_cast<float(&)[2]>(ev[2]), se, reinterpret_cast<const float(&)[2 * CJ]>(ar[2 * CJ]));
+      row_bcast_dot<2, CJ, false>(reinterpret_cast<float(&)[2]>(ev[2]), se, reinterpret_cast<const float(&)[2 * CJ]>(ar[2 * CJ]));
       pre = rows_transpose_add(ev[0], ev[1], ev[2], ev[3]);
     };
     auto bar = [] { __builtin_amdgcn_sched_barrier(0); };
