@@ -22,13 +22,18 @@
 
 namespace es {
 
-template <int HW>
+template <int HW, int CJ>
 struct SingleMap {
   static constexpr int HID = 32 * HW, NI = HW / 2, PW = 64 + 4, PW3 = HID + 4;
-  // LDS (bytes): exchange buffers, then the staging window
+  // More than 32 observations: the environment's matrices pass through the LDS.  Its lanes fetching their own elements is a line per lane and load, 64 loads a
+  // wavefront of A alone: 60-100-100-8, 128 x 4 copies, 2 steps 36 -> 29 us; up to 32 observations the additional round costs as much as it saves
+  static constexpr bool ENV_LDS = CJ > 8;
+  static constexpr int ROWS = 4 * CJ, PA = ROWS + 4, PB = 16 + 4;
+  // LDS (bytes): exchange buffers, the staging window, the environment's matrices
   static constexpr int OFF_H = 0, OFF_P = 2 * 4 * HID, OFF_WIN = OFF_P + 2 * 4 * 16 * HW;
   static constexpr int WIN = 4 * HID * PW > 4 * 16 * PW3 ? 4 * HID * PW : 4 * 16 * PW3;
-  static constexpr int LDS_BYTES = OFF_WIN + WIN;
+  static constexpr int OFF_A = OFF_WIN + WIN, OFF_B = OFF_A + 4 * ROWS * PA;
+  static constexpr int LDS_BYTES = ENV_LDS ? OFF_B + 4 * ROWS * PB : OFF_A;
   static_assert(LDS_BYTES <= 160 * 1024, "LDS budget");
 };
 
@@ -36,7 +41,7 @@ struct SingleMap {
 template <int HW, int CJ, int NAR, int MODE, int M>
 __global__ __launch_bounds__(64 * HW) __attribute__((amdgpu_waves_per_eu(HW / 4, HW / 4)))
 void rollout_single_kernel(const QuadArgs a, const uint32_t hidden_relu) {
-  using Map = SingleMap<HW>;
+  using Map = SingleMap<HW, CJ>;
   constexpr int HID = Map::HID, NI = Map::NI;
   constexpr bool NORM = MODE < 0 || (MODE & 1);
   extern __shared__ __align__(16) unsigned char lds[];
@@ -56,20 +61,30 @@ void rollout_single_kernel(const QuadArgs a, const uint32_t hidden_relu) {
 
   // ---- environment matrices and statistics, requested first (masked elements read the matrix's first entry) ----
   float ar[4 * CJ], br[NAR];
+  float* ea = reinterpret_cast<float*>(lds + Map::OFF_A);
+  float* eb = reinterpret_cast<float*>(lds + Map::OFF_B);
+  auto load_env = [&](const float* A, int pitch_a, const float* B, int pitch_b) {
 #pragma unroll
-  for (int r = 0; r < 4; ++r)
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
-    for (int j = 0; j < CJ; ++j) {
-      const int el = 4 * lc + r, k = 4 * j + lr;
-      const bool ok = lc < CJ && el < no && k < no;
-      const float v = a.A[ok ? el * no + k : 0];
-      ar[CJ * r + j] = ok ? v : 0.f;
+      for (int j = 0; j < CJ; ++j) {
+        const int el = 4 * lc + r, k = 4 * j + lr;
+        const bool ok = lc < CJ && el < no && k < no;
+        const float v = A[ok ? el * pitch_a + k : 0];
+        ar[CJ * r + j] = ok ? v : 0.f;
+      }
+#pragma unroll
+    for (int c = 0; c < NAR; ++c) {
+      const bool ok = sval && c < na;
+      const float v = B[ok ? ks * pitch_b + c : 0];
+      br[c] = ok ? v : 0.f;
     }
-#pragma unroll
-  for (int c = 0; c < NAR; ++c) {
-    const bool ok = sval && c < na;
-    const float v = a.B[ok ? ks * na + c : 0];
-    br[c] = ok ? v : 0.f;
+  };
+  if constexpr (Map::ENV_LDS) {
+    stage_cols<Map::ROWS, false>(ea, Map::PA, Map::ROWS, no, no, 0, a.A, NoiseRow{}, 0.0f, 0u);
+    stage_cols<16, false>(eb, Map::PB, Map::ROWS, no, na, 0, a.B, NoiseRow{}, 0.0f, 0u);
+  } else {
+    load_env(a.A, no, a.B, na);
   }
   const bool stats = a.obs_mean != nullptr;
   const float mu = (NORM && stats && sval) ? a.obs_mean[ks] : 0.f;
@@ -91,6 +106,7 @@ void rollout_single_kernel(const QuadArgs a, const uint32_t hidden_relu) {
   float w1[2 * CJ], wh[M > 1 ? M - 1 : 1][M > 1 ? NI : 1][32], w3[8];
   stage_cols<64, true>(win, Map::PW, HID, nh, no, 0, a.theta, nz, scale, a.oW1);
   __syncthreads();
+  if constexpr (Map::ENV_LDS) load_env(ea, Map::PA, eb, Map::PB);      // (staged before the barrier above)
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
@@ -193,10 +209,11 @@ void rollout_single_kernel(const QuadArgs a, const uint32_t hidden_relu) {
 template <int HW, int CJ, int MODE, int M>
 int launch_single_act(es_ctx* ctx, QuadArgs a, float* fitness, hipStream_t st) {
   a.fitness = a.E == 1u ? fitness : nullptr;
+  constexpr int lds = SingleMap<HW, CJ>::LDS_BYTES;
   auto go = [&](auto kernel) {
-    const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, SingleMap<HW>::LDS_BYTES);
+    const hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (err != hipSuccess) return fail(ctx, ES_EHIP, std::string("hipFuncSetAttribute: ") + hipGetErrorString(err));
-    hipLaunchKernelGGL(kernel, dim3(a.N * a.E), dim3(64 * HW), SingleMap<HW>::LDS_BYTES, st, a, ctx->cfg.hidden_act == 1 ? 1u : 0u);
+    hipLaunchKernelGGL(kernel, dim3(a.N * a.E), dim3(64 * HW), lds, st, a, ctx->cfg.hidden_act == 1 ? 1u : 0u);
     const int rc = check_launch(ctx, "es_rollout (one copy per workgroup)");
     return rc != ES_OK || a.E == 1u ? rc : launch_fitness(ctx, a.returns, fitness, st);
   };
