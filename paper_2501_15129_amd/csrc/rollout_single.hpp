@@ -28,6 +28,7 @@ struct SingleMap {
   // More than 32 observations: the environment's matrices pass through the LDS.  Its lanes fetching their own elements is a line per lane and load, 64 loads a
   // wavefront of A alone: 60-100-100-8, 128 x 4 copies, 2 steps 36 -> 29 us; up to 32 observations the additional round costs as much as it saves
   static constexpr bool ENV_LDS = CJ > 8;
+  static_assert(!ENV_LDS || CJ == 16, "a column each");
   static constexpr int ROWS = 4 * CJ, PA = ROWS + 4, PB = 16 + 4;
   // LDS (bytes): exchange buffers, the staging window, the environment's matrices
   static constexpr int OFF_H = 0, OFF_P = 2 * 4 * HID, OFF_WIN = OFF_P + 2 * 4 * 16 * HW;
@@ -63,28 +64,25 @@ void rollout_single_kernel(const QuadArgs a, const uint32_t hidden_relu) {
   float ar[4 * CJ], br[NAR];
   float* ea = reinterpret_cast<float*>(lds + Map::OFF_A);
   float* eb = reinterpret_cast<float*>(lds + Map::OFF_B);
-  auto load_env = [&](const float* A, int pitch_a, const float* B, int pitch_b) {
+  if constexpr (Map::ENV_LDS) {
+    stage_cols<Map::ROWS, false>(ea, Map::PA, Map::ROWS, no, no, 0, a.A, NoiseRow{}, 0.0f, 0u);
+    stage_cols<16, false>(eb, Map::PB, Map::ROWS, no, na, 0, a.B, NoiseRow{}, 0.0f, 0u);
+  } else {
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
       for (int j = 0; j < CJ; ++j) {
         const int el = 4 * lc + r, k = 4 * j + lr;
         const bool ok = lc < CJ && el < no && k < no;
-        const float v = A[ok ? el * pitch_a + k : 0];
+        const float v = a.A[ok ? el * no + k : 0];
         ar[CJ * r + j] = ok ? v : 0.f;
       }
 #pragma unroll
     for (int c = 0; c < NAR; ++c) {
       const bool ok = sval && c < na;
-      const float v = B[ok ? ks * pitch_b + c : 0];
+      const float v = a.B[ok ? ks * na + c : 0];
       br[c] = ok ? v : 0.f;
     }
-  };
-  if constexpr (Map::ENV_LDS) {
-    stage_cols<Map::ROWS, false>(ea, Map::PA, Map::ROWS, no, no, 0, a.A, NoiseRow{}, 0.0f, 0u);
-    stage_cols<16, false>(eb, Map::PB, Map::ROWS, no, na, 0, a.B, NoiseRow{}, 0.0f, 0u);
-  } else {
-    load_env(a.A, no, a.B, na);
   }
   const bool stats = a.obs_mean != nullptr;
   const float mu = (NORM && stats && sval) ? a.obs_mean[ks] : 0.f;
@@ -106,7 +104,14 @@ void rollout_single_kernel(const QuadArgs a, const uint32_t hidden_relu) {
   float w1[2 * CJ], wh[M > 1 ? M - 1 : 1][M > 1 ? NI : 1][32], w3[8];
   stage_cols<64, true>(win, Map::PW, HID, nh, no, 0, a.theta, nz, scale, a.oW1);
   __syncthreads();
-  if constexpr (Map::ENV_LDS) load_env(ea, Map::PA, eb, Map::PB);      // (staged before the barrier above)
+  if constexpr (Map::ENV_LDS) {      // (staged before the barrier above, zero beyond the matrices; all sixteen columns hold elements)
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int j = 0; j < CJ; ++j) ar[CJ * r + j] = ea[(4 * lc + r) * Map::PA + 4 * j + lr];
+#pragma unroll
+    for (int c = 0; c < NAR; ++c) br[c] = eb[ks * Map::PB + c];
+  }
 #pragma unroll
   for (int t = 0; t < 2; ++t)
 #pragma unroll
