@@ -38,7 +38,7 @@ def flop_per_env_step(w) -> int:
 
 
 def columns_per_pass(kernel: str) -> int:
-    """Columns of a matrix-core rollout kernel that the environment copies fill: four on the 4x4 shapes, else sixteen."""
+    """Columns of a matrix-core rollout kernel ("mfma" in its name) that the environment copies fill: four on the 4x4 shapes, else sixteen."""
     return 4 if "_quad_" in kernel else 16
 
 

@@ -133,14 +133,18 @@ int es_create(const es_config* cfg, es_ctx** out) {
   ctx->mfma_variant = mfma_variant_for(c);
   ctx->reg_variant = reg_variant_for(c);
   if (quad_fits(c, ctx->shp.E, cus)) {
-    ctx->rollout_kind = ROLLOUT_QUAD;
-    ctx->kernel_name = quad_variant_name(c);
+    ctx->rollout_kind = quad_kind(c, ctx->shp.E, cus);
+    ctx->kernel_name = quad_variant_name(c, ctx->rollout_kind);
   } else if (ctx->reg_variant >= 0) {
-    ctx->rollout_kind = ROLLOUT_WAVE_REG;
-    ctx->kernel_name = reg_variant_name(ctx->reg_variant, c.dtype == 1, (uint32_t)m);
+    const bool team = reg_team(c, ctx->shp.E, cus);
+    ctx->rollout_kind = team ? ROLLOUT_WAVE_TEAM : ROLLOUT_WAVE_REG;
+    ctx->kernel_name = team ? team_variant_name(c) : reg_variant_name(ctx->reg_variant, c.dtype == 1, (uint32_t)m);
   } else if (mfma_f32_fits(c)) {
     ctx->rollout_kind = ROLLOUT_MFMA_F32;
     ctx->kernel_name = mfma_f32_variant_name(c);
+  } else if (quad_spread_pays(c, ctx->mfma_variant, ctx->shp.E, cus)) {
+    ctx->rollout_kind = ROLLOUT_QUAD_SPREAD;
+    ctx->kernel_name = quad_variant_name(c, ctx->rollout_kind);
   } else if (ctx->mfma_variant >= 0) {
     ctx->rollout_kind = ROLLOUT_MFMA_REG;
     ctx->kernel_name = mfma_variant_name(ctx->mfma_variant);
@@ -266,15 +270,15 @@ static int enqueue_sample(es_ctx* ctx, uint32_t generation, void* noise_d, hipSt
 static int enqueue_rollout(es_ctx* ctx, uint32_t generation, const float* theta_d, const void* noise_d, const float* A_d,
                            const float* B_d, float* returns_d, int32_t* ep_len_d, float* fitness_d, void* workspace_d,
                            hipStream_t st) {
-  if (ctx->rollout_kind == ROLLOUT_WAVE_REG)
-    return launch_rollout_reg(ctx, generation, theta_d, noise_d, A_d, B_d, returns_d, ep_len_d, fitness_d, workspace_d, st);
-  if (ctx->rollout_kind == ROLLOUT_MFMA_F32)
-    return launch_rollout_mfma_f32(ctx, generation, theta_d, noise_d, A_d, B_d, returns_d, ep_len_d, fitness_d, workspace_d, st);
-  if (ctx->rollout_kind == ROLLOUT_QUAD)
-    return launch_rollout_quad(ctx, generation, theta_d, noise_d, A_d, B_d, returns_d, ep_len_d, fitness_d, workspace_d, st);
-  if (ctx->rollout_kind == ROLLOUT_MFMA_REG)
-    return launch_rollout_mfma(ctx, generation, theta_d, noise_d, A_d, B_d, returns_d, ep_len_d, fitness_d, workspace_d, st);
-  return launch_rollout_wave(ctx, generation, theta_d, noise_d, A_d, B_d, returns_d, ep_len_d, fitness_d, workspace_d, st);
+  auto launch = [&](auto rollout) { return rollout(ctx, generation, theta_d, noise_d, A_d, B_d, returns_d, ep_len_d, fitness_d, workspace_d, st); };
+  switch (ctx->rollout_kind) {
+    case ROLLOUT_WAVE_REG: case ROLLOUT_WAVE_TEAM: return launch(launch_rollout_reg);
+    case ROLLOUT_MFMA_F32: return launch(launch_rollout_mfma_f32);
+    case ROLLOUT_QUAD: case ROLLOUT_QUAD_SPREAD: case ROLLOUT_COLS: case ROLLOUT_SINGLE: return launch(launch_rollout_quad);
+    case ROLLOUT_MFMA_REG: return launch(launch_rollout_mfma);
+    case ROLLOUT_WAVE_LDS: break;
+  }
+  return launch(launch_rollout_wave);
 }
 
 int es_sample_population(es_ctx* ctx, uint64_t generation, void* noise_d, void* stream) {
@@ -335,7 +339,7 @@ int es_generation(es_ctx* ctx, uint64_t generation, uint64_t adam_step, void* no
   const uint32_t gen = (uint32_t)generation;
   if (int rc = enqueue_sample(ctx, gen, noise_d, st)) return rc;
   if (update_ranks(ctx)) {      // a small population: fitness, ranks and update by one launch
-    const bool left = ctx->rollout_kind == ROLLOUT_WAVE_REG || ctx->rollout_kind == ROLLOUT_WAVE_LDS || ctx->rollout_kind == ROLLOUT_QUAD;
+    const bool left = ctx->rollout_kind != ROLLOUT_MFMA_REG && ctx->rollout_kind != ROLLOUT_MFMA_F32 && ctx->rollout_kind != ROLLOUT_QUAD_SPREAD;
     if (int rc = enqueue_rollout(ctx, gen, theta_d, noise_d, A_d, B_d, returns_d, ep_len_d, left ? nullptr : fitness_d, workspace_d, st)) return rc;
     return launch_rank_update(ctx, adam_step, noise_d, left ? returns_d : nullptr, fitness_d, rank_d, shaped_d, theta_d, m_d, v_d, grad_d, st);
   }

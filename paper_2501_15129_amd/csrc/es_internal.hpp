@@ -14,7 +14,11 @@ enum RolloutKind : int {
   ROLLOUT_MFMA_REG = 1,   // one workgroup per individual; bf16 weights resident in registers, MFMA
   ROLLOUT_WAVE_REG = 2,   // one wavefront per (individual, env); binary32 weights resident in registers
   ROLLOUT_MFMA_F32 = 3,   // one workgroup per individual; binary32 weights resident in registers, fp32 MFMA
-  ROLLOUT_QUAD = 4,       // passes of four copies on the 4x4 MFMA shapes (narrow policies: or of sixteen); weights resident in registers
+  ROLLOUT_QUAD = 4,       // passes of up to four copies on the 4x4 MFMA shapes; weights resident in registers
+  ROLLOUT_QUAD_SPREAD = 5,   // ... with 65 to 256 observations and up to 32 actions
+  ROLLOUT_COLS = 6,       // narrow policies in passes of sixteen copies, one wavefront each
+  ROLLOUT_SINGLE = 7,     // one copy per workgroup on the vector ALU, binary32
+  ROLLOUT_WAVE_TEAM = 8,  // four wavefronts per (individual, env)
 };
 
 struct Shape {
@@ -32,7 +36,7 @@ struct Shape {
 struct es_ctx {
   es_config cfg;
   es::Shape shp;
-  int rollout_kind;
+  es::RolloutKind rollout_kind;
   int mfma_variant;          // index of the instantiated register-resident kernel, or -1
   int reg_variant;           // index of the register-resident binary32 kernel, or -1
   size_t lds_bytes_wave;     // dynamic LDS of the wave/LDS rollout
@@ -104,14 +108,16 @@ int launch_rollout_mfma_f32(es_ctx* ctx, uint32_t gen, const float* theta, const
 int launch_rollout_quad(es_ctx* ctx, uint32_t gen, const float* theta, const void* noise,
                         const float* A, const float* B, float* returns, int32_t* ep_len,
                         float* fitness, void* ws, hipStream_t st);
-// bf16, two layers, 65 .. 256 observations, up to 32 actions and four copies (launch_rollout_mfma)
-int launch_rollout_quad_spread(es_ctx* ctx, uint32_t gen, const float* theta, const void* noise, const float* A, const float* B, float* returns,
-                               int32_t* ep_len, float* fitness, hipStream_t st);
-bool quad_fits(const es_config& cfg, uint32_t copies, int cus);   // copies = episodes evaluated per individual
-std::string quad_variant_name(const es_config& cfg);
+// copies = episodes evaluated per individual
+bool quad_fits(const es_config& cfg, uint32_t copies, int cus);
+RolloutKind quad_kind(const es_config& cfg, uint64_t copies, int cus);      // of a shape that quad_fits takes: ROLLOUT_QUAD, _COLS or _SINGLE
+bool quad_spread_pays(const es_config& cfg, int mfma_variant, uint64_t copies, int cus);   // ROLLOUT_QUAD_SPREAD instead of ROLLOUT_MFMA_REG
+std::string quad_variant_name(const es_config& cfg, RolloutKind kind);
 bool mfma_f32_fits(const es_config& cfg);
 const char* mfma_f32_variant_name(const es_config& cfg);
 int launch_fitness(es_ctx* ctx, const float* returns, float* fitness, hipStream_t st);
+bool reg_team(const es_config& cfg, uint64_t copies, int cus);      // ROLLOUT_WAVE_TEAM instead of ROLLOUT_WAVE_REG
+std::string team_variant_name(const es_config& cfg);
 int reg_variant_for(const es_config& cfg);        // -1 when no one-wavefront register-resident kernel is built for the shape
 std::string reg_variant_name(int variant, bool bf16, uint32_t layers);
 int mfma_variant_for(const es_config& cfg);       // -1 when no register-resident kernel fits

@@ -941,7 +941,7 @@ int launch_rollout_mfma(es_ctx* ctx, uint32_t gen, const float* theta, const voi
     if (ctx->mfma_variant == 1) return launch_variant<V64F<4>>(ctx, a, units, st);
     return fail(ctx, ES_EUNSUPPORTED, "es_rollout: no register-resident variant with a binary32 environment for this shape");
   }
-  // (obs <= 64 with up to four copies: rollout_quad.hpp)
+  // (up to four copies, and passes of four that fit the chip at once: rollout_quad.hip)
   if (s.m == 1) {
     if (ctx->mfma_variant == 0) return launch_variant<V32S<4>>(ctx, a, units, st);
     if (ctx->mfma_variant == 1) return launch_variant<V64S<4>>(ctx, a, units, st);
@@ -953,12 +953,6 @@ int launch_rollout_mfma(es_ctx* ctx, uint32_t gen, const float* theta, const voi
     if (ctx->mfma_variant == 1) return s.nh < 128 ? launch_variant<V64D<4, 2, true>>(ctx, a, units, st) : launch_variant<V64D<4, 2, false>>(ctx, a, units, st);
   }
   if (s.m != 2) return fail(ctx, ES_EUNSUPPORTED, "es_rollout: no register-resident variant for this depth");
-  // 65 to 256 observations: up to four copies, or passes of four that fit the chip at once, in the four-copy kernel.  Per 100 steps of obs-256-256-17, up to
-  // sixteen columns a pass here (or, before, four of them) / there: four copies of 1024 individuals obs 128 649 / 556 us, 244 777 / 700 (a step 3 730 / 3 320
-  // cycles), one copy 645 / 470 and 774 / 620; obs 244 64 x 16 copies 256 / 207, 128 x 8 266 / 207, 40 x 24 471 / 204; more passes of five copies and more:
-  // 256 x 6 277 us here, 1024 x 8 986 (four each: 200 and 700).
-  if (ctx->mfma_variant >= 2 && (s.E <= 4 || (uint64_t)s.N * ((s.E + 3) / 4) <= (uint64_t)ctx->num_cus))
-    return launch_rollout_quad_spread(ctx, gen, theta, noise, A, B, returns, ep_len, fitness, st);
   switch (ctx->mfma_variant) {
     case 0: return launch_variant<V32<4>>(ctx, a, units, st);
     case 1: return launch_variant<V64<4>>(ctx, a, units, st);

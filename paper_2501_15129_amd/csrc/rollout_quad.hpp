@@ -817,8 +817,6 @@ int launch_quad_obs64(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_
   return launch_quad_copies<BF16, NW, 16, M, true, NEAR>(ctx, a, fitness, st);
 }
 
-int narrow_copies(const es_config& c, uint64_t copies, int cus);      // of a pass of a narrow policy: 1, 4 or 16
-
 // one source file each (compile time); M = hidden layers of the context
 int launch_quad_bf16_mid(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st);     // two wavefronts, one or two layers
 int launch_quad_bf16_wide(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st);    // four wavefronts, one or two layers

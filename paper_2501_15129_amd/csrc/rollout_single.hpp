@@ -234,8 +234,6 @@ int launch_single_mode(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream
   return plain ? launch_single_act<HW, CJ, 2, M>(ctx, a, fitness, st) : launch_single_act<HW, CJ, -1, M>(ctx, a, fitness, st);
 }
 
-bool single_pays(const es_config& c, uint64_t copies, int cus);
-
 // one source file each (compile time)
 int launch_single_mid(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st);      // four wavefronts: up to 128 units
 int launch_single_wide(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st);     // eight

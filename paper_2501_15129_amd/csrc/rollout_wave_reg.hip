@@ -49,9 +49,16 @@ static void launch_fixed(int mode, dim3 grid, size_t lds, hipStream_t st, const 
 // Four wavefronts share an episode (rollout_wave_team.hpp) while every episode has a compute unit of its own; two episodes on a compute
 // unit only with four layers.  Per 200 steps, four wavefronts against one: 256 episodes of 17-64-64-6 84 us against 90, 512 episodes 108 against
 // 91; three layers of 64 97 against 145, 145 against 147; 30-40x4-6 124 against 212, 178 against 218, 640 episodes 241 against 219.
-static bool reg_team(const es_ctx* ctx) {
-  const Shape& s = ctx->shp;
-  return s.nh > 32 && s.m >= 2 && s.m <= 4 && (uint64_t)s.N * s.E <= (uint64_t)ctx->num_cus * (s.m == 4 ? 2u : 1u);
+bool reg_team(const es_config& c, uint64_t copies, int cus) {
+  const uint32_t m = c.num_hidden ? c.num_hidden : 2;
+  return c.hid_dim > 32 && m >= 2 && m <= 4 && c.pop * copies <= (uint64_t)cus * (m == 4 ? 2u : 1u);
+}
+
+std::string team_variant_name(const es_config& c) {
+  const uint32_t m = c.num_hidden ? c.num_hidden : 2;
+  const char *obs = c.obs_dim <= 20 ? "20" : c.obs_dim <= 32 ? "32" : c.obs_dim <= 48 ? "48" : "64", *act = c.act_dim <= 4 ? "4" : c.act_dim <= 6 ? "6" : c.act_dim <= 8 ? "8" : "16";
+  const std::string s = std::string(c.dtype == 1 ? "rollout_wave_reg_team_bf16<obs<=" : "rollout_wave_reg_team_f32<obs<=") + obs + ",hid<=64,act<=" + act + ">";
+  return m == 2 ? s : s + ",depth" + std::to_string(m);
 }
 
 int launch_rollout_reg(es_ctx* ctx, uint32_t gen, const float* theta, const void* noise, const float* A,
@@ -81,7 +88,7 @@ int launch_rollout_reg(es_ctx* ctx, uint32_t gen, const float* theta, const void
   if (v < 0 || s.no > 64 || s.nh > 64 || s.na > 16 || s.m > 4)
     return fail(ctx, ES_EUNSUPPORTED, "es_rollout: no register-resident binary32 variant for this shape");
   int rc = ES_OK;
-  if (reg_team(ctx)) {
+  if (ctx->rollout_kind == ROLLOUT_WAVE_TEAM) {
     rc = c.dtype == 1 ? launch_team_bf16(ctx, grid, whole, st, a) : launch_team_f32(ctx, mode, grid, whole, st, a);
     if (rc != ES_OK) return rc;
   } else if (v == 0) launch_fixed<3, 2, 3>(mode, grid, lds, st, a);

@@ -22,9 +22,18 @@ def test_columns_per_pass_follow_the_kernel():
     from paper_2501_15129_amd import EsContext
     from paper_2501_15129_amd.workloads import Workload
     base = Workload("paper-base", pop=128, envs=1, horizon=1000, obs=8, hid=256, act=2, dtype=0, noise_dtype=0, seed=5)
-    for kw, columns in ((dict(), 4), (dict(pop=64, episodes=16), 4), (dict(episodes=16), 16), (dict(episodes=8), 4), (dict(dtype=1, noise_dtype=1), 4),
-                        (dict(dtype=1, noise_dtype=1, episodes=16), 16), (dict(dtype=1, noise_dtype=1, envs=4, obs=244, act=17), 16)):
-        assert columns_per_pass(EsContext(replace(base, **kw)).rollout_kernel) == columns, kw
+    for kw, columns in ((dict(pop=64, episodes=16), 4), (dict(episodes=16), 16), (dict(episodes=8), 4), (dict(dtype=1, noise_dtype=1), 4),
+                        (dict(dtype=1, noise_dtype=1, episodes=16), 16), (dict(dtype=1, noise_dtype=1, envs=4, obs=244, act=17), 4),
+                        (dict(dtype=1, noise_dtype=1, envs=16, obs=244, act=17), 16), (dict(hid=48, pop=1000, envs=16), 16)):
+        kernel = EsContext(replace(base, **kw)).rollout_kernel
+        assert "mfma" in kernel and columns_per_pass(kernel) == columns, kw
+
+
+def test_one_copy_per_workgroup_is_no_matrix_core_kernel():
+    """... so that the benchmark prices it against the vector ALU."""
+    from paper_2501_15129_amd import EsContext
+    from paper_2501_15129_amd.workloads import Workload
+    assert "mfma" not in EsContext(Workload("paper-base", pop=128, envs=1, horizon=1000, obs=8, hid=256, act=2, dtype=0, noise_dtype=0, seed=5)).rollout_kernel
 
 
 @pytest.mark.gpu

@@ -31,20 +31,34 @@ def test_env_dtype_counts_with_bf16_operands_only(kernel, obs, hid, act, envs, l
 
 
 @pytest.mark.parametrize("kw,name", [
-    (dict(), "rollout_mfma_quad_f32<obs32,hid256,act16>"),
-    (dict(obs=16, envs=16, pop=16), "rollout_mfma_quad_f32<obs16,hid256,act16>"),
+    (dict(), "rollout_single_f32<obs32,hid256,act16>"),
+    (dict(obs=16, envs=16, pop=16), "rollout_single_f32<obs20,hid256,act16>"),
+    (dict(obs=12, pop=512), "rollout_single_f32<obs12,hid256,act16>"),
+    (dict(obs=33, hid=128, num_hidden=3), "rollout_single_f32<obs64,hid128,act16>,depth3"),
+    (dict(envs=4), "rollout_mfma_quad_f32<obs32,hid256,act16>"),
+    (dict(obs=16, pop=128, envs=3), "rollout_mfma_quad_f32<obs16,hid256,act16>"),
+    (dict(obs=33), "rollout_mfma_quad_f32<obs64,hid256,act16>"),
     (dict(envs=16), "rollout_mfma_reg_f32<obs32,hid256,act16>"),
     (dict(envs=16, hid=128), "rollout_mfma_quad_f32<obs32,hid128,act16>"),
-    (dict(hid=64, obs=17, act=6), "rollout_wave_reg_f32<17,64,6>"),
-    (dict(hid=64, obs=17, act=6, envs=16, pop=1000), "rollout_mfma_quad_f32<obs32,hid64,act16>"),
-    (dict(hid=64, obs=17, act=6, num_hidden=3), "rollout_wave_reg_f32<obs<=32,hid<=64,act<=8>,depth3"),
+    (dict(hid=64, obs=17, act=6), "rollout_wave_reg_team_f32<obs<=20,hid<=64,act<=6>"),
+    (dict(hid=64, obs=17, act=6, pop=258), "rollout_wave_reg_f32<17,64,6>"),
+    (dict(hid=64, obs=17, act=6, envs=8, pop=512), "rollout_mfma_quad_f32<obs32,hid64,act16>"),
+    (dict(hid=64, obs=17, act=6, envs=16, pop=1000), "rollout_mfma_cols_f32<obs20,hid64,act8>"),
+    (dict(hid=30, obs=40, act=9, envs=16, pop=1000), "rollout_mfma_cols_f32<obs48,hid32,act16>"),
+    (dict(hid=20, envs=16, pop=1000, dtype=1, noise_dtype=1), "rollout_mfma_cols_bf16<obs32,hid32,act16>"),
+    (dict(hid=64, obs=17, act=6, num_hidden=3), "rollout_wave_reg_team_f32<obs<=20,hid<=64,act<=6>,depth3"),
+    (dict(hid=64, obs=17, act=6, num_hidden=3, pop=258), "rollout_wave_reg_f32<obs<=32,hid<=64,act<=8>,depth3"),
+    (dict(hid=40, obs=50, num_hidden=4, pop=512, dtype=1, noise_dtype=1), "rollout_wave_reg_team_bf16<obs<=64,hid<=64,act<=8>,depth4"),
     (dict(hid=24, num_hidden=5), "rollout_wave_lds_f32"),
     (dict(obs=70, hid=100), "rollout_wave_lds_f32"),
     (dict(dtype=1, noise_dtype=1, hid=48, num_hidden=1), "rollout_wave_reg_bf16<obs<=32,hid<=64,act<=8>,depth1"),
     (dict(dtype=1, noise_dtype=1, hid=100, obs=70), "rollout_mfma_quad_bf16<obs128,hid128,act32>"),
     (dict(dtype=1, noise_dtype=1, num_hidden=3), "rollout_mfma_quad_bf16<obs32,hid256,act16>,depth3"),
     (dict(dtype=1, noise_dtype=1, envs=16, pop=512, num_hidden=3), "rollout_mfma_reg_bf16<obs32,hid256,act16>,depth3"),
-    (dict(dtype=1, noise_dtype=1, envs=4, obs=244, act=17), "rollout_mfma_reg_bf16<obs256,hid256,act32>"),
+    (dict(dtype=1, noise_dtype=1, envs=4, obs=244, act=17), "rollout_mfma_quad_bf16<obs256,hid256,act32>"),
+    (dict(dtype=1, noise_dtype=1, envs=4, obs=129), "rollout_mfma_quad_bf16<obs192,hid256,act32>"),
+    (dict(dtype=1, noise_dtype=1, envs=16, obs=40, act=17, pop=64), "rollout_mfma_quad_bf16<obs128,hid256,act32>"),
+    (dict(dtype=1, noise_dtype=1, envs=16, obs=244, act=17), "rollout_mfma_reg_bf16<obs256,hid256,act32>"),
     (dict(dtype=1, noise_dtype=1, env_dtype=1), "rollout_mfma_reg_bf16<obs32,hid256,act16>,env_f32"),
     (dict(dtype=1, noise_dtype=1, obs=70, hid=40), "rollout_wave_lds_bf16"),
 ], ids=lambda v: v if isinstance(v, str) else "")

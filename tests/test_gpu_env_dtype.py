@@ -26,7 +26,7 @@ CASES = [
     (Workload("envf-reg-13-29-7", pop=10, envs=5, horizon=60, obs=13, hid=29, act=7, dtype=1, noise_dtype=1, seed=61, env_dtype=1), "wave_reg_bf16"),
     (Workload("envf-reg-net16-relu", pop=8, envs=2, horizon=60, obs=27, hid=16, act=8, dtype=1, noise_dtype=1, seed=62, env_dtype=1, hidden_act=1), "wave_reg_bf16"),
     (Workload("envf-lds-70-100-9", pop=4, envs=2, horizon=40, obs=70, hid=100, act=9, dtype=1, noise_dtype=1, seed=63, env_dtype=1), "wave_lds_bf16"),
-    (Workload("envf-reg-depth3", pop=4, envs=2, horizon=30, obs=20, hid=40, act=5, dtype=1, noise_dtype=1, seed=64, env_dtype=1, num_hidden=3), "wave_reg_bf16"),
+    (Workload("envf-reg-depth3", pop=4, envs=2, horizon=30, obs=20, hid=40, act=5, dtype=1, noise_dtype=1, seed=64, env_dtype=1, num_hidden=3), "wave_reg_team_bf16"),
     (Workload("envf-mfma32", pop=6, envs=16, horizon=40, obs=27, hid=256, act=8, dtype=1, noise_dtype=1, seed=65, env_dtype=1), "mfma_reg_bf16"),
     (Workload("envf-mfma32-E3-relu", pop=4, envs=3, horizon=40, obs=27, hid=256, act=8, dtype=1, noise_dtype=1, seed=66, env_dtype=1, hidden_act=1), "mfma_reg_bf16"),
     (Workload("envf-mfma32-E21-linear", pop=4, envs=21, horizon=30, obs=32, hid=200, act=16, dtype=1, noise_dtype=1, seed=67, env_dtype=1, out_tanh=0), "mfma_reg_bf16"),

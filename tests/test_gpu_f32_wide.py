@@ -29,7 +29,9 @@ def _case(es, w, gen=1, obs_norm=None):
     a_mat, b_mat, theta = make_inputs(w)
     theta = (theta + np.random.default_rng(w.seed).standard_normal(theta.size) * 0.02).astype(np.float32)     # non-zero biases
     ctx = es.EsContext(w)
-    assert "quad_f32" in ctx.rollout_kernel, ctx.rollout_kernel
+    # up to one episode per compute unit: one copy per workgroup, where the shape has that kernel
+    one = w.pop * ctx.episodes <= torch.cuda.get_device_properties(0).multi_processor_count and (w.obs <= 32 or w.hid <= 128)
+    assert ("single_f32" if one else "quad_f32") in ctx.rollout_kernel, ctx.rollout_kernel
     keep = None
     if obs_norm is not None:
         keep = (dev(obs_norm[0]), dev(obs_norm[1]))
@@ -92,10 +94,11 @@ def test_four_copy_variant_is_chosen_up_to_eight_copies_or_one_pass_per_compute_
     for envs, episodes, pop, four in ((1, 1, 6, True), (4, 2, 6, True), (8, 1, 6, True), (3, 3, 6, True), (16, 1, 6, True), (16, 1, 64, True),
                                       (8, 1, 1000, True), (3, 3, 86, False), (16, 1, 66, False), (16, 1, 1000, False)):
         ctx = es.EsContext(replace(BASE, envs=envs, episodes=episodes, pop=pop))
-        assert ("quad_f32" in ctx.rollout_kernel) == four, (envs, episodes, pop, ctx.rollout_kernel)
-        assert ("mfma_reg_f32" in ctx.rollout_kernel) != four, (envs, episodes, pop, ctx.rollout_kernel)
-    ctx = es.EsContext(replace(BASE, num_hidden=1))
-    assert "quad_f32" in ctx.rollout_kernel and "depth1" in ctx.rollout_kernel, ctx.rollout_kernel
+        family = "mfma_reg_f32" if not four else "single_f32" if envs * episodes * pop <= 256 else "quad_f32"
+        assert family in ctx.rollout_kernel, (envs, episodes, pop, ctx.rollout_kernel)
+    for pop, family in ((6, "single_f32"), (66, "quad_f32")):
+        ctx = es.EsContext(replace(BASE, num_hidden=1, pop=pop))
+        assert family in ctx.rollout_kernel and "depth1" in ctx.rollout_kernel, ctx.rollout_kernel
 
 
 def test_rollout_f32_wide_with_observation_statistics(es):

@@ -23,9 +23,9 @@ BF = dict(dtype=1, noise_dtype=1)
     ids=lambda v: str(v) if not isinstance(v, dict) else "-".join(f"{k}{x}" for k, x in v.items()))
 def test_edges(es, obs, hid, act, kw):  # noqa: F811
     w = replace(F, name=f"columns-{obs}-{hid}-{act}", obs=obs, hid=hid, act=act, seed=801 + obs + hid)
-    assert "hid64" in _case(es, replace(w, **kw)).rollout_kernel
+    assert "rollout_mfma_cols_" in _case(es, replace(w, **kw)).rollout_kernel
 
 
 @pytest.mark.parametrize("kw", [dict(), dict(obs=64, hid=64, act=16, hidden_act=1), dict(BF, obs=40), dict(BF, obs=20, hid=64, hidden_act=1)], ids=str)
 def test_observation_statistics(es, kw):  # noqa: F811
-    _case(es, replace(F, name="columns-norm", seed=833, **kw), norm=True)
+    assert "rollout_mfma_cols_" in _case(es, replace(F, name="columns-norm", seed=833, **kw), norm=True).rollout_kernel

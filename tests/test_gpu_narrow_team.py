@@ -25,12 +25,13 @@ F = Workload("team", pop=4, envs=3, horizon=30, obs=17, hid=64, act=6, dtype=0, 
     ids=lambda v: str(v) if not isinstance(v, dict) else "-".join(f"{k}{x}" for k, x in v.items()))
 def test_edges(es, m, obs, hid, act, T, kw):  # noqa: F811
     w = replace(F, name=f"team-{obs}-{hid}x{m}-{act}-T{T}", num_hidden=m, obs=obs, hid=hid, act=act, horizon=T, seed=701 + obs + hid)
-    assert "wave_reg" in _case(es, replace(w, **kw)).rollout_kernel
+    assert "wave_reg_team_" in _case(es, replace(w, **kw)).rollout_kernel
 
 
 @pytest.mark.parametrize("m,dtype", [(2, 0), (3, 0), (4, 0), (2, 1), (3, 1)])
 def test_observation_statistics(es, m, dtype):  # noqa: F811
-    _case(es, replace(F, name=f"team-norm-x{m}-{dtype}", num_hidden=m, obs=40, dtype=dtype, noise_dtype=dtype, seed=733 + m), norm=True)
+    w = replace(F, name=f"team-norm-x{m}-{dtype}", num_hidden=m, obs=40, dtype=dtype, noise_dtype=dtype, seed=733 + m)
+    assert "wave_reg_team_" in _case(es, w, norm=True).rollout_kernel
 
 
 @pytest.mark.parametrize("m", [2, 3, 4])
@@ -44,8 +45,9 @@ def test_four_wavefronts_and_one_evaluate_the_same(es, m):  # noqa: F811
     many = replace(few, pop=few.pop + 2)
     a_mat, b_mat, theta = make_inputs(few)
     got = []
-    for w in (few, many):
+    for w, kernel in ((few, "rollout_wave_reg_team_f32"), (many, "rollout_wave_reg_f32")):
         ctx = es.EsContext(w)
+        assert kernel in ctx.rollout_kernel
         noise = ctx.alloc_noise()
         ctx.sample_population(3, noise)
         got.append(run_rollout(ctx, w, 3, theta, noise, a_mat, b_mat))

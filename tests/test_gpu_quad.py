@@ -86,8 +86,8 @@ F = Workload("quadf", pop=4, envs=4, horizon=30, obs=27, hid=256, act=8, dtype=0
     ids=lambda v: str(v) if not isinstance(v, dict) else "-".join(f"{k}{x}" for k, x in v.items()))
 def test_f32_edges(es, obs, hid, act, envs, layers, kw):
     w = replace(F, name=f"quadf-{obs}-{hid}x{layers}-{act}-E{envs}", obs=obs, hid=hid, act=act, envs=envs, num_hidden=layers, seed=501 + obs + hid)
-    ctx = _case(es, replace(w, **kw))
-    assert "quad_f32" in ctx.rollout_kernel
+    ctx = _case(es, replace(w, **kw))      # (small populations: one copy per workgroup up to 128 units, and up to 32 observations)
+    assert ("single_f32" if hid <= 128 or obs <= 32 else "quad_f32") in ctx.rollout_kernel
 
 
 @pytest.mark.parametrize("w", [
@@ -96,8 +96,8 @@ def test_f32_edges(es, obs, hid, act, envs, layers, kw):
     replace(B, name="quadn-bf16-32-64", pop=1100, envs=8, horizon=12, obs=32, hid=64, act=16), replace(B, name="quadn-bf16-33-16", pop=900, envs=11, horizon=12, obs=33, hid=16, act=1)],
     ids=lambda w: w.name)
 def test_narrow_policies_in_numbers(es, w):
-    name = _case(es, w).rollout_kernel
-    assert "quad" in name and "hid64" in name
+    """passes of sixteen copies, one of them of four (the latter's own: test_gpu_larger_populations.py)"""
+    assert ("rollout_mfma_quad_f32<obs32,hid64,act16>" if w.hid == 49 else "rollout_mfma_cols_") in _case(es, w).rollout_kernel
     _case(es, w, norm=True)
 
 

@@ -5,6 +5,7 @@ from dataclasses import replace
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2501_15129_amd.workloads import Workload, make_inputs
 from gpu_util import run_rollout
@@ -23,23 +24,27 @@ F = Workload("single", pop=4, envs=1, horizon=30, obs=17, hid=128, act=6, dtype=
     ids=lambda v: str(v) if not isinstance(v, dict) else "-".join(f"{k}{x}" for k, x in v.items()))
 def test_edges(es, m, obs, hid, act, T, kw):  # noqa: F811
     w = replace(F, name=f"single-{obs}-{hid}x{m}-{act}-T{T}", num_hidden=m, obs=obs, hid=hid, act=act, horizon=T, seed=951 + obs + hid)
-    assert "f32" in _case(es, replace(w, **kw)).rollout_kernel
+    assert "rollout_single_f32" in _case(es, replace(w, **kw)).rollout_kernel
 
 
 @pytest.mark.parametrize("kw", [dict(), dict(num_hidden=3, obs=50), dict(hid=256, obs=30), dict(hid=200, num_hidden=1, hidden_act=1)], ids=str)
 def test_observation_statistics(es, kw):  # noqa: F811
-    _case(es, replace(F, name="single-norm", **kw), norm=True)
+    assert "rollout_single_f32" in _case(es, replace(F, name="single-norm", **kw), norm=True).rollout_kernel
 
 
-@pytest.mark.parametrize("kw,pops", [(dict(), (256, 258)), (dict(envs=2), (256, 258)), (dict(envs=4, num_hidden=3), (128, 130)), (dict(hid=256, envs=4), (64, 66)), (dict(hid=200, num_hidden=1), (256, 258))], ids=str)
-def test_both_sides_of_the_rule(es, kw, pops):  # noqa: F811
+# (the number of individuals up to which the rule takes them, in quarters of the compute units)
+@pytest.mark.parametrize("kw,quarters", [(dict(), 4), (dict(envs=2), 4), (dict(envs=4, num_hidden=3), 2), (dict(hid=256, envs=4), 1), (dict(hid=200, num_hidden=1), 4)], ids=str)
+def test_both_sides_of_the_rule(es, kw, quarters):  # noqa: F811
     """The two kernels add the same products in another order, which forty contracting steps turn into less than 1e-5 of a return."""
     got = []
+    most = torch.cuda.get_device_properties(0).multi_processor_count * quarters // 8 * 2
+    pops = (most, most + 2)
     base = replace(F, name="single-rule", horizon=40, **kw)
     a_mat, b_mat, theta = make_inputs(replace(base, pop=pops[0]).contractive())
-    for pop in pops:
+    for pop, kernel in zip(pops, ("rollout_single_f32", "rollout_mfma_quad_f32")):
         w = replace(base, pop=pop).contractive()
         ctx = es.EsContext(w)
+        assert kernel in ctx.rollout_kernel
         noise = ctx.alloc_noise()
         ctx.sample_population(3, noise)
         got.append(run_rollout(ctx, w, 3, theta, noise, a_mat, b_mat))
