@@ -163,7 +163,7 @@ __device__ __forceinline__ float tanh_b(float x, float cb) {
 
 // BF16: operand type.  NW: wavefronts (hidden width <= 64 NW).  KG: observation width in groups of four (<= 16: every
 // wavefront holds the whole state; else the rows are spread, 64 NW >= 4 KG).  M: hidden layers.  NC: copies a pass serves
-// (4, or 1: the activations of the three idle copies and most of the transposes drop out).  RELU / NORM: hidden
+// (4; 2 or 1: the activations of the idle copies and most of the transposes drop out).  RELU / NORM: hidden
 // activation, observation statistics (compile-time: a taken branch costs a single wavefront some sixty cycles).
 // NEAR: the tanh that is accurate near zero (bf16 policies of fewer than 128 units).
 template <bool BF16_, int NW_, int KG_, int M_, int NC_, bool RELU_, bool NORM_, bool NEAR_>
@@ -786,12 +786,11 @@ int launch_quad_options(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStrea
   return relu ? launch_quad_shape<QuadShape<BF16, NW, KG, M, NC, true, false, NEAR>>(ctx, a, fitness, st)
               : launch_quad_shape<QuadShape<BF16, NW, KG, M, NC, false, false, NEAR>>(ctx, a, fitness, st);
 }
-// obs <= 64: the width class (in binary32, where a group of four costs four instructions twice a step, one more class;
-// observation statistics only in the widest) and the number of copies of a pass
 // Copies of a pass: as few as the chip can take side by side, one wavefront per SIMD, since the activations of a copy are on the chain of a step.
 // Per 100 steps of bf16 27-100-100-8, four copies a pass / as chosen: 128 individuals x 2 copies 97 / 75 us (one), 128 x 3 97 / 84 (one), 128 x 5 100 / 87
 // (two), 512 x 2 127 / 85 (two; 42 us of it wavefront_place), 8-256-256-2 64 x 8 129 / 118 (two); three layers per 200 steps, 27-100x3-6 128 x 4
-// 321 / 270 (two), 8-256x3-6 512 x 2 614 / 535 (two).  (Four layers split the action layer by lane groups, which needs all four rows or one.)
+// 321 / 270 (two), 8-256x3-6 512 x 2 614 / 535 (two).  An individual is then staged by several workgroups, which very few steps do not bring back: 27-256-256-8
+// 128 x 2 2 steps 32 / 34, 244-256-256-17 64 x 4 44 / 49.  (Four layers split the action layer by lane groups, which needs all four rows or one.)
 template <bool BF16, int NW, int KG, int M, bool WITH_NORM, bool NEAR>
 int launch_quad_copies(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st) {
   auto apart = [&](uint32_t nc) { return (uint64_t)a.N * ((a.E + nc - 1u) / nc) * NW <= 4u * (uint64_t)ctx->num_cus; };
@@ -801,6 +800,8 @@ int launch_quad_copies(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream
   }
   return launch_quad_options<BF16, NW, KG, M, 4, WITH_NORM, NEAR>(ctx, a, fitness, st);
 }
+// obs <= 64: the width class (in binary32, where a group of four costs four instructions twice a step, one more class;
+// observation statistics only in the widest)
 template <bool BF16, int NW, int M, bool NEAR>
 int launch_quad_obs64(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st) {
   if constexpr (!BF16) {

@@ -13,7 +13,7 @@
 //   * state, action and environment are kept by every wavefront for itself from the same operands in the same order (bit-identical, no
 //     exchange); A s is computed where a hand-over would be waited for.
 // Bound: the multiply-adds of the wavefronts on a SIMD, which do not overlap (256 units: 128 each, two wavefronts), then the two hand-overs of a step.
-// Whole rollout, 1000 steps of 8-256-256-2, 128 individuals: 1.56 ms on the four-copy kernel -> 1.06 ms; 17-128-128-6, 128 x 100 steps 126 -> 70 us.  Which
+// Whole rollout, 1000 steps of 8-256-256-2, 128 individuals: 1.56 ms on the four-copy kernel -> 1.03 ms; 17-128-128-6, 128 x 100 steps 126 -> 70 us.  Which
 // populations: single_pays (rollout_quad.hip).
 #pragma once
 

@@ -13,7 +13,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
-// Staging iterations whose loads are in flight together (at 244-256-256-17 4 is 24 % slower, 16 spills).
+// Staging iterations whose loads are in flight together (at 244-256-256-17 4 is 24 % slower, 16 spills; QuadShape::BATCH).
 constexpr int STAGE_BATCH = 8;
 
 // Four binary32 values -> four bf16 (round to nearest even), by the packed hardware convert.
