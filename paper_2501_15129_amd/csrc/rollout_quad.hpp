@@ -229,7 +229,7 @@ struct QuadShape {
   // (lane_now), BATCH halves a batch where a second workgroup fills the waits.  4096 x 4 copies, 2 steps, neither / FRESH / both: 244-256-256-17 (96 registers) 567 / 560 / 692 us, 100-256-256-17 (224)
   // 388 / 416 / 521; 512 x 2 of 27-256-256-8 (72) 42 / 52 / 35
   static constexpr int SLACK = (OCC == 3 ? 168 : OCC == 2 ? 256 : 512) - WREGS;
-  static constexpr bool FRESH = SLACK <= 96 && M < 4;      // (four layers: 65 us of 2 steps without, 70 with)
+  static constexpr bool FRESH = SLACK <= 112 && M < 4;      // (41-74-74-3, 104 registers, 182 x 6 copies, 34 steps: 63.5 us without, 58.8 with; four layers: 65 us of 2 steps without, 70 with)
   static constexpr int BATCH = OCC == 2 && SLACK < 80 ? STAGE_BATCH / 2 : STAGE_BATCH;
   static constexpr bool PLACED = NW == 2 && OCC > 1;                     // may be launched with four wavefronts, two of which leave (wavefront_place)
   // first K group of portion k of A s: in the first activation, after the first exchange, in the second activation, after
