@@ -19,13 +19,16 @@
 //     same operands in the same order (bit-identical, no exchange); beyond that the state rows are spread over the
 //     wavefronts and cross the LDS as well (one more barrier).
 //   * NW = 1: nothing leaves the wavefront; no barriers.
+//   * bf16, NW > 1: a product whose input has crossed the LDS runs on a larger shape, v_smfmac_f32_16x16x64_bf16, at twice the weights per cycle (pair_mac).
 // Returns are accumulated per lane and added up once after the last step.
 // Bound: the dependent chain of a step when a few individuals are evaluated; with a full chip, matrix-core issue
 // (8.5 cycles per 4x4 instruction, measured) plus the vector work of the activations (5.8 cycles per instruction of a
 // lone wavefront).
 // Measured, whole rollout, T = 1000 unless noted: bf16 8-256-256-2, 128 individuals x 1 copy 1.23 ms (padded 16-column kernel) -> 0.77 ms -> 0.74 with
 // the books and the two branches of a step's end behind the loop; bf16 27-100-100-8, 128 x 5 copies, T = 400: 8.05 ms (LDS kernel) -> 0.34 ms -> 0.27 with
-// passes of two copies on SIMDs of their own; 244-256-256-17, 1024 x 4 copies, T = 1000: 6.3 ms (16-column kernel with compacted columns) -> 5.7.
+// passes of two copies on SIMDs of their own; 244-256-256-17, 1024 x 4 copies, T = 1000: 6.3 ms (16-column kernel with compacted columns) -> 5.7.  Paired products (below),
+// 200 steps: 244-256-256-17 128 x 1 292 -> 222 us, 1024 x 4 1278 -> 1086; 8-256-256-2 128 x 1 166 -> 142, 1024 x 4 551 -> 494; 20-100x3-6 128 x 1 246 -> 195; 27-100-100-8 128 x 1
+// 128 -> 111, 1024 x 4 256 -> 248 (two steps of 4096 x 4 of 244-256-256-17, all staging: 569 -> 584).
 #pragma once
 
 #include <type_traits>
@@ -137,6 +140,73 @@ template <> struct Oper<false> {
   static __device__ __forceinline__ V4 zero() { return V4{0.f, 0.f, 0.f, 0.f}; }
 };
 
+// Paired products, v_smfmac_f32_16x16x64_bf16: sixteen units x 64 K values of weights an instruction in the time of a dense 16x16x32 product (16.6 cycles
+// measured, dependent or not; a vector instruction behind it waits 13 of them), so twice the weights per cycle of it or of the 4x4 shapes (8.9 cycles for 256 weights).  The instruction skips half of every four K values of its first operand, row by row; here
+// a copy is TWO rows, one that takes the first two values of every four and one that takes the other two, and the sum of the two rows
+// is the whole product.  The weights are the dense operand.  What is doubled is the rows, of which one to four copies leave most idle.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+
+__device__ __forceinline__ f32x4 pair_mac(u32x4 act, u32x8 w, f32x4 acc, int which) {
+  return __builtin_amdgcn_smfmac_f32_16x16x64_bf16(__builtin_bit_cast(bf16x8, act), __builtin_bit_cast(bf16x16, w), acc, which, 0, 0);
+}
+// Rows of the product: row 4 g + i stands in result register i of lane group g.  One copy: its first half in even groups, its second in odd ones.  Two: copy 0 in
+// even groups, 1 in odd ones, the halves in registers 0 and 1.  Four: copies 0 and 1 in even groups, 2 and 3 in odd ones, halves in registers 2 k and 2 k + 1.
+// (Groups 2 and 3 repeat 0 and 1: see pair_units.)
+template <int NC> __device__ __forceinline__ int pair_copy(int row) {
+  const int odd = (row >> 2) & 1;
+  return NC == 1 ? 0 : NC == 2 ? odd : 2 * odd + ((row >> 1) & 1);
+}
+template <int NC> __device__ __forceinline__ int pair_half(int row) { return NC == 1 ? (row >> 2) & 1 : row & 1; }
+// The four tiles' products -> a unit per lane (lane group g: tile g), a register per copy.
+template <int NC>
+__device__ __forceinline__ void pair_units(const f32x4 (&d)[4], bool upper, float (&z)[NC]) {
+  auto swap = [](float& x, float& y) {      // odd lane groups of x against even ones of y
+    const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y), false, false);
+    x = __builtin_bit_cast(float, (unsigned)r[0]); y = __builtin_bit_cast(float, (unsigned)r[1]);
+  };
+  if constexpr (NC == 1) {
+    float x = upper ? d[2][0] : d[0][0], y = upper ? d[3][0] : d[1][0];
+    swap(x, y);
+    z[0] = x + y;
+  } else {
+#pragma unroll
+    for (int k = 0; k < NC / 2; ++k) {
+      float v[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[t] = d[t][2 * k] + d[t][2 * k + 1];
+      float x = upper ? v[2] : v[0], y = upper ? v[3] : v[1];
+      swap(x, y);
+      z[k] = x; z[k + NC / 2] = y;
+    }
+  }
+}
+// One row (unit) per lane, a register per copy -> rows of an exchange buffer, one per copy: `to` is the lane's place in the first.  (As an operand through a
+// transpose inside the lane quad and one write of four units: 9 to 5 instructions more.)
+template <int NC, int PITCH>
+__device__ __forceinline__ void put_units(unsigned char* to, const float (&v)[NC]) {
+#pragma unroll
+  for (int c = 0; c < NC; c += 2) {
+    const uint32_t r = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{v[c], v[c + 1 < NC ? c + 1 : c]}, bf16x2));
+    *reinterpret_cast<uint16_t*>(to + 2 * c * PITCH) = (uint16_t)r;
+    if (c + 1 < NC) *reinterpret_cast<uint16_t*>(to + 2 * (c + 1) * PITCH) = (uint16_t)(r >> 16);
+  }
+}
+// Place of unit u of 64 in a row of an exchange buffer: the first operand's share of lane (q, half), values 4 j + 2 half and 4 j + 2 half + 1 of q's sixteen, is contiguous.
+__device__ __forceinline__ int pair_place(int u) { return (u & 48) + 8 * ((u >> 1) & 1) + 2 * ((u & 15) >> 2) + (u & 1); }
+// registers of a tile's product that count
+template <int NC> __device__ __forceinline__ void pair_zero(f32x4 (&d)[4]) {
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (i < (NC == 4 ? 4 : NC)) d[t][i] = 0.0f;
+      else { float any; asm volatile("" : "=v"(any)); d[t][i] = any; }
+    }
+  }
+}
+
 // A value known to be the same in every lane, as a scalar.
 __device__ __forceinline__ uint32_t uniform(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 __device__ __forceinline__ float uniform(float v) { return __builtin_bit_cast(float, uniform(__builtin_bit_cast(uint32_t, v))); }
@@ -149,6 +219,7 @@ __device__ __forceinline__ void pin_agpr(f32x4& v) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) { float t = v[j]; asm volatile("" : "+a"(t)); v[j] = t; }
 }
+__device__ __forceinline__ void pin_agpr(u32x8& v) { asm volatile("" : "+a"(v)); }
 
 // tanh(x + b) as 1 - 2 / (2^{c (x + b)} + 1) with cb = c b, c = 2 log2 e: the bias costs no instruction of its own
 constexpr float TANH_C = 2.88539008f;
@@ -175,12 +246,16 @@ struct QuadShape {
   static constexpr int NT = 64 * NW, HID = 64 * NW, HG = 16 * NW;        // threads, padded hidden width, its K groups
   static constexpr bool SPREAD = KG > 16;                                // state rows over the wavefronts
   static constexpr int NR = (KG + 15) / 16;                              // operand registers of the state
+  // products whose input comes through the LDS run as paired ones (pair_mac): the layers behind the first one, and A s and the first where rows are spread
+  static constexpr bool PAIRS_H = BF16 && NW > 1 && M > 1, PAIRS_X = BF16 && SPREAD;
+  using WX = std::conditional_t<PAIRS_X, quad::u32x8[NR][4], typename O::V4[KG]>;                 // a lane's weights of the first layer, its elements of A
+  using WH = std::conditional_t<PAIRS_H, quad::u32x8[NW][4], typename O::V4[M > 1 ? HG : 1]>;     // ... of a layer behind it
   static constexpr int KGA = SPREAD ? 8 : 4;                             // action width in groups of four
   static constexpr int NA = 4 * KGA;                                     // padded action width
   static constexpr int ENV_ROWS = SPREAD ? 64 * NW : 64;
   static constexpr int COLS = KG < 8 ? 16 : BF16 && KG >= 16 ? 64 : 32;    // columns of a staging round
   static constexpr int GR = COLS / 4;                                    // ... in groups
-  static constexpr int PWIN = O::PITCH;                                  // window pitch: vector reads of consecutive rows hit distinct banks
+  static constexpr int PWIN = BF16 && NW > 1 ? 64 + 8 : O::PITCH;                                  // window pitch: vector reads of consecutive rows hit distinct banks
   static constexpr int PW3 = HID + 4;
   static constexpr int ES = (int)sizeof(Elem);
   // LDS map (bytes).  Exchange buffers: rows of HID elements, one per copy; the pad puts the four copies' rows 64 bytes apart
@@ -223,12 +298,19 @@ struct QuadShape {
   // before (one barrier a round).  Three workgroups would not fit the LDS: one layer, 1000 x 4 copies of 27-256-8, 200 steps 237 us, two windows 289
   static constexpr bool TWO_WIN = NW == 4 && OCC < 3;
   static constexpr int OFF_S0 = RUN_BYTES > (TWO_WIN ? 2 : 1) * WIN_BYTES ? RUN_BYTES : (TWO_WIN ? 2 : 1) * WIN_BYTES;
-  static constexpr int LDS_BYTES = (OFF_S0 + (KEEP_S0 ? 4 * NC * NT : 0) + 15) / 16 * 16;
+  // The widest states leave no registers for B beside the operands of paired products (sixteen would be reloaded from scratch memory every step), so a lane's part of B
+  // stays in LDS, [group pair][thread], and is fetched when the hidden layers' operands are done
+  static constexpr bool B_LDS = PAIRS_X && KG > 48;
+  static constexpr int OFF_B = (OFF_S0 + (KEEP_S0 ? 4 * NC * NT : 0) + 15) / 16 * 16;
+  static constexpr int LDS_BYTES = OFF_B + (B_LDS ? KGA / 2 * 16 * NT : 0);
   // Registers beside the weights while they are staged.  Where they are short, a batch of loads, or what the compiler derives from the lane's number once for
   // all individuals, is spilled, and the reloads are waited for one after the other between the loads: FRESH computes the lane's number anew
   // (lane_now), BATCH halves a batch where a second workgroup fills the waits.  4096 x 4 copies, 2 steps, neither / FRESH / both: 244-256-256-17 (96 registers) 567 / 560 / 692 us, 100-256-256-17 (224)
   // 388 / 416 / 521; 512 x 2 of 27-256-256-8 (72) 42 / 52 / 35
   static constexpr int SLACK = (OCC == 3 ? 168 : OCC == 2 ? 256 : 512) - WREGS;
+  // Few registers beside the weights: the next layer's operand in a ring of two reads (200 steps of 8-256-256-2, 256 x 4 copies: all four reads at once 247 us, sixteen
+  // registers reloaded from scratch memory every step; 198; four layers of 256 128 x 1 copy 355 / 317)
+  static constexpr bool TIGHT = PAIRS_H && SLACK <= 80 && (NC > 1 || M == 4);
   static constexpr bool FRESH = SLACK <= 112 && M < 4;      // (41-74-74-3, 104 registers, 182 x 6 copies, 34 steps: 63.5 us without, 58.8 with; four layers: 65 us of 2 steps without, 70 with)
   static constexpr int BATCH = OCC == 2 && SLACK < 80 ? STAGE_BATCH / 2 : STAGE_BATCH;
   static constexpr bool PLACED = NW == 2 && OCC > 1;                     // may be launched with four wavefronts, two of which leave (wavefront_place)
@@ -236,6 +318,14 @@ struct QuadShape {
   // the action's exchange, with the action's tanh
   static constexpr int env_at(int k) {
     constexpr bool two = M > 1;
+    if (PAIRS_X && two) {      // between a write and its barrier and between a read and its use, at both exchanges (other splits: within 1 % at four copies, 5 % slower with nothing before the barriers at one)
+      constexpr int n = 4 * NR, at[6] = {0, n / 4, n / 2, n * 3 / 4, n, n};
+      return at[k];
+    }
+    if (PAIRS_X) {
+      constexpr int n = 4 * NR, at[6] = {0, n * 3 / 8, n * 3 / 8, n * 3 / 8, n, n};
+      return at[k];
+    }
     if (SPREAD && two) {      // (244-256-256-17: 3 470 cycles a step with the split below, 3 330 with more of it behind the barriers)
       constexpr int at[6] = {0, KG / 8, KG * 3 / 8, KG / 2, KG * 7 / 8, KG};
       return at[k];
@@ -296,6 +386,27 @@ void rollout_quad_kernel(const QuadArgs a) {
   auto window = [&](int round) { return win + (S::TWO_WIN && (round & 1) ? S::WIN_BYTES / S::ES : 0); };
   auto window_read = [&] { if constexpr (!S::TWO_WIN) stage_sync(); };
   auto win_group = [&](int round, int row, int pitch, int g) { return *reinterpret_cast<const V4*>(window(round) + row * pitch + 4 * g); };
+  // Columns COLS r .. of a matrix from the window of `round` -> registers: K groups r GR .. of row l, or, for paired products, of lane l's rows 64 w + 16 t + (l & 15) of the
+  // four tiles, of which lane (q, n) supplies K values 8 q .. and 32 + 8 q .. of every 64.
+  auto take = [&](auto& W, auto rc, int round, int l) {
+    constexpr int r = decltype(rc)::value;
+    if constexpr (std::is_same_v<std::remove_reference_t<decltype(W[0])>, V4>) {
+#pragma unroll
+      for (int g = 0; g < GR; ++g) W[GR * r + g] = win_group(round, l, S::PWIN, g);
+    } else {
+#pragma unroll
+      for (int k = 0; k < COLS / 32; ++k) {
+        constexpr int per = 64 / COLS;      // rounds of 64 K values
+        const int j = 4 * (per == 2 ? r & 1 : k);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          const u32x4 v = *reinterpret_cast<const u32x4*>(window(round) + (64 * w + 16 * t + (l & 15)) * S::PWIN + 32 * k + 8 * (l >> 4));
+          u32x8& d = W[r / per][t];
+          d[j] = v.x; d[j + 1] = v.y; d[j + 2] = v.z; d[j + 3] = v.w;
+        }
+      }
+    }
+  };
 
   // FRESH: the lane and thread number, computed where they are needed.  What the compiler derives from the ones above and keeps from one individual to
   // the next does not fit the registers beside the weights there, and its reloads are waited for one after the other
@@ -307,20 +418,28 @@ void rollout_quad_kernel(const QuadArgs a) {
   };
   auto tid_now = [&] { return S::FRESH ? 64 * w + lane_now() : tid; };
 
-  // ---- environment matrices -> registers: Ae[g] = A[erow][4g .. 4g+3], Be[g] = B[erow][4g .. 4g+3] ----
-  V4 Ae[KG], Be[KGA];
+  // ---- environment matrices -> registers: Ae[g] = A[erow][4g .. 4g+3] (paired: see take), Be[g] = B[erow][4g .. 4g+3] ----
+  typename S::WX Ae;
+  V4 Be[S::B_LDS ? 1 : KGA];
+  u32x4* bl = reinterpret_cast<u32x4*>(lds + S::OFF_B);
   static_for<0, KG / GR>([&](auto rc) {
     constexpr int r = decltype(rc)::value;
     stage_cols<COLS, false>(window(r), S::PWIN, S::ENV_ROWS, no, no, COLS * r, a.A, NoiseRow{}, 0.0f, 0u, tid, threads);
     stage_sync();
-#pragma unroll
-    for (int g = 0; g < GR; ++g) Ae[GR * r + g] = win_group(r, erow, S::PWIN, g);
+    take(Ae, rc, r, S::PAIRS_X ? lane : erow);
     window_read();
   });
   stage_cols<4 * KGA, false>(window(KG / GR), S::PWIN, S::ENV_ROWS, no, na, 0, a.B, NoiseRow{}, 0.0f, 0u, tid, threads);
   stage_sync();
 #pragma unroll
-  for (int g = 0; g < KGA; ++g) Be[g] = win_group(KG / GR, erow, S::PWIN, g);
+  for (int g = 0; g < KGA; ++g) {
+    if constexpr (!S::B_LDS) {
+      Be[g] = win_group(KG / GR, erow, S::PWIN, g);
+    } else if (g % 2 == 0) {      // (read by this thread only)
+      const u32x2 b0 = win_group(KG / GR, erow, S::PWIN, g), b1 = win_group(KG / GR, erow, S::PWIN, g + 1);
+      bl[(g / 2) * NT + tid] = u32x4{b0.x, b0.y, b1.x, b1.y};
+    }
+  }
   float mu = 0.f, iv = 0.f;                            // observation statistics of this row (padded rows: scale 0)
   if (NORM && erow < no) { mu = a.obs_mean[erow]; iv = a.obs_inv[erow]; }
 
@@ -343,7 +462,9 @@ void rollout_quad_kernel(const QuadArgs a) {
     else if (a.noise_mode == 0u) nz.ptr = static_cast<const float*>(a.noise) + (size_t)row * a.ld;
 
     // ---- perturbed parameters -> LDS window -> registers ----
-    V4 W1[KG], Wh[M > 1 ? M - 1 : 1][M > 1 ? HG : 1], W3[S::W3N];
+    typename S::WX W1;
+    typename S::WH Wh[M > 1 ? M - 1 : 1];
+    V4 W3[S::W3N];
     // A lane's own biases, requested together before anything else (a load behind a bounds test would be waited for by itself: three latencies an
     // individual).  hb: as the activation takes them, c b for tanh, b for ReLU; b3: of this lane's action rows
     constexpr int RPL = S::RPL, NB = M + RPL;
@@ -368,9 +489,7 @@ void rollout_quad_kernel(const QuadArgs a) {
       constexpr int r = decltype(rc)::value;
       stage_cols<COLS, true, S::BATCH>(window(r), S::PWIN, HID, nh, no, COLS * r, a.theta, nz, scale, a.oW1, tid_now(), threads);
       stage_sync();
-      const int u = tid_now();
-#pragma unroll
-      for (int g = 0; g < GR; ++g) W1[GR * r + g] = win_group(r, u, S::PWIN, g);
+      take(W1, rc, r, S::PAIRS_X ? lane_now() : tid_now());
       window_read();
     });
     static_for<0, M - 1>([&](auto lc) {
@@ -379,9 +498,7 @@ void rollout_quad_kernel(const QuadArgs a) {
         constexpr int r = decltype(rc)::value, round = KG / GR + l * (HG / GR) + r;
         stage_cols<COLS, true, S::BATCH>(window(round), S::PWIN, HID, nh, nh, COLS * r, a.theta, nz, scale, a.oW2 + (uint32_t)l * (uint32_t)(nh * nh + nh), tid_now(), threads);
         stage_sync();
-        const int u = tid_now();
-#pragma unroll
-        for (int g = 0; g < GR; ++g) Wh[l][GR * r + g] = win_group(round, u, S::PWIN, g);
+        take(Wh[l], rc, round, S::PAIRS_H ? lane_now() : tid_now());
         window_read();
       });
     });
@@ -421,6 +538,7 @@ void rollout_quad_kernel(const QuadArgs a) {
       uint32_t alive = 0u;       // bit c: copy c of this pass still runs (uniform)
       float ninv[NC], ncost[NC], thr[NC];   // per copy while it runs: -1 / obs, -cost, threshold; 0, 0, +inf after its end
       int len[NC];
+      const int tid_b = tid_now();
       const int tid_p = tid_now(), erow_p = SPREAD ? tid_p : tid_p - 64 * w;
       float s[NC];               // state row of this lane, one register per copy (binary32)
       const bool mine = SPREAD || w == 0;      // the wavefront that adds up the state's share of the reward
@@ -448,7 +566,12 @@ void rollout_quad_kernel(const QuadArgs a) {
       float Rx = 0.0f;           // ... of copy x: action rows (ROWS_COPY)
 #pragma unroll
       for (int c = 0; c < NC; ++c) Rs[c] = 0.0f;
-      V4 sop[NR], pop[NORM ? NR : 1];           // the state as an operand: raw for A s, normalised for the policy
+      // a lane's part of paired products' first operand: elements from a row of an exchange buffer
+      const int prow = lane & 15, phalf = pair_half<NC>(prow), pcopy = pair_copy<NC>(prow), pat = 16 * (lane >> 4) + 8 * phalf, pwhich = phalf ? (int)0xEEEEEEEEu : 0x44444444;
+      const int pplace = pair_place(lane);
+      const bool upper = lane >= 32;
+      using SOp = std::conditional_t<S::PAIRS_X, u32x4, V4>;
+      SOp sop[NR], pop[NORM ? NR : 1];          // the state as an operand: raw for A s, normalised for the policy
       // one row (unit) per lane, a register per copy -> operand
       auto operand = [&](const float (&v)[NC]) {
         if constexpr (NC == 1) return O::gather(v[0]);
@@ -456,6 +579,18 @@ void rollout_quad_kernel(const QuadArgs a) {
         else return O::transpose(f32x4{v[0], v[1], v[2], v[3]}, p, q, psel);
       };
       auto publish = [&] {       // s -> operand (own registers, or the exchange buffer)
+        if constexpr (S::PAIRS_X) {
+          if (NW * 64 == 4 * KG || 64 * w < 4 * KG) {
+            put_units<NC, S::PX>(lds + S::OFF_X + 2 * (64 * w + pplace), s);
+            if constexpr (NORM) {
+              float sn[NC];
+#pragma unroll
+              for (int c = 0; c < NC; ++c) sn[c] = (s[c] - mu) * iv;
+              put_units<NC, S::PX>(lds + S::OFF_XP + 2 * (64 * w + pplace), sn);
+            }
+          }
+          return;
+        }
         const V4 t = operand(s);
         V4 tn = t;
         if constexpr (NORM) {
@@ -469,13 +604,19 @@ void rollout_quad_kernel(const QuadArgs a) {
             *reinterpret_cast<V4*>(lds + S::OFF_X + (x * S::PX + 64 * w + 4 * blk) * S::ES) = t;
             if (NORM) *reinterpret_cast<V4*>(lds + S::OFF_XP + (x * S::PX + 64 * w + 4 * blk) * S::ES) = tn;
           }
-        } else {
+        } else if constexpr (!SPREAD) {
           sop[0] = t;
           if (NORM) pop[0] = tn;
         }
       };
       auto fetch_state = [&] {
-        if constexpr (SPREAD) {
+        if constexpr (S::PAIRS_X) {
+#pragma unroll
+          for (int r = 0; r < NR; ++r) {
+            sop[r] = *reinterpret_cast<const u32x4*>(lds + S::OFF_X + (pcopy * S::PX + 64 * r + pat) * S::ES);
+            if (NORM) pop[r] = *reinterpret_cast<const u32x4*>(lds + S::OFF_XP + (pcopy * S::PX + 64 * r + pat) * S::ES);
+          }
+        } else if constexpr (SPREAD) {
 #pragma unroll
           for (int r = 0; r < NR; ++r) {
             sop[r] = *reinterpret_cast<const V4*>(lds + S::OFF_X + (x * S::PX + 64 * r + 4 * blk) * S::ES);
@@ -506,13 +647,21 @@ void rollout_quad_kernel(const QuadArgs a) {
             if (!S::ROWS_COPY) pin_sgpr(ncost[c]);
           }
         // (two wait states must lie between instructions on one accumulator: two accumulators alternate)
-        f32x4 accE[2] = {zero4, zero4};
+        f32x4 accE[2] = {zero4, zero4}, pairE[4];
+        if constexpr (S::PAIRS_X) pair_zero<NC>(pairE);
         // A s is off the chain of dependent layers: its K groups are issued in five portions, between the vector
         // instructions of the activations and where the chain waits for the LDS
+        auto env_done = [&] {      // (what has been issued so far stays in front of what follows)
+          if constexpr (S::PAIRS_X) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(pairE[k]));
+          }
+        };
         auto env_part = [&](auto from, auto to) {
           static_for<S::env_at(decltype(from)::value), S::env_at(decltype(to)::value)>([&](auto gc) {
             constexpr int g = decltype(gc)::value;
-            O::template mac<4, g % 16, g>(sop[g / 16], Ae[g], accE);
+            if constexpr (S::PAIRS_X) pairE[g % 4] = pair_mac(sop[g / 4], Ae[g / 4][g % 4], pairE[g % 4], pwhich);
+            else O::template mac<4, g % 16, g>(sop[g / 16], Ae[g], accE);
           });
         };
         auto bar = [] { __builtin_amdgcn_sched_barrier(0); };
@@ -522,63 +671,101 @@ void rollout_quad_kernel(const QuadArgs a) {
 #pragma unroll
           for (int k = 0; k < n; ++k) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, S::PAIRS_X ? 3 : 1, 0);
           }
+          env_done();
           bar();
         };
-        auto act = [&](const f32x4 (&v)[2], float b, float (&h)[NC]) {
+        // (v: two accumulators of the 4x4 shapes, or the four tiles of paired products)
+        auto act = [&](const auto& v, float b, float (&h)[NC]) {
+          float z[NC];
+          if constexpr (sizeof(v) == 4 * sizeof(f32x4)) {
+            pair_units<NC>(v, upper, z);
+          } else {
 #pragma unroll
-          for (int c = 0; c < NC; ++c) {
-            const float z = v[0][c] + v[1][c];
-            h[c] = S::RELU ? fmaxf(z + b, 0.f) : tanh_b<S::NEAR>(z, b);
+            for (int c = 0; c < NC; ++c) z[c] = v[0][c] + v[1][c];
           }
+#pragma unroll
+          for (int c = 0; c < NC; ++c) h[c] = S::RELU ? fmaxf(z[c] + b, 0.f) : tanh_b<S::NEAR>(z[c], b);
         };
         using I0 = std::integral_constant<int, 0>; using I1 = std::integral_constant<int, 1>; using I2 = std::integral_constant<int, 2>;
         using I3 = std::integral_constant<int, 3>; using I4 = std::integral_constant<int, 4>; using I5 = std::integral_constant<int, 5>;
         // ---- layer 1 ----
         bar();
-        f32x4 acc[2] = {zero4, zero4};
-        static_for<0, KG>([&](auto gc) {
-          constexpr int g = decltype(gc)::value;
-          if (S::OCC == 1 && KG > 16) pin_agpr(W1[g]);
-          O::template mac<4, g % 16, g>(NORM ? pop[NORM ? g / 16 : 0] : sop[g / 16], W1[g], acc);
-        });
+        f32x4 acc[S::PAIRS_X ? 4 : 2];
+        if constexpr (S::PAIRS_X) {
+          pair_zero<NC>(acc);
+          static_for<0, 4 * NR>([&](auto gc) {
+            constexpr int m = decltype(gc)::value / 4, k = decltype(gc)::value % 4;
+            if (S::OCC == 1) pin_agpr(W1[m][k]);
+            acc[k] = pair_mac(NORM ? pop[NORM ? m : 0] : sop[m], W1[m][k], acc[k], pwhich);
+          });
+        } else {
+          acc[0] = acc[1] = zero4;
+          static_for<0, KG>([&](auto gc) {
+            constexpr int g = decltype(gc)::value;
+            if (S::OCC == 1 && KG > 16) pin_agpr(W1[g]);
+            O::template mac<4, g % 16, g>(NORM ? pop[NORM ? g / 16 : 0] : sop[g / 16], W1[g], acc);
+          });
+        }
         // the reward's state term, from the pre-step state
 #pragma unroll
         for (int c = 0; c < NC; ++c) Rs[c] = __fmaf_rn(s[c] * s[c], ninv[c], Rs[c]);
         bar();
         float hv[NC];
-        env_part(I0{}, I1{});
+        if constexpr (!S::PAIRS_X || M == 1) env_part(I0{}, I1{});
         act(acc, hb[0], hv);
-        V4 h = operand(hv);      // this wavefront's 64 units, as an operand
-        mix(I0{}, I1{});
+        V4 h;                    // this wavefront's 64 units, as an operand
+        if constexpr (S::PAIRS_H) put_units<NC, S::PH>(lds + S::OFF_H + 2 * (64 * w + pplace), hv);
+        else h = operand(hv);
+        if constexpr (S::PAIRS_X && M > 1) { bar(); env_part(I0{}, I1{}); env_done(); bar(); }      // (while the writes are under way)
+        else mix(I0{}, I1{});
         // ---- further hidden layers ----
         static_for<0, M - 1>([&](auto lc) {
           constexpr int l = decltype(lc)::value;
-          V4 hf[NW];
+          constexpr int RING = S::PAIRS_H && S::TIGHT ? 2 : NW;
+          std::conditional_t<S::PAIRS_H, u32x4, V4> hf[RING];
+          f32x4 acch[S::PAIRS_H ? 4 : 2];
+          if constexpr (S::PAIRS_H) pair_zero<NC>(acch);
+          else acch[0] = acch[1] = zero4;
           if constexpr (NW > 1) {
             unsigned char* hbuf = lds + S::OFF_H + (l & 1) * S::HB;
-            *reinterpret_cast<V4*>(hbuf + (x * S::PH + 64 * w + 4 * blk) * S::ES) = h;
+            if constexpr (!S::PAIRS_H) *reinterpret_cast<V4*>(hbuf + (x * S::PH + 64 * w + 4 * blk) * S::ES) = h;
             sync();
 #pragma unroll
-            for (int r = 0; r < NW; ++r) hf[r] = *reinterpret_cast<const V4*>(hbuf + (x * S::PH + 64 * r + 4 * blk) * S::ES);
+            for (int r = 0; r < RING; ++r) {
+              if constexpr (S::PAIRS_H) hf[r] = *reinterpret_cast<const u32x4*>(hbuf + (pcopy * S::PH + 64 * r + pat) * S::ES);
+              else hf[r] = *reinterpret_cast<const V4*>(hbuf + (x * S::PH + 64 * r + 4 * blk) * S::ES);
+            }
             bar();
-            if constexpr (l == 0) env_part(I1{}, I2{});
+            if constexpr (l == 0) { env_part(I1{}, I2{}); env_done(); }
             bar();
           } else {
             hf[0] = h;
           }
-          f32x4 acch[2] = {zero4, zero4};
-          static_for<0, HG>([&](auto gc) {
-            constexpr int g = decltype(gc)::value;
-            if (S::OCC == 1 && l < (BF16 ? 2 : 1)) pin_agpr(Wh[l][g]);
-            O::template mac<4, g % 16, g>(hf[g / 16], Wh[l][g], acch);
-          });
+          if constexpr (S::PAIRS_H) {
+            static_for<0, 4 * NW>([&](auto gc) {
+              constexpr int m = decltype(gc)::value / 4, k = decltype(gc)::value % 4;
+              if (S::OCC == 1 && l < 2) pin_agpr(Wh[l][m][k]);
+              acch[k] = pair_mac(hf[m % RING], Wh[l][m][k], acch[k], pwhich);
+              if constexpr (k == 3 && m + RING < NW) {
+                hf[m % RING] = *reinterpret_cast<const u32x4*>(lds + S::OFF_H + (l & 1) * S::HB + (pcopy * S::PH + 64 * (m + RING) + pat) * S::ES);
+                bar();
+              }
+            });
+          } else {
+            static_for<0, HG>([&](auto gc) {
+              constexpr int g = decltype(gc)::value;
+              if (S::OCC == 1 && l < (BF16 ? 2 : 1)) pin_agpr(Wh[l][g]);
+              O::template mac<4, g % 16, g>(hf[g / 16], Wh[l][g], acch);
+            });
+          }
           bar();
-          if constexpr (l == 0) env_part(I2{}, I3{});
+          if constexpr (l == 0 && !S::PAIRS_X) env_part(I2{}, I3{});
           act(acch, hb[l + 1], hv);
-          h = operand(hv);
-          if constexpr (l == 0) mix(I2{}, I3{}); else bar();
+          if constexpr (S::PAIRS_H && l < M - 2) put_units<NC, S::PH>(lds + S::OFF_H + ((l + 1) & 1) * S::HB + 2 * (64 * w + pplace), hv);
+          else h = operand(hv);
+          if constexpr (l == 0 && !S::PAIRS_X) mix(I2{}, I3{}); else bar();
         });
         // ---- action layer: this wavefront's K slice ----
         f32x4 pa, pq[2] = {zero4, zero4};
@@ -608,6 +795,7 @@ void rollout_quad_kernel(const QuadArgs a) {
           } else {
             if ((lane & (NC == 1 ? 15 : 12)) == 0) *reinterpret_cast<f32x4*>(pb + (w * NC + (NC == 1 ? 0 : x)) * S::PP + 4 * (lane >> 4)) = pa;
           }
+          if constexpr (S::PAIRS_X) { bar(); env_part(I2{}, I3{}); env_done(); bar(); }
           sync();
           float pv[S::NP][RPL];
           const float* src = pb + (S::ROWS_COPY ? (x & (NC - 1)) * S::PP + RPL * blk : lane);
@@ -618,6 +806,7 @@ void rollout_quad_kernel(const QuadArgs a) {
           }
           bar();
           env_part(I3{}, I4{});
+          env_done();
           bar();
           constexpr int NV = S::ROWS_COPY ? RPL : 1;
 #pragma unroll
@@ -638,6 +827,11 @@ void rollout_quad_kernel(const QuadArgs a) {
           env_part(I3{}, I4{});
         }
         // ---- the action, its cost, B a ----
+        u32x4 bw[S::B_LDS ? KGA / 2 : 1];
+        if constexpr (S::B_LDS) {
+#pragma unroll
+          for (int g = 0; g < KGA / 2; ++g) bw[g] = bl[g * NT + tid_b];
+        }
         env_part(I4{}, I5{});
         V4 aop;
         if constexpr (S::ROWS_COPY) {
@@ -659,10 +853,18 @@ void rollout_quad_kernel(const QuadArgs a) {
           }
           aop = operand(av);
         }
+        if constexpr (S::PAIRS_X) {
+          float ea[NC];
+          pair_units<NC>(pairE, upper, ea);
+#pragma unroll
+          for (int c = 0; c < NC; ++c) accE[0][c] = ea[c];
+        }
         mix(I4{}, I5{});
         static_for<0, KGA>([&](auto gc) {
           constexpr int g = decltype(gc)::value;
-          O::template mac<4, S::ROWS_COPY ? (RPL == 2 ? 2 * g : 4 * g) : g, g>(aop, Be[g], accE);
+          constexpr int from = S::ROWS_COPY ? (RPL == 2 ? 2 * g : 4 * g) : g;
+          if constexpr (S::B_LDS) O::template mac<4, from, g>(aop, g % 2 ? u32x2{bw[g / 2].z, bw[g / 2].w} : u32x2{bw[g / 2].x, bw[g / 2].y}, accE);
+          else O::template mac<4, from, g>(aop, Be[g], accE);
         });
 #pragma unroll
         for (int c = 0; c < NC; ++c) s[c] = tanh_b<S::NEAR>(accE[0][c] + accE[1][c], 0.0f);       // padded rows: tanh(0) = 0
