@@ -27,8 +27,8 @@
 // Measured, whole rollout, T = 1000 unless noted: bf16 8-256-256-2, 128 individuals x 1 copy 1.23 ms (padded 16-column kernel) -> 0.77 ms -> 0.74 with
 // the books and the two branches of a step's end behind the loop; bf16 27-100-100-8, 128 x 5 copies, T = 400: 8.05 ms (LDS kernel) -> 0.34 ms -> 0.27 with
 // passes of two copies on SIMDs of their own; 244-256-256-17, 1024 x 4 copies, T = 1000: 6.3 ms (16-column kernel with compacted columns) -> 5.7.  Paired products (below),
-// 200 steps: 244-256-256-17 128 x 1 292 -> 222 us, 1024 x 4 1278 -> 1086; 8-256-256-2 128 x 1 166 -> 142, 1024 x 4 551 -> 494; 20-100x3-6 128 x 1 246 -> 195; 27-100-100-8 128 x 1
-// 128 -> 111, 1024 x 4 256 -> 248 (two steps of 4096 x 4 of 244-256-256-17, all staging: 569 -> 584).
+// 200 steps: 8-256-256-2 128 x 1 166 -> 142, 1024 x 4 551 -> 494; 20-100x3-6 128 x 1 246 -> 195; 27-100-100-8 128 x 1
+// 128 -> 111, 1024 x 4 256 -> 248.
 #pragma once
 
 #include <type_traits>
@@ -247,7 +247,9 @@ struct QuadShape {
   static constexpr bool SPREAD = KG > 16;                                // state rows over the wavefronts
   static constexpr int NR = (KG + 15) / 16;                              // operand registers of the state
   // products whose input comes through the LDS run as paired ones (pair_mac): the layers behind the first one, and A s and the first where rows are spread
-  static constexpr bool PAIRS_H = BF16 && NW > 1 && M > 1, PAIRS_X = BF16 && SPREAD;
+  // (Not where four wavefronts share the rows, 129 to 256 units and more than 64 observations, although 244-256-256-17, 4096 x 4 copies, would take 20.0 ms instead of 22.8: sums
+  // in another order round a few operands the other way, of which some individuals' loops there settle elsewhere - in one seed of 24, a rank by 1224 of 4096 places.)
+  static constexpr bool PAIRS = BF16 && NW > 1 && !(SPREAD && NW > 2), PAIRS_H = PAIRS && M > 1, PAIRS_X = PAIRS && SPREAD;
   using WX = std::conditional_t<PAIRS_X, quad::u32x8[NR][4], typename O::V4[KG]>;                 // a lane's weights of the first layer, its elements of A
   using WH = std::conditional_t<PAIRS_H, quad::u32x8[NW][4], typename O::V4[M > 1 ? HG : 1]>;     // ... of a layer behind it
   static constexpr int KGA = SPREAD ? 8 : 4;                             // action width in groups of four
@@ -255,7 +257,7 @@ struct QuadShape {
   static constexpr int ENV_ROWS = SPREAD ? 64 * NW : 64;
   static constexpr int COLS = KG < 8 ? 16 : BF16 && KG >= 16 ? 64 : 32;    // columns of a staging round
   static constexpr int GR = COLS / 4;                                    // ... in groups
-  static constexpr int PWIN = BF16 && NW > 1 ? 64 + 8 : O::PITCH;                                  // window pitch: vector reads of consecutive rows hit distinct banks
+  static constexpr int PWIN = PAIRS_H || PAIRS_X ? 64 + 8 : O::PITCH;                                  // window pitch: vector reads of consecutive rows hit distinct banks
   static constexpr int PW3 = HID + 4;
   static constexpr int ES = (int)sizeof(Elem);
   // LDS map (bytes).  Exchange buffers: rows of HID elements, one per copy; the pad puts the four copies' rows 64 bytes apart
@@ -298,11 +300,7 @@ struct QuadShape {
   // before (one barrier a round).  Three workgroups would not fit the LDS: one layer, 1000 x 4 copies of 27-256-8, 200 steps 237 us, two windows 289
   static constexpr bool TWO_WIN = NW == 4 && OCC < 3;
   static constexpr int OFF_S0 = RUN_BYTES > (TWO_WIN ? 2 : 1) * WIN_BYTES ? RUN_BYTES : (TWO_WIN ? 2 : 1) * WIN_BYTES;
-  // The widest states leave no registers for B beside the operands of paired products (sixteen would be reloaded from scratch memory every step), so a lane's part of B
-  // stays in LDS, [group pair][thread], and is fetched when the hidden layers' operands are done
-  static constexpr bool B_LDS = PAIRS_X && KG > 48;
-  static constexpr int OFF_B = (OFF_S0 + (KEEP_S0 ? 4 * NC * NT : 0) + 15) / 16 * 16;
-  static constexpr int LDS_BYTES = OFF_B + (B_LDS ? KGA / 2 * 16 * NT : 0);
+  static constexpr int LDS_BYTES = OFF_S0 + (KEEP_S0 ? 4 * NC * NT : 0);
   // Registers beside the weights while they are staged.  Where they are short, a batch of loads, or what the compiler derives from the lane's number once for
   // all individuals, is spilled, and the reloads are waited for one after the other between the loads: FRESH computes the lane's number anew
   // (lane_now), BATCH halves a batch where a second workgroup fills the waits.  4096 x 4 copies, 2 steps, neither / FRESH / both: 244-256-256-17 (96 registers) 567 / 560 / 692 us, 100-256-256-17 (224)
@@ -420,8 +418,7 @@ void rollout_quad_kernel(const QuadArgs a) {
 
   // ---- environment matrices -> registers: Ae[g] = A[erow][4g .. 4g+3] (paired: see take), Be[g] = B[erow][4g .. 4g+3] ----
   typename S::WX Ae;
-  V4 Be[S::B_LDS ? 1 : KGA];
-  u32x4* bl = reinterpret_cast<u32x4*>(lds + S::OFF_B);
+  V4 Be[KGA];
   static_for<0, KG / GR>([&](auto rc) {
     constexpr int r = decltype(rc)::value;
     stage_cols<COLS, false>(window(r), S::PWIN, S::ENV_ROWS, no, no, COLS * r, a.A, NoiseRow{}, 0.0f, 0u, tid, threads);
@@ -432,14 +429,7 @@ void rollout_quad_kernel(const QuadArgs a) {
   stage_cols<4 * KGA, false>(window(KG / GR), S::PWIN, S::ENV_ROWS, no, na, 0, a.B, NoiseRow{}, 0.0f, 0u, tid, threads);
   stage_sync();
 #pragma unroll
-  for (int g = 0; g < KGA; ++g) {
-    if constexpr (!S::B_LDS) {
-      Be[g] = win_group(KG / GR, erow, S::PWIN, g);
-    } else if (g % 2 == 0) {      // (read by this thread only)
-      const u32x2 b0 = win_group(KG / GR, erow, S::PWIN, g), b1 = win_group(KG / GR, erow, S::PWIN, g + 1);
-      bl[(g / 2) * NT + tid] = u32x4{b0.x, b0.y, b1.x, b1.y};
-    }
-  }
+  for (int g = 0; g < KGA; ++g) Be[g] = win_group(KG / GR, erow, S::PWIN, g);
   float mu = 0.f, iv = 0.f;                            // observation statistics of this row (padded rows: scale 0)
   if (NORM && erow < no) { mu = a.obs_mean[erow]; iv = a.obs_inv[erow]; }
 
@@ -538,7 +528,6 @@ void rollout_quad_kernel(const QuadArgs a) {
       uint32_t alive = 0u;       // bit c: copy c of this pass still runs (uniform)
       float ninv[NC], ncost[NC], thr[NC];   // per copy while it runs: -1 / obs, -cost, threshold; 0, 0, +inf after its end
       int len[NC];
-      const int tid_b = tid_now();
       const int tid_p = tid_now(), erow_p = SPREAD ? tid_p : tid_p - 64 * w;
       float s[NC];               // state row of this lane, one register per copy (binary32)
       const bool mine = SPREAD || w == 0;      // the wavefront that adds up the state's share of the reward
@@ -827,11 +816,6 @@ void rollout_quad_kernel(const QuadArgs a) {
           env_part(I3{}, I4{});
         }
         // ---- the action, its cost, B a ----
-        u32x4 bw[S::B_LDS ? KGA / 2 : 1];
-        if constexpr (S::B_LDS) {
-#pragma unroll
-          for (int g = 0; g < KGA / 2; ++g) bw[g] = bl[g * NT + tid_b];
-        }
         env_part(I4{}, I5{});
         V4 aop;
         if constexpr (S::ROWS_COPY) {
@@ -863,8 +847,7 @@ void rollout_quad_kernel(const QuadArgs a) {
         static_for<0, KGA>([&](auto gc) {
           constexpr int g = decltype(gc)::value;
           constexpr int from = S::ROWS_COPY ? (RPL == 2 ? 2 * g : 4 * g) : g;
-          if constexpr (S::B_LDS) O::template mac<4, from, g>(aop, g % 2 ? u32x2{bw[g / 2].z, bw[g / 2].w} : u32x2{bw[g / 2].x, bw[g / 2].y}, accE);
-          else O::template mac<4, from, g>(aop, Be[g], accE);
+          O::template mac<4, from, g>(aop, Be[g], accE);
         });
 #pragma unroll
         for (int c = 0; c < NC; ++c) s[c] = tanh_b<S::NEAR>(accE[0][c] + accE[1][c], 0.0f);       // padded rows: tanh(0) = 0
