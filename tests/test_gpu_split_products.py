@@ -1,0 +1,48 @@
+"""Binary32 policies in passes of sixteen copies, whose products run on three-piece values: every way the pairs of a lane are grouped (one, two, three padded to four, four, six
+and eight pairs), both activations, statistics - against the CPU checker, to binary32's own precision over a few steps; and actions beyond the pieces' range."""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import noise_to_device, run_rollout
+from paper_2501_15129_amd.workloads import Workload, make_inputs
+from test_gpu_quad import es  # noqa: F401  (fixture)
+
+pytestmark = pytest.mark.gpu
+
+F = Workload("split", pop=1200, envs=16, horizon=3, obs=17, hid=48, act=5, dtype=0, noise_dtype=0, seed=901)
+
+
+@pytest.mark.parametrize("relu", [0, 1])
+@pytest.mark.parametrize("obs,hid,act", [(3, 16, 2), (16, 17, 9), (17, 48, 8), (20, 33, 16), (32, 64, 5), (33, 16, 3), (48, 60, 16), (64, 32, 12), (64, 48, 4), (48, 64, 16)])
+def test_binary32_precision(es, obs, hid, act, relu):  # noqa: F811
+    """Three steps: each product is good to 2^-24, each sum of up to 64 of them to some 2^-24 of its terms, each tanh to 1.2e-7, so a step moves a reward (1 less means of squares) by
+    1e-7 or so; 2e-6 leaves a factor of ten.  Two pieces of either factor instead of three would be off by 2^-17 = 8e-6 of a product."""
+    w = replace(F, name=f"split-{obs}-{hid}-{act}", obs=obs, hid=hid, act=act, hidden_act=relu, seed=901 + obs + hid)
+    ctx = es.EsContext(w)
+    assert "rollout_mfma_cols_f32" in ctx.rollout_kernel
+    a_mat, b_mat, theta = make_inputs(w)
+    eps = oracle.sample_population(w, 0)
+    ret, _, _ = run_rollout(ctx, w, 0, theta, noise_to_device(ctx, eps), a_mat, b_mat)
+    ref = oracle.rollout(w, 0, theta, eps, a_mat, b_mat, individuals=(590, 610))[0]
+    assert np.abs(ret[590:610] - ref).max() <= 2e-6 * np.abs(ref).max()
+
+
+def test_actions_beyond_the_pieces_range(es):  # noqa: F811
+    """A linear output that overflows (one action, so that no infinities meet): the copy ends where it ends on one wavefront an episode, binary32 throughout, and
+    its return is infinite there as here."""
+    few, many = (replace(F, name="split-overflow", obs=16, hid=32, act=1, out_tanh=0, done_thresh=0.95, horizon=6, pop=n, envs=e) for n, e in ((4, 2), (2000, 16)))
+    a_mat, b_mat, theta = make_inputs(few)
+    o, h, a = few.obs, few.hid, few.act
+    w3 = (o + 1) * h + (h + 1) * h
+    theta[w3:w3 + a * h] = np.float32(2.9e38) * np.sign(theta[w3:w3 + a * h])
+    got = []
+    for w in (few, many):
+        ctx = es.EsContext(w)
+        got.append(run_rollout(ctx, w, 0, theta, noise_to_device(ctx, oracle.sample_population(w, 0)), a_mat, b_mat))
+    assert "cols_f32" in ctx.rollout_kernel
+    assert np.isinf(got[0][0]).any() and (got[0][1] < few.horizon).all()
+    assert np.array_equal(got[0][1], got[1][1][:4, :2])
+    assert np.array_equal(got[0][0], got[1][0][:4, :2])
