@@ -9,8 +9,9 @@
 //   * a lane owns ONE unit of a layer and accumulates it for the four copies in its four result registers: there are no
 //     padded columns (a 16-column tile would be a quarter full) and the activation functions run on full lanes;
 //   * the whole state of four copies, as an operand, is one 8-byte value per lane for every 64 elements;
-//   * after the activation a 4x4 transpose inside each lane quad turns "unit per lane, copy per register" into the next
-//     operand "copy per lane, unit per register".
+//   * after the activation "unit per lane, copy per register" becomes the next operand, "copy per lane, unit per register", by the write to and the read from the LDS where
+//     there are several wavefronts, else (and for the action layer) by a 4x4 transpose inside each lane quad.  (A transpose in front of the LDS as well, with one write of four units:
+//     244-256-256-17, 4096 x 4 copies, 22.8 ms against 22.0; 200-256-256-8 128 x 1, 200 steps, 291 us against 271; binary32 12-100-100-8 256 x 8 298 against 289.)
 // A workgroup of NW wavefronts (64 units of every hidden layer each) evaluates one individual; its perturbed weights and
 // the environment matrices stay in registers for all T steps.
 //   * NW > 1: a hidden layer's outputs cross the LDS as operands (one barrier per layer but the last); the action layer
@@ -182,10 +183,14 @@ __device__ __forceinline__ void pair_units(const f32x4 (&d)[4], bool upper, floa
     }
   }
 }
-// One row (unit) per lane, a register per copy -> rows of an exchange buffer, one per copy: `to` is the lane's place in the first.  (As an operand through a
-// transpose inside the lane quad and one write of four units: 9 to 5 instructions more.)
-template <int NC, int PITCH>
+// One row (unit) per lane, a register per copy -> rows of an exchange buffer, one per copy: `to` is the lane's place in the first.
+template <bool BF16, int NC, int PITCH>
 __device__ __forceinline__ void put_units(unsigned char* to, const float (&v)[NC]) {
+  if constexpr (!BF16) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) *reinterpret_cast<float*>(to + 4 * c * PITCH) = v[c];
+    return;
+  }
 #pragma unroll
   for (int c = 0; c < NC; c += 2) {
     const uint32_t r = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{v[c], v[c + 1 < NC ? c + 1 : c]}, bf16x2));
@@ -557,7 +562,7 @@ void rollout_quad_kernel(const QuadArgs a) {
       for (int c = 0; c < NC; ++c) Rs[c] = 0.0f;
       // a lane's part of paired products' first operand: elements from a row of an exchange buffer
       const int prow = lane & 15, phalf = pair_half<NC>(prow), pcopy = pair_copy<NC>(prow), pat = 16 * (lane >> 4) + 8 * phalf, pwhich = phalf ? (int)0xEEEEEEEEu : 0x44444444;
-      const int pplace = pair_place(lane);
+      const int pplace = pair_place(lane), copy_x = x & (NC - 1);      // (rows past the last copy are nobody's)
       const bool upper = lane >= 32;
       using SOp = std::conditional_t<S::PAIRS_X, u32x4, V4>;
       SOp sop[NR], pop[NORM ? NR : 1];          // the state as an operand: raw for A s, normalised for the policy
@@ -570,32 +575,34 @@ void rollout_quad_kernel(const QuadArgs a) {
       auto publish = [&] {       // s -> operand (own registers, or the exchange buffer)
         if constexpr (S::PAIRS_X) {
           if (NW * 64 == 4 * KG || 64 * w < 4 * KG) {
-            put_units<NC, S::PX>(lds + S::OFF_X + 2 * (64 * w + pplace), s);
+            put_units<BF16, NC, S::PX>(lds + S::OFF_X + 2 * (64 * w + pplace), s);
             if constexpr (NORM) {
               float sn[NC];
 #pragma unroll
               for (int c = 0; c < NC; ++c) sn[c] = (s[c] - mu) * iv;
-              put_units<NC, S::PX>(lds + S::OFF_XP + 2 * (64 * w + pplace), sn);
+              put_units<BF16, NC, S::PX>(lds + S::OFF_XP + 2 * (64 * w + pplace), sn);
             }
           }
           return;
         }
-        const V4 t = operand(s);
-        V4 tn = t;
-        if constexpr (NORM) {
-          float sn[NC];
-#pragma unroll
-          for (int c = 0; c < NC; ++c) sn[c] = (s[c] - mu) * iv;
-          tn = operand(sn);
-        }
         if constexpr (SPREAD) {
-          if (NW * 64 == 4 * KG || 64 * w + 4 * blk < 4 * KG) {
-            *reinterpret_cast<V4*>(lds + S::OFF_X + (x * S::PX + 64 * w + 4 * blk) * S::ES) = t;
-            if (NORM) *reinterpret_cast<V4*>(lds + S::OFF_XP + (x * S::PX + 64 * w + 4 * blk) * S::ES) = tn;
+          if (NW * 64 == 4 * KG || 64 * w < 4 * KG) {      // (KG: 64 rows a wavefront, or none)
+            put_units<BF16, NC, S::PX>(lds + S::OFF_X + (64 * w + lane) * S::ES, s);
+            if constexpr (NORM) {
+              float sn[NC];
+#pragma unroll
+              for (int c = 0; c < NC; ++c) sn[c] = (s[c] - mu) * iv;
+              put_units<BF16, NC, S::PX>(lds + S::OFF_XP + (64 * w + lane) * S::ES, sn);
+            }
           }
-        } else if constexpr (!SPREAD) {
-          sop[0] = t;
-          if (NORM) pop[0] = tn;
+        } else {
+          sop[0] = operand(s);
+          if constexpr (NORM) {
+            float sn[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) sn[c] = (s[c] - mu) * iv;
+            pop[0] = operand(sn);
+          }
         }
       };
       auto fetch_state = [&] {
@@ -608,16 +615,16 @@ void rollout_quad_kernel(const QuadArgs a) {
         } else if constexpr (SPREAD) {
 #pragma unroll
           for (int r = 0; r < NR; ++r) {
-            sop[r] = *reinterpret_cast<const V4*>(lds + S::OFF_X + (x * S::PX + 64 * r + 4 * blk) * S::ES);
-            if (NORM) pop[r] = *reinterpret_cast<const V4*>(lds + S::OFF_XP + (x * S::PX + 64 * r + 4 * blk) * S::ES);
+            sop[r] = *reinterpret_cast<const V4*>(lds + S::OFF_X + (copy_x * S::PX + 64 * r + 4 * blk) * S::ES);
+            if (NORM) pop[r] = *reinterpret_cast<const V4*>(lds + S::OFF_XP + (copy_x * S::PX + 64 * r + 4 * blk) * S::ES);
           }
         }
       };
-      // SPREAD: bits of the copies that rows of wavefront w have ended so far
+      // SPREAD: bits of the copies that rows of any wavefront have ended so far
       uint32_t* flags = reinterpret_cast<uint32_t*>(lds + S::OFF_FLAG);
       publish();
       if constexpr (SPREAD) {
-        if (lane == 0) flags[w] = 0u;
+        if (tid == 0) *flags = 0u;
         sync();
         fetch_state();
       }
@@ -705,7 +712,7 @@ void rollout_quad_kernel(const QuadArgs a) {
         if constexpr (!S::PAIRS_X || M == 1) env_part(I0{}, I1{});
         act(acc, hb[0], hv);
         V4 h;                    // this wavefront's 64 units, as an operand
-        if constexpr (S::PAIRS_H) put_units<NC, S::PH>(lds + S::OFF_H + 2 * (64 * w + pplace), hv);
+        if constexpr (NW > 1 && M > 1) put_units<BF16, NC, S::PH>(lds + S::OFF_H + S::ES * (64 * w + (S::PAIRS_H ? pplace : lane)), hv);
         else h = operand(hv);
         if constexpr (S::PAIRS_X && M > 1) { bar(); env_part(I0{}, I1{}); env_done(); bar(); }      // (while the writes are under way)
         else mix(I0{}, I1{});
@@ -719,12 +726,11 @@ void rollout_quad_kernel(const QuadArgs a) {
           else acch[0] = acch[1] = zero4;
           if constexpr (NW > 1) {
             unsigned char* hbuf = lds + S::OFF_H + (l & 1) * S::HB;
-            if constexpr (!S::PAIRS_H) *reinterpret_cast<V4*>(hbuf + (x * S::PH + 64 * w + 4 * blk) * S::ES) = h;
             sync();
 #pragma unroll
             for (int r = 0; r < RING; ++r) {
               if constexpr (S::PAIRS_H) hf[r] = *reinterpret_cast<const u32x4*>(hbuf + (pcopy * S::PH + 64 * r + pat) * S::ES);
-              else hf[r] = *reinterpret_cast<const V4*>(hbuf + (x * S::PH + 64 * r + 4 * blk) * S::ES);
+              else hf[r] = *reinterpret_cast<const V4*>(hbuf + (copy_x * S::PH + 64 * r + 4 * blk) * S::ES);
             }
             bar();
             if constexpr (l == 0) { env_part(I1{}, I2{}); env_done(); }
@@ -752,7 +758,7 @@ void rollout_quad_kernel(const QuadArgs a) {
           bar();
           if constexpr (l == 0 && !S::PAIRS_X) env_part(I2{}, I3{});
           act(acch, hb[l + 1], hv);
-          if constexpr (S::PAIRS_H && l < M - 2) put_units<NC, S::PH>(lds + S::OFF_H + ((l + 1) & 1) * S::HB + 2 * (64 * w + pplace), hv);
+          if constexpr (NW > 1 && l < M - 2) put_units<BF16, NC, S::PH>(lds + S::OFF_H + ((l + 1) & 1) * S::HB + S::ES * (64 * w + (S::PAIRS_H ? pplace : lane)), hv);
           else h = operand(hv);
           if constexpr (l == 0 && !S::PAIRS_X) mix(I2{}, I3{}); else bar();
         });
@@ -860,17 +866,14 @@ void rollout_quad_kernel(const QuadArgs a) {
             uint32_t f = 0u;
 #pragma unroll
             for (int c = 0; c < NC; ++c) f |= over[c] != 0ull ? 1u << c : 0u;
-            if (lane == 0) flags[w] |= f;
+            if (lane == 0) atomicOr(flags, f);
           }
         }
         publish();
         if constexpr (SPREAD) {
           sync();
           fetch_state();
-          uint32_t f = flags[0];
-#pragma unroll
-          for (int ww = 1; ww < NW; ++ww) f |= flags[ww];
-          seen = uniform(f) & alive;
+          seen = uniform(*flags) & alive;
         }
         ++t;
         asm volatile("s_cmp_eq_u32 %1, %2\n\ts_cselect_b32 %0, 1, 0" : "=s"(stop) : "s"(t), "s"(a.T) : "scc");      // (scalar: the compiler makes masks of it)
