@@ -329,8 +329,10 @@ struct QuadShape {
       constexpr int n = 4 * NR, at[6] = {0, n * 3 / 8, n * 3 / 8, n * 3 / 8, n, n};
       return at[k];
     }
-    if (SPREAD && two) {      // (244-256-256-17: 3 470 cycles a step with the split below, 3 330 with more of it behind the barriers)
-      constexpr int at[6] = {0, KG / 8, KG * 3 / 8, KG / 2, KG * 7 / 8, KG};
+    // (244-256-256-17: 3 470 cycles a step with the split below, 3 330 with more of it behind the barriers.  One copy a pass, 400 steps, 7/8 / 3/4 of it before the action's tanh: 244-256-256-17
+    // 128 x 1 500 / 494 us, 100-256-256-17 405 / 398; four copies, 1024 x 4, 600 steps: 3 320 / 3 390)
+    if (SPREAD && two) {
+      constexpr int at[6] = {0, KG / 8, KG * 3 / 8, KG / 2, NC == 1 ? KG * 3 / 4 : KG * 7 / 8, KG};
       return at[k];
     }
     constexpr int at[6] = {0, KG * 3 / 8, NW > 1 && two ? KG / 2 : KG * 3 / 8, two ? KG * 13 / 16 : (NW > 1 && two ? KG / 2 : KG * 3 / 8), NW > 1 ? KG * 15 / 16 : (two ? KG * 13 / 16 : KG * 3 / 8), KG};
