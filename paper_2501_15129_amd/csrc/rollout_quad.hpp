@@ -676,15 +676,16 @@ void rollout_quad_kernel(const QuadArgs a) {
         };
         // (v: two accumulators of the 4x4 shapes, or the four tiles of paired products)
         auto act = [&](const auto& v, float b, float (&h)[NC]) {
-          float z[NC];
+          auto squash = [&](float z) { return S::RELU ? fmaxf(z + b, 0.f) : tanh_b<S::NEAR>(z, b); };
           if constexpr (sizeof(v) == 4 * sizeof(f32x4)) {
+            float z[NC];
             pair_units<NC>(v, upper, z);
-          } else {
 #pragma unroll
-            for (int c = 0; c < NC; ++c) z[c] = v[0][c] + v[1][c];
+            for (int c = 0; c < NC; ++c) h[c] = squash(z[c]);
+          } else {      // (a copy's sum right in front of its activation: with all four sums first a one-layer step of four copies is 2 to 3 % longer, binary32 34-156-8, 462 x 12, 401 steps 2301 / 2371 us)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) h[c] = squash(v[0][c] + v[1][c]);
           }
-#pragma unroll
-          for (int c = 0; c < NC; ++c) h[c] = S::RELU ? fmaxf(z[c] + b, 0.f) : tanh_b<S::NEAR>(z[c], b);
         };
         using I0 = std::integral_constant<int, 0>; using I1 = std::integral_constant<int, 1>; using I2 = std::integral_constant<int, 2>;
         using I3 = std::integral_constant<int, 3>; using I4 = std::integral_constant<int, 4>; using I5 = std::integral_constant<int, 5>;
