@@ -225,16 +225,6 @@ void rollout_cols_kernel(const QuadArgs a) {
       return src(4 * kk + g);
     }
   };
-  // weights of an output tile: src(k) for the K indices of this lane (SPLIT: src of V values of the contraction)
-  auto weights = [&](auto& W, auto split, auto src) {
-    if constexpr (SPLIT) {
-      decltype(split)::weights(W, [&](int v) { return src(elem(v >> 2, v & 3)); });
-    } else {
-      constexpr int K = (int)(sizeof(W) / sizeof(Op));
-#pragma unroll
-      for (int kk = 0; kk < K; ++kk) W[kk] = operand(kk, src);
-    }
-  };
   auto mma = [](Op w, Op x, f32x4 c) {
     if constexpr (BF16 || SPLIT) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, x, c, 0, 0, 0);
     else return __builtin_amdgcn_mfma_f32_16x16x4f32(w, x, c, 0, 0, 0);
@@ -249,8 +239,17 @@ void rollout_cols_kernel(const QuadArgs a) {
 #pragma unroll
   for (int t = 0; t < OT; ++t) {
     const int el = row_of(t);
-    weights(Ae[t], SX{}, [&](int k) { const bool ok = el < no && k < no; const float v = a.A[ok ? el * no + k : 0]; return ok ? v : 0.0f; });
-    weights(Be[t], SA{}, [&](int k) { const bool ok = el < no && k < na; const float v = a.B[ok ? el * na + k : 0]; return ok ? v : 0.0f; });
+    auto of_A = [&](int k) { const bool ok = el < no && k < no; const float v = a.A[ok ? el * no + k : 0]; return ok ? v : 0.0f; };
+    auto of_B = [&](int k) { const bool ok = el < no && k < na; const float v = a.B[ok ? el * na + k : 0]; return ok ? v : 0.0f; };
+    if constexpr (SPLIT) {
+      SX::weights(Ae[t], [&](int v) { return of_A(elem(v >> 2, v & 3)); });
+      SA::weights(Be[t], [&](int v) { return of_B(elem(v >> 2, v & 3)); });
+    } else {
+#pragma unroll
+      for (int kk = 0; kk < K1; ++kk) Ae[t][kk] = operand(kk, of_A);
+#pragma unroll
+      for (int kk = 0; kk < KA; ++kk) Be[t][kk] = operand(kk, of_B);
+    }
   }
   f32x4 mu[NORM ? OT : 1], iv[NORM ? OT : 1];
   if constexpr (NORM) {
@@ -281,15 +280,30 @@ void rollout_cols_kernel(const QuadArgs a) {
 #pragma unroll
   for (int u = 0; u < HT; ++u) {
     const int unit = row_of(u);
-    weights(W1[u], SX{}, [&](int k) { return pick(unit < nh && k < no, (int)a.oW1 + unit * no + k); });
-    weights(W2[u], SH{}, [&](int k) { return pick(unit < nh && k < nh, (int)a.oW2 + unit * nh + k); });
+    auto of_1 = [&](int k) { return pick(unit < nh && k < no, (int)a.oW1 + unit * no + k); };
+    auto of_2 = [&](int k) { return pick(unit < nh && k < nh, (int)a.oW2 + unit * nh + k); };
+    if constexpr (SPLIT) {
+      SX::weights(W1[u], [&](int v) { return of_1(elem(v >> 2, v & 3)); });
+      SH::weights(W2[u], [&](int v) { return of_2(elem(v >> 2, v & 3)); });
+    } else {
+#pragma unroll
+      for (int kk = 0; kk < K1; ++kk) W1[u][kk] = operand(kk, of_1);
+#pragma unroll
+      for (int kk = 0; kk < KH; ++kk) W2[u][kk] = operand(kk, of_2);
+    }
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       b1[u][r] = pick(elem(u, r) < nh, (int)a.ob1 + elem(u, r));
       b2[u][r] = pick(elem(u, r) < nh, (int)a.ob2 + elem(u, r));
     }
   }
-  weights(W3, SH{}, [&](int k) { return pick(row_of(0) < na && k < nh, (int)a.oW3 + row_of(0) * nh + k); });
+  auto of_3 = [&](int k) { return pick(row_of(0) < na && k < nh, (int)a.oW3 + row_of(0) * nh + k); };
+  if constexpr (SPLIT) {
+    SH::weights(W3, [&](int v) { return of_3(elem(v >> 2, v & 3)); });
+  } else {
+#pragma unroll
+    for (int kk = 0; kk < KH; ++kk) W3[kk] = operand(kk, of_3);
+  }
 #pragma unroll
   for (int r = 0; r < 4; ++r) b3[r] = pick(elem(0, r) < na, (int)a.ob3 + elem(0, r));
 
@@ -311,21 +325,6 @@ void rollout_cols_kernel(const QuadArgs a) {
       } else if constexpr (!SPLIT) {
         x[kk] = v[kk >> 2][kk & 3];
       }
-    }
-  };
-  // acc + an output tile's weights times the inputs
-  auto product = [&](auto& W, auto split, const auto& x, f32x4 acc, auto pinned) {
-    if constexpr (S::OCC == 1 && decltype(pinned)::value) {
-#pragma unroll
-      for (int kk = 0; kk < (int)(sizeof(W) / sizeof(Op)); ++kk) pin(W[kk]);
-    }
-    if constexpr (SPLIT) {
-      quad::static_for<0, decltype(split)::MF>([&](auto kc) { acc = decltype(split)::template step<decltype(kc)::value>(W, x, acc, mma); });
-      return acc;
-    } else {
-#pragma unroll
-      for (int kk = 0; kk < (int)(sizeof(W) / sizeof(Op)); ++kk) acc = mma(W[kk], x[kk], acc);
-      return acc;
     }
   };
   auto squash = [](f32x4 v) { return f32x4{tanh_fast(v.x), tanh_fast(v.y), tanh_fast(v.z), tanh_fast(v.w)}; };
@@ -360,20 +359,6 @@ void rollout_cols_kernel(const QuadArgs a) {
     while (true) {
       Op x[K1], xe[K1], h[KH], ax[KA];
       f32x4 acc[HT], accE[OT], v[HT], av;
-      auto state_term = [&] {      // the reward's state term, from the pre-step state
-        float ss = 0.0f;
-#pragma unroll
-        for (int q = 0; q < OT; ++q)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) ss = q + r == 0 ? s[0][0] * s[0][0] : __fmaf_rn(s[q][r], s[q][r], ss);
-        R = __fmaf_rn(ss, ninv, R);
-      };
-      auto normalised = [&] {
-        f32x4 sn[OT];
-#pragma unroll
-        for (int q = 0; q < OT; ++q) sn[q] = (s[q] - mu[NORM ? q : 0]) * iv[NORM ? q : 0];
-        supply(x, SX{}, sn);
-      };
       if constexpr (SPLIT) {
         // The vector work of one tile beside the products of the next, by hand: left to itself the compiler issues one after the other.  products(k), k < M, over the
         // stages of the vector work, stage(i), i < V, before each its share
@@ -420,8 +405,14 @@ void rollout_cols_kernel(const QuadArgs a) {
             }
           }
         };
-        if constexpr (NORM) normalised();
-        else supply(xe, SX{}, s);
+        if constexpr (NORM) {
+          f32x4 sn[OT];
+#pragma unroll
+          for (int q = 0; q < OT; ++q) sn[q] = (s[q] - mu[q]) * iv[q];
+          supply(x, SX{}, sn);
+        } else {
+          supply(xe, SX{}, s);
+        }
         __builtin_amdgcn_sched_barrier(0);
         quad::static_for<0, HT>([&](auto uc) {
           constexpr int u = decltype(uc)::value;
@@ -434,7 +425,13 @@ void rollout_cols_kernel(const QuadArgs a) {
           if constexpr (u == 0) {
             quad::static_for<0, M1>(products);
             if constexpr (NORM) supply(xe, SX{}, s);
-            state_term();
+            // the reward's state term, from the pre-step state
+            float ss = 0.0f;
+#pragma unroll
+            for (int q = 0; q < OT; ++q)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) ss = q + r == 0 ? s[0][0] * s[0][0] : __fmaf_rn(s[q][r], s[q][r], ss);
+            R = __fmaf_rn(ss, ninv, R);
             __builtin_amdgcn_sched_barrier(0);
           } else {
             weave(std::integral_constant<int, M1>{}, products, std::integral_constant<int, TILE>{}, [&](auto ic) { tile_stage(std::integral_constant<int, u - 1>{}, ic); });
@@ -510,26 +507,54 @@ void rollout_cols_kernel(const QuadArgs a) {
         SA::inputs(ax, cuts);
       } else {
         supply(xe, SX{}, s);
-        if constexpr (NORM) normalised();
+        if constexpr (NORM) {
+          f32x4 sn[OT];
+#pragma unroll
+          for (int q = 0; q < OT; ++q) sn[q] = (s[q] - mu[q]) * iv[q];
+          supply(x, SX{}, sn);
+        }
         // ---- the hidden layers ----
 #pragma unroll
         for (int u = 0; u < HT; ++u) {
-          if constexpr (NORM) acc[u] = product(W1[u], SX{}, x, b1[u], std::true_type{});
-          else acc[u] = product(W1[u], SX{}, xe, b1[u], std::true_type{});
+          acc[u] = b1[u];
+#pragma unroll
+          for (int kk = 0; kk < K1; ++kk) {
+            if (S::OCC == 1) pin(W1[u][kk]);
+            acc[u] = mma(W1[u][kk], NORM ? x[kk] : xe[kk], acc[u]);
+          }
         }
-        state_term();
+        // the reward's state term, from the pre-step state
+        float ss = 0.0f;
+#pragma unroll
+        for (int q = 0; q < OT; ++q)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) ss = q + r == 0 ? s[0][0] * s[0][0] : __fmaf_rn(s[q][r], s[q][r], ss);
+        R = __fmaf_rn(ss, ninv, R);
 #pragma unroll
         for (int u = 0; u < HT; ++u) v[u] = hidden(acc[u]);
         supply(h, SH{}, v);
 #pragma unroll
-        for (int u = 0; u < HT; ++u) acc[u] = product(W2[u], SH{}, h, b2[u], std::true_type{});
+        for (int u = 0; u < HT; ++u) {
+          acc[u] = b2[u];
+#pragma unroll
+          for (int kk = 0; kk < KH; ++kk) {
+            if (S::OCC == 1) pin(W2[u][kk]);
+            acc[u] = mma(W2[u][kk], h[kk], acc[u]);
+          }
+        }
 #pragma unroll
         for (int u = 0; u < HT; ++u) v[u] = hidden(acc[u]);
         supply(h, SH{}, v);
         // ---- the action and its cost, under it A s ----
-        av = product(W3, SH{}, h, b3, std::false_type{});
+        av = b3;
 #pragma unroll
-        for (int q = 0; q < OT; ++q) accE[q] = product(Ae[q], SX{}, xe, zero4, std::false_type{});
+        for (int kk = 0; kk < KH; ++kk) av = mma(W3[kk], h[kk], av);
+#pragma unroll
+        for (int q = 0; q < OT; ++q) {
+          accE[q] = zero4;
+#pragma unroll
+          for (int kk = 0; kk < K1; ++kk) accE[q] = mma(Ae[q][kk], xe[kk], accE[q]);
+        }
         const f32x4 ta = squash(av);
 #pragma unroll
         for (int r = 0; r < S::NAK; ++r) av[r] = squash_l ? ta[r] : av[r];
@@ -546,7 +571,12 @@ void rollout_cols_kernel(const QuadArgs a) {
       float top = 0.0f;
 #pragma unroll
       for (int q = 0; q < OT; ++q) {
-        accE[q] = product(Be[q], SA{}, ax, accE[q], std::false_type{});
+        if constexpr (SPLIT) {
+          quad::static_for<0, SA::MF>([&](auto kc) { accE[q] = SA::template step<decltype(kc)::value>(Be[q], ax, accE[q], mma); });
+        } else {
+#pragma unroll
+          for (int kk = 0; kk < KA; ++kk) accE[q] = mma(Be[q][kk], ax[kk], accE[q]);
+        }
       }
 #pragma unroll
       for (int q = 0; q < OT; ++q) {
