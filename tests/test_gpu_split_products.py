@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 import oracle
-from gpu_util import noise_to_device, run_rollout
+from gpu_util import dev, noise_to_device, run_rollout
 from paper_2501_15129_amd.workloads import Workload, make_inputs
 from test_gpu_quad import es  # noqa: F401  (fixture)
 
@@ -46,3 +46,48 @@ def test_actions_beyond_the_pieces_range(es):  # noqa: F811
     assert np.isinf(got[0][0]).any() and (got[0][1] < few.horizon).all()
     assert np.array_equal(got[0][1], got[1][1][:4, :2])
     assert np.array_equal(got[0][0], got[1][0][:4, :2])
+
+
+def _infinite_weight(w, theta):
+    theta[0] = np.inf
+
+
+def _not_a_number(w, theta):
+    theta[w.obs * w.hid] = np.nan      # b1[0]
+
+
+def _overflowing_products(w, theta):
+    """Units that overflow by one product, whose pieces' products are infinities of both signs."""
+    o, h, a = w.obs, w.hid, w.act
+    w2, w3 = (o + 1) * h, (o + 1) * h + (h + 1) * h
+    theta[:o * h] *= np.float32(1e20)
+    theta[w2:w2 + h * h] = (np.float32(1e20) * np.eye(h, dtype=np.float32)).ravel()
+    theta[w3:w3 + a * h] = np.abs(theta[w3:w3 + a * h]) + np.float32(0.1)
+
+
+@pytest.mark.parametrize("relu,change,mean,inv,finite", [
+    (0, None, 1e9, 1e-9, True), (1, None, -3e8, 1e-8, True), (1, None, 0.0, 1e14, True), (0, None, 0.0, 3e30, True), (0, None, 0.0, np.inf, False), (1, None, np.nan, 1.0, True),
+    (1, _infinite_weight, None, None, False), (1, _overflowing_products, None, None, True), (0, _not_a_number, None, None, False)],
+    ids=lambda v: v.__name__.strip("_") if callable(v) else str(v))
+def test_values_beyond_the_pieces_range(es, relu, change, mean, inv, finite):  # noqa: F811
+    """Statistics and parameters that three bf16 pieces do not carry: the individual runs on the binary32 shape, and its returns are the CPU checker's, infinities and NaN
+    included.  (Widths without padding, where an infinity would meet a zero.)"""
+    w = replace(F, name="split-range", obs=16, hid=32, act=16, hidden_act=relu, horizon=4, pop=2000)
+    a_mat, b_mat, theta = make_inputs(w)
+    if change:
+        change(w, theta)
+    ctx = es.EsContext(w)
+    assert "cols_f32" in ctx.rollout_kernel
+    stats = None if mean is None else tuple(np.full(w.obs, v, np.float32) for v in (mean, inv))
+    if stats:
+        held = tuple(dev(v) for v in stats)
+        ctx.set_obs_norm(*held)
+    eps = oracle.sample_population(w, 0)
+    ret, length, _ = run_rollout(ctx, w, 0, theta, noise_to_device(ctx, eps), a_mat, b_mat)
+    want, ref_len, _, _ = oracle.rollout(w, 0, theta, eps, a_mat, b_mat, individuals=(0, 6), obs_norm=stats)
+    have = ret[:6]
+    assert np.array_equal(length[:6], ref_len)
+    assert np.isfinite(want).all() == finite
+    assert np.array_equal(np.isnan(want), np.isnan(have)) and np.array_equal(np.isinf(want), np.isinf(have))
+    ok = np.isfinite(want)
+    assert np.all(np.abs(want - have)[ok] <= 2e-6 * np.abs(want[ok]))      # (test_binary32_precision)
