@@ -142,7 +142,8 @@ size_t es_noise_rows(const es_ctx* ctx);       /* N/2 (mirrored) or N           
 size_t es_noise_ld(const es_ctx* ctx);         /* row stride of the noise matrix, in elements */
 size_t es_noise_bytes(const es_ctx* ctx);      /* rows * ld * sizeof(element)                 */
 size_t es_workspace_bytes(const es_ctx* ctx);  /* scratch for es_rollout / es_update (>= 256) */
-const char* es_rollout_kernel(const es_ctx* ctx); /* name of the rollout kernel chosen: its family and width classes (the matrix-core
+const char* es_rollout_kernel(const es_ctx* ctx); /* name of the rollout kernel chosen, with or without observation statistics as they are
+                                                   * set now (valid until es_destroy): its family and width classes (the matrix-core
                                                    * families take up to four copies a pass where "quad", sixteen otherwise) */
 const char* es_update_kernel(const es_ctx* ctx);  /* name of the es_update kernel(s) chosen        */
 const char* es_strerror(int status);

@@ -167,6 +167,7 @@ class EsContext:
         self._obs_norm = (mean, inv_std)
         self._check(_lib.es_set_obs_norm(self._h, _ptr(mean, torch.float32, n, "mean"),
                                          _ptr(inv_std, torch.float32, n, "inv_std")))
+        self.rollout_kernel = _lib.es_rollout_kernel(self._h).decode()      # (it may be another one)
 
     # -- the four hot calls ---------------------------------------------------------
     def sample_population(self, generation: int, noise):

@@ -53,6 +53,25 @@ static int static_scratch(es_ctx* ctx, void** out) {
   return ES_OK;
 }
 
+static RolloutChoice choose_rollout(const es_ctx* ctx, bool norm) {
+  const es_config& c = ctx->cfg;
+  const uint32_t m = c.num_hidden;
+  const int cus = ctx->num_cus;
+  if (quad_fits(c, ctx->shp.E, cus, norm)) {
+    const RolloutKind kind = quad_kind(c, ctx->shp.E, cus, norm);
+    return {kind, quad_variant_name(c, kind)};
+  }
+  if (ctx->reg_variant >= 0) {
+    if (reg_team(c, ctx->shp.E, cus)) return {ROLLOUT_WAVE_TEAM, team_variant_name(c)};
+    return {ROLLOUT_WAVE_REG, reg_variant_name(ctx->reg_variant, c.dtype == 1, m)};
+  }
+  if (mfma_f32_fits(c)) return {ROLLOUT_MFMA_F32, mfma_f32_variant_name(c)};
+  if (quad_spread_pays(c, ctx->mfma_variant, ctx->shp.E, cus)) return {ROLLOUT_QUAD_SPREAD, quad_variant_name(c, ROLLOUT_QUAD_SPREAD)};
+  if (ctx->mfma_variant >= 0)
+    return {ROLLOUT_MFMA_REG, mfma_variant_name(ctx->mfma_variant) + (m != 2 ? ",depth" + std::to_string(m) : std::string()) + (c.env_dtype == 1 ? ",env_f32" : "")};
+  return {ROLLOUT_WAVE_LDS, c.dtype == 1 ? "rollout_wave_lds_bf16" : "rollout_wave_lds_f32"};
+}
+
 }  // namespace es
 
 using namespace es;
@@ -132,28 +151,8 @@ int es_create(const es_config* cfg, es_ctx** out) {
   ctx->lds_bytes_wave = wave_rollout_lds_bytes(c);
   ctx->mfma_variant = mfma_variant_for(c);
   ctx->reg_variant = reg_variant_for(c);
-  if (quad_fits(c, ctx->shp.E, cus)) {
-    ctx->rollout_kind = quad_kind(c, ctx->shp.E, cus);
-    ctx->kernel_name = quad_variant_name(c, ctx->rollout_kind);
-  } else if (ctx->reg_variant >= 0) {
-    const bool team = reg_team(c, ctx->shp.E, cus);
-    ctx->rollout_kind = team ? ROLLOUT_WAVE_TEAM : ROLLOUT_WAVE_REG;
-    ctx->kernel_name = team ? team_variant_name(c) : reg_variant_name(ctx->reg_variant, c.dtype == 1, (uint32_t)m);
-  } else if (mfma_f32_fits(c)) {
-    ctx->rollout_kind = ROLLOUT_MFMA_F32;
-    ctx->kernel_name = mfma_f32_variant_name(c);
-  } else if (quad_spread_pays(c, ctx->mfma_variant, ctx->shp.E, cus)) {
-    ctx->rollout_kind = ROLLOUT_QUAD_SPREAD;
-    ctx->kernel_name = quad_variant_name(c, ctx->rollout_kind);
-  } else if (ctx->mfma_variant >= 0) {
-    ctx->rollout_kind = ROLLOUT_MFMA_REG;
-    ctx->kernel_name = mfma_variant_name(ctx->mfma_variant);
-    if (m != 2) ctx->kernel_name += ",depth" + std::to_string(m);
-    if (c.env_dtype == 1) ctx->kernel_name += ",env_f32";
-  } else {
-    ctx->rollout_kind = ROLLOUT_WAVE_LDS;
-    ctx->kernel_name = c.dtype == 1 ? "rollout_wave_lds_bf16" : "rollout_wave_lds_f32";
-  }
+  ctx->choice[0] = choose_rollout(ctx, false);
+  ctx->choice[1] = choose_rollout(ctx, true);
   if (c.noise_dtype >= 4 && (c.noise_table_len % 8 != 0 || c.noise_table_len < s.ld || c.noise_table_len >= (1ull << 32))) {
     delete ctx;
     return bad("noise_table_len must be a multiple of 8, at least the padded row length, and below 2^32");
@@ -185,7 +184,7 @@ size_t es_noise_bytes(const es_ctx* ctx) {
   return (size_t)ctx->shp.rows * ctx->shp.ld * (nd == 1 ? 2 : 4);
 }
 size_t es_workspace_bytes(const es_ctx* ctx) { return ctx ? ctx->workspace_bytes : 0; }
-const char* es_rollout_kernel(const es_ctx* ctx) { return ctx ? ctx->kernel_name.c_str() : ""; }
+const char* es_rollout_kernel(const es_ctx* ctx) { return ctx ? ctx->rollout().name.c_str() : ""; }
 const char* es_update_kernel(const es_ctx* ctx) {
   if (!ctx) return "";
   if (ctx->cfg.noise_dtype == 2 || ctx->cfg.noise_dtype == 3) return "grad_regen_kernel+adam_kernel";
@@ -231,7 +230,7 @@ static int check_rollout(es_ctx* ctx, uint64_t generation, const float* theta_d,
   if (generation >> 32) return fail(ctx, ES_EINVAL, "es_rollout: generation must be < 2^32");
   if (misaligned16(theta_d) || misaligned16(noise_d) || misaligned16(A_d) || misaligned16(B_d) || misaligned16(workspace_d))
     return fail(ctx, ES_EINVAL, "es_rollout: theta_d, noise_d, A_d, B_d and workspace_d must be 16-byte aligned");
-  if (ctx->rollout_kind == ROLLOUT_WAVE_LDS && ctx->lds_bytes_wave > (size_t)ctx->lds_limit)
+  if (ctx->rollout().kind == ROLLOUT_WAVE_LDS && ctx->lds_bytes_wave > (size_t)ctx->lds_limit)
     return fail(ctx, ES_EUNSUPPORTED, "es_rollout: perturbed parameters of one individual (" +
                                           std::to_string(ctx->lds_bytes_wave) + " B) exceed the LDS of a workgroup (" +
                                           std::to_string(ctx->lds_limit) + " B) and no register-resident kernel is built for this shape");
@@ -271,7 +270,7 @@ static int enqueue_rollout(es_ctx* ctx, uint32_t generation, const float* theta_
                            const float* B_d, float* returns_d, int32_t* ep_len_d, float* fitness_d, void* workspace_d,
                            hipStream_t st) {
   auto launch = [&](auto rollout) { return rollout(ctx, generation, theta_d, noise_d, A_d, B_d, returns_d, ep_len_d, fitness_d, workspace_d, st); };
-  switch (ctx->rollout_kind) {
+  switch (ctx->rollout().kind) {
     case ROLLOUT_WAVE_REG: case ROLLOUT_WAVE_TEAM: return launch(launch_rollout_reg);
     case ROLLOUT_MFMA_F32: return launch(launch_rollout_mfma_f32);
     case ROLLOUT_QUAD: case ROLLOUT_QUAD_SPREAD: case ROLLOUT_COLS: case ROLLOUT_SINGLE: return launch(launch_rollout_quad);
@@ -339,7 +338,7 @@ int es_generation(es_ctx* ctx, uint64_t generation, uint64_t adam_step, void* no
   const uint32_t gen = (uint32_t)generation;
   if (int rc = enqueue_sample(ctx, gen, noise_d, st)) return rc;
   if (update_ranks(ctx)) {      // a small population: fitness, ranks and update by one launch
-    const bool left = ctx->rollout_kind != ROLLOUT_MFMA_REG && ctx->rollout_kind != ROLLOUT_MFMA_F32 && ctx->rollout_kind != ROLLOUT_QUAD_SPREAD;
+    const bool left = ctx->rollout().kind != ROLLOUT_MFMA_REG && ctx->rollout().kind != ROLLOUT_MFMA_F32 && ctx->rollout().kind != ROLLOUT_QUAD_SPREAD;
     if (int rc = enqueue_rollout(ctx, gen, theta_d, noise_d, A_d, B_d, returns_d, ep_len_d, left ? nullptr : fitness_d, workspace_d, st)) return rc;
     return launch_rank_update(ctx, adam_step, noise_d, left ? returns_d : nullptr, fitness_d, rank_d, shaped_d, theta_d, m_d, v_d, grad_d, st);
   }

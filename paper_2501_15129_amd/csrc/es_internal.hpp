@@ -31,12 +31,19 @@ struct Shape {
   uint32_t oW1, ob1, oW2, ob2, oW3, ob3;
 };
 
+// Which rollout kernel runs, and its name
+struct RolloutChoice {
+  RolloutKind kind;
+  std::string name;
+};
+
 }  // namespace es
 
 struct es_ctx {
   es_config cfg;
   es::Shape shp;
-  es::RolloutKind rollout_kind;
+  es::RolloutChoice choice[2];   // without and with observation statistics, both settled by es_create
+  const es::RolloutChoice& rollout() const { return choice[obs_mean ? 1 : 0]; }
   int mfma_variant;          // index of the instantiated register-resident kernel, or -1
   int reg_variant;           // index of the register-resident binary32 kernel, or -1
   size_t lds_bytes_wave;     // dynamic LDS of the wave/LDS rollout
@@ -48,7 +55,6 @@ struct es_ctx {
   size_t workspace_bytes;
   int lds_limit;             // LDS bytes per workgroup on the device seen at es_create
   int num_cus;               // compute units of that device
-  std::string kernel_name;
   std::string last_error;
 };
 
@@ -109,8 +115,8 @@ int launch_rollout_quad(es_ctx* ctx, uint32_t gen, const float* theta, const voi
                         const float* A, const float* B, float* returns, int32_t* ep_len,
                         float* fitness, void* ws, hipStream_t st);
 // copies = episodes evaluated per individual
-bool quad_fits(const es_config& cfg, uint32_t copies, int cus);
-RolloutKind quad_kind(const es_config& cfg, uint64_t copies, int cus);      // of a shape that quad_fits takes: ROLLOUT_QUAD, _COLS or _SINGLE
+bool quad_fits(const es_config& cfg, uint32_t copies, int cus, bool norm);      // norm: with observation statistics
+RolloutKind quad_kind(const es_config& cfg, uint64_t copies, int cus, bool norm);      // of a shape that quad_fits takes: ROLLOUT_QUAD, _COLS or _SINGLE
 bool quad_spread_pays(const es_config& cfg, int mfma_variant, uint64_t copies, int cus);   // ROLLOUT_QUAD_SPREAD instead of ROLLOUT_MFMA_REG
 std::string quad_variant_name(const es_config& cfg, RolloutKind kind);
 bool mfma_f32_fits(const es_config& cfg);

@@ -5,7 +5,7 @@
 namespace es {
 
 int launch_quad_narrow(es_ctx* ctx, const QuadArgs& a, float* fitness, hipStream_t st) {
-  if (ctx->rollout_kind == ROLLOUT_COLS) {
+  if (ctx->rollout().kind == ROLLOUT_COLS) {
     if (ctx->cfg.dtype == 1) return launch_cols_bf16(ctx, a, fitness, st);
     if (a.nh <= 32) return launch_cols_f32_small(ctx, a, fitness, st);
     return a.nh <= 48 ? launch_cols_f32_48(ctx, a, fitness, st) : launch_cols_f32_64(ctx, a, fitness, st);

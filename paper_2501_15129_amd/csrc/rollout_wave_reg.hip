@@ -88,7 +88,7 @@ int launch_rollout_reg(es_ctx* ctx, uint32_t gen, const float* theta, const void
   if (v < 0 || s.no > 64 || s.nh > 64 || s.na > 16 || s.m > 4)
     return fail(ctx, ES_EUNSUPPORTED, "es_rollout: no register-resident binary32 variant for this shape");
   int rc = ES_OK;
-  if (ctx->rollout_kind == ROLLOUT_WAVE_TEAM) {
+  if (ctx->rollout().kind == ROLLOUT_WAVE_TEAM) {
     rc = c.dtype == 1 ? launch_team_bf16(ctx, grid, whole, st, a) : launch_team_f32(ctx, mode, grid, whole, st, a);
     if (rc != ES_OK) return rc;
   } else if (v == 0) launch_fixed<3, 2, 3>(mode, grid, lds, st, a);

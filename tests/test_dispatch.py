@@ -98,3 +98,19 @@ def test_rows_of_the_update_are_split_where_it_pays(kw, split):
     from paper_2501_15129_amd.binding import EsContext
     ctx = EsContext(replace(replace(F32, obs=17, hid=64, act=6), **kw))
     assert ctx.update_kernel == ("grad_partial_kernel+adam_kernel" if split else "update_single_pass_kernel")
+
+
+@pytest.mark.parametrize("kw,without,with_stats", [
+    (dict(obs=45, hid=52, act=4, pop=614, envs=5), "mfma_cols_f32<obs48,hid64,act8>", "wave_reg_f32<obs<=64,hid<=64,act<=4>"),
+    (dict(obs=63, hid=48, act=4, pop=1064, envs=5), "mfma_cols_f32<obs64,hid48,act8>", "wave_reg_f32<obs<=64,hid<=64,act<=4>"),
+    (dict(obs=38, hid=56, act=12, pop=578, envs=10), "mfma_cols_f32<obs48,hid64,act16>", "mfma_cols_f32<obs48,hid64,act16>"),
+    (dict(obs=48, hid=48, act=4, pop=614, envs=5), "mfma_cols_f32<obs48,hid48,act8>", "mfma_cols_f32<obs48,hid48,act8>")], ids=str)
+def test_statistics_have_a_choice_of_their_own(kw, without, with_stats):
+    """Where the three-piece products do not fit beside statistics, sixteen columns are counted as what runs there then, the binary32 shape; back without statistics the first choice holds again."""
+    from paper_2501_15129_amd.binding import EsContext, _lib
+    ctx = EsContext(replace(F32, **kw))
+    name = lambda: _lib.es_rollout_kernel(ctx._h).decode().replace("rollout_", "")      # noqa: E731
+    assert name() == without
+    for ptr, expected in ((1 << 20, with_stats), (None, without)):      # (the call is host-side: the pointers are not followed)
+        assert _lib.es_set_obs_norm(ctx._h, ptr, ptr) == 0
+        assert name() == expected
