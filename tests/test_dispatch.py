@@ -114,3 +114,11 @@ def test_statistics_have_a_choice_of_their_own(kw, without, with_stats):
     for ptr, expected in ((1 << 20, with_stats), (None, without)):      # (the call is host-side: the pointers are not followed)
         assert _lib.es_set_obs_norm(ctx._h, ptr, ptr) == 0
         assert name() == expected
+
+
+@pytest.mark.parametrize("kw,name", [
+    (dict(obs=26, hid=19, act=5, pop=1456, envs=4), "wave_reg_f32<obs<=32,hid<=32,act<=8>"), (dict(obs=24, hid=8, act=16, pop=1922, envs=2), "wave_reg_f32<obs<=32,hid<=16,act<=16>"),
+    (dict(obs=26, hid=19, act=5, pop=1456, envs=8), "mfma_cols_f32<obs32,hid32,act8>"), (dict(obs=26, hid=19, act=5, pop=1456, envs=4, hidden_act=1), "mfma_cols_f32<obs32,hid32,act8>")], ids=str)
+def test_several_column_wavefronts_on_a_simd(kernel, kw, name):
+    """Two or three wavefronts of sixteen copies on a SIMD take 0.88 (tanh) of two or three times one's time: a few copies each stay in one wavefront an episode."""
+    assert kernel(replace(F32, **kw)) == "rollout_" + name
