@@ -215,6 +215,14 @@ void rollout_cols_kernel(const QuadArgs a) {
 
 template <class S>
 int launch_cols_shape(es_ctx* ctx, QuadArgs a, float* fitness, hipStream_t st) {
+  // The smallest class, up to 16 observations and units, has some fifteen products a step, few for what the cuts cost: with four wavefronts on a compute unit the binary32 shape is as fast or faster where two of
+  // statistics, more than eight actions and tanh add to the vector work; with fewer the pieces are, and with more, since there vector and matrix instructions of two wavefronts overlap.  300 steps,
+  // pieces / 16x16x4: 16-13-9 700 x 16 177 / 189 us, 800 193 / 189, 1024 197 / 189, 1100 283 / 332; 10-16-4 with statistics 700 x 16 169 / 173, 800 184 / 174, 1024 186 / 174, 1100 282 / 302
+  // (without: 161 / 170, 164 / 170, 166 / 170, 258 / 295); 16-13-9 with statistics and ReLU 800 174 / 170.
+  if constexpr (S::SPLIT && S::KS == 4 && S::HT == 1 && S::NORM + (S::NAK == 4) + !S::RELU >= 2) {
+    const uint64_t wavefronts = (uint64_t)a.N * ((a.E + 15u) / 16u), cus = (uint64_t)std::max(1, ctx->num_cus);
+    if (wavefronts > 3 * cus && wavefronts <= 4 * cus) return launch_cols_shape<typename S::Plain>(ctx, a, fitness, st);
+  }
   const size_t lds = cols::param_bytes<std::conditional_t<S::BF16, uint16_t, float>>(a.ob3 + a.na) + 64u * sizeof(float);      // at most 38 KB
   const uint32_t npass = (a.E + 15u) / 16u, per_cu = (uint32_t)std::max<size_t>(1, std::min<size_t>(4 * S::OCC, (size_t)ctx->lds_limit / lds));
   a.split = quad_split(a.N, npass, (uint32_t)std::max(1, ctx->num_cus) * per_cu);

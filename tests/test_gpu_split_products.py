@@ -4,6 +4,7 @@ from dataclasses import replace
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from gpu_util import dev, noise_to_device, run_rollout
@@ -15,19 +16,37 @@ pytestmark = pytest.mark.gpu
 F = Workload("split", pop=1200, envs=16, horizon=3, obs=17, hid=48, act=5, dtype=0, noise_dtype=0, seed=901)
 
 
+def _precise(es, w, norm):
+    ctx = es.EsContext(w)
+    stats = None
+    if norm:
+        rng = np.random.default_rng(w.seed)
+        stats = (rng.standard_normal(w.obs) * 0.05).astype(np.float32), (1.0 / (0.33 + rng.random(w.obs) * 0.67)).astype(np.float32)
+        held = tuple(dev(v) for v in stats)
+        ctx.set_obs_norm(*held)
+    assert "rollout_mfma_cols_f32" in ctx.rollout_kernel
+    a_mat, b_mat, theta = make_inputs(w)
+    eps = oracle.sample_population(w, 0)
+    ret, _, _ = run_rollout(ctx, w, 0, theta, noise_to_device(ctx, eps), a_mat, b_mat)
+    few = (590, 610)
+    ref = oracle.rollout(w, 0, theta, eps, a_mat, b_mat, individuals=few, obs_norm=stats)[0]
+    assert np.abs(ret[slice(*few)] - ref).max() <= 2e-6 * np.abs(ref).max()
+
+
 @pytest.mark.parametrize("relu", [0, 1])
 @pytest.mark.parametrize("obs,hid,act", [(3, 16, 2), (16, 17, 9), (17, 48, 8), (20, 33, 16), (32, 64, 5), (33, 16, 3), (48, 60, 16), (64, 32, 12), (64, 48, 4), (48, 64, 16)])
 def test_binary32_precision(es, obs, hid, act, relu):  # noqa: F811
     """Three steps: each product is good to 2^-24, each sum of up to 64 of them to some 2^-24 of its terms, each tanh to 1.2e-7, so a step moves a reward (1 less means of squares) by
     1e-7 or so; 2e-6 leaves a factor of ten.  Two pieces of either factor instead of three would be off by 2^-17 = 8e-6 of a product."""
-    w = replace(F, name=f"split-{obs}-{hid}-{act}", obs=obs, hid=hid, act=act, hidden_act=relu, seed=901 + obs + hid)
-    ctx = es.EsContext(w)
-    assert "rollout_mfma_cols_f32" in ctx.rollout_kernel
-    a_mat, b_mat, theta = make_inputs(w)
-    eps = oracle.sample_population(w, 0)
-    ret, _, _ = run_rollout(ctx, w, 0, theta, noise_to_device(ctx, eps), a_mat, b_mat)
-    ref = oracle.rollout(w, 0, theta, eps, a_mat, b_mat, individuals=(590, 610))[0]
-    assert np.abs(ret[590:610] - ref).max() <= 2e-6 * np.abs(ref).max()
+    _precise(es, replace(F, name=f"split-{obs}-{hid}-{act}", obs=obs, hid=hid, act=act, hidden_act=relu, seed=901 + obs + hid), norm=False)
+
+
+@pytest.mark.parametrize("norm,act", [(True, 4), (False, 16)])
+@pytest.mark.parametrize("wavefronts,extra", [(3, 0), (3, 2), (4, 0), (4, 2)])
+def test_smallest_class_around_a_full_chip(es, wavefronts, extra, norm, act):  # noqa: F811
+    """Up to 16 observations and units: pieces, but for four wavefronts a compute unit (16x16x4) - the same precision on both sides of both lines."""
+    pop = wavefronts * torch.cuda.get_device_properties(0).multi_processor_count + extra
+    _precise(es, replace(F, name=f"split-smallest-{pop}", obs=16, hid=16, act=act, pop=pop, seed=951), norm)
 
 
 def test_actions_beyond_the_pieces_range(es):  # noqa: F811
