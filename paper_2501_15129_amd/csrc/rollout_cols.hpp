@@ -215,11 +215,11 @@ void rollout_cols_kernel(const QuadArgs a) {
 
 template <class S>
 int launch_cols_shape(es_ctx* ctx, QuadArgs a, float* fitness, hipStream_t st) {
-  // The smallest class, up to 16 observations and units, has some fifteen products a step, few for what the cuts cost: with four wavefronts on a compute unit the binary32 shape is as fast or faster where two of
-  // statistics, more than eight actions and tanh add to the vector work; with fewer the pieces are, and with more, since there vector and matrix instructions of two wavefronts overlap.  300 steps,
+  // The smallest class, up to 16 observations and units, has some fifteen products a step, few for what the cuts cost: with four wavefronts on a compute unit the binary32 shape is as fast or faster where
+  // statistics or more than eight actions add to the vector work; with fewer the pieces are, and with more, since there vector and matrix instructions of two wavefronts overlap.  300 steps,
   // pieces / 16x16x4: 16-13-9 700 x 16 177 / 189 us, 800 193 / 189, 1024 197 / 189, 1100 283 / 332; 10-16-4 with statistics 700 x 16 169 / 173, 800 184 / 174, 1024 186 / 174, 1100 282 / 302
-  // (without: 161 / 170, 164 / 170, 166 / 170, 258 / 295); 16-13-9 with statistics and ReLU 800 174 / 170.
-  if constexpr (S::SPLIT && S::KS == 4 && S::HT == 1 && S::NORM + (S::NAK == 4) + !S::RELU >= 2) {
+  // (without: 161 / 170, 164 / 170, 166 / 170, 258 / 295); ReLU, 900 x 16: 16-13-9 160 / 162, with statistics 174 / 170, 10-16-4 with statistics 157 / 154.
+  if constexpr (S::SPLIT && S::KS == 4 && S::HT == 1 && (S::NORM || S::NAK == 4)) {
     const uint64_t wavefronts = (uint64_t)a.N * ((a.E + 15u) / 16u), cus = (uint64_t)std::max(1, ctx->num_cus);
     if (wavefronts > 3 * cus && wavefronts <= 4 * cus) return launch_cols_shape<typename S::Plain>(ctx, a, fitness, st);
   }
