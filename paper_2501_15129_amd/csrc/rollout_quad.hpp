@@ -254,7 +254,9 @@ struct QuadShape {
   // products whose input comes through the LDS run as paired ones (pair_mac): the layers behind the first one, and A s and the first where rows are spread
   // (Not where four wavefronts share the rows, 129 to 256 units and more than 64 observations, although 244-256-256-17, 4096 x 4 copies, would take 20.0 ms instead of 22.8: sums
   // in another order round a few operands the other way, of which some individuals' loops there settle elsewhere - in one seed of 24, a rank by 1224 of 4096 places.)
-  static constexpr bool PAIRS = BF16 && NW > 1 && !(SPREAD && NW > 2), PAIRS_H = PAIRS && M > 1, PAIRS_X = PAIRS && SPREAD;
+  // (Nor for four layers in the class of 64 observations, which statistics take at any width: paired products need their operands beside the weights, seven of which are then reloaded from scratch
+  // memory in every step.  100 steps, 4x4 / paired: 62-256x4-8 128 x 1 207 / 293 us, 1000 x 1 813 / 1140, with statistics 27-256x4-8 128 x 1 217 / 303, 512 x 4 701 / 754.)
+  static constexpr bool PAIRS = BF16 && NW > 1 && !(SPREAD && NW > 2) && !(M == 4 && KG > 8), PAIRS_H = PAIRS && M > 1, PAIRS_X = PAIRS && SPREAD;
   using WX = std::conditional_t<PAIRS_X, quad::u32x8[NR][4], typename O::V4[KG]>;                 // a lane's weights of the first layer, its elements of A
   using WH = std::conditional_t<PAIRS_H, quad::u32x8[NW][4], typename O::V4[M > 1 ? HG : 1]>;     // ... of a layer behind it
   static constexpr int KGA = SPREAD ? 8 : 4;                             // action width in groups of four
