@@ -1,5 +1,6 @@
 """Binary32 policies in passes of sixteen copies, whose products run on three-piece values: every way the pairs of a lane are grouped (one, two, three padded to four, four, six
-and eight pairs), both activations, statistics - against the CPU checker, to binary32's own precision over a few steps; and actions beyond the pieces' range."""
+and eight pairs), both activations - against the CPU checker, to binary32's own precision over a few steps; the populations at which the smallest class changes its form, with
+statistics; and actions, parameters and statistics beyond the pieces' range."""
 from dataclasses import replace
 
 import numpy as np
@@ -14,6 +15,21 @@ from test_gpu_quad import es  # noqa: F401  (fixture)
 pytestmark = pytest.mark.gpu
 
 F = Workload("split", pop=1200, envs=16, horizon=3, obs=17, hid=48, act=5, dtype=0, noise_dtype=0, seed=901)
+
+
+@pytest.mark.parametrize("relu", [0, 1])
+@pytest.mark.parametrize("obs,hid,act", [(3, 16, 2), (16, 17, 9), (17, 48, 8), (20, 33, 16), (32, 64, 5), (33, 16, 3), (48, 60, 16), (64, 32, 12), (64, 48, 4), (48, 64, 16)])
+def test_binary32_precision(es, obs, hid, act, relu):  # noqa: F811
+    """Three steps: each product is good to 2^-24, each sum of up to 64 of them to some 2^-24 of its terms, each tanh to 1.2e-7, so a step moves a reward (1 less means of squares) by
+    1e-7 or so; 2e-6 is some twenty times that.  (A missing piece averages out over the elements and stays within it: those are test_gpu_piece_terms.py.)"""
+    w = replace(F, name=f"split-{obs}-{hid}-{act}", obs=obs, hid=hid, act=act, hidden_act=relu, seed=901 + obs + hid)
+    ctx = es.EsContext(w)
+    assert "rollout_mfma_cols_f32" in ctx.rollout_kernel
+    a_mat, b_mat, theta = make_inputs(w)
+    eps = oracle.sample_population(w, 0)
+    ret, _, _ = run_rollout(ctx, w, 0, theta, noise_to_device(ctx, eps), a_mat, b_mat)
+    ref = oracle.rollout(w, 0, theta, eps, a_mat, b_mat, individuals=(590, 610))[0]
+    assert np.abs(ret[590:610] - ref).max() <= 2e-6 * np.abs(ref).max()
 
 
 def _precise(es, w, norm):
@@ -31,14 +47,6 @@ def _precise(es, w, norm):
     few = (590, 610)
     ref = oracle.rollout(w, 0, theta, eps, a_mat, b_mat, individuals=few, obs_norm=stats)[0]
     assert np.abs(ret[slice(*few)] - ref).max() <= 2e-6 * np.abs(ref).max()
-
-
-@pytest.mark.parametrize("relu", [0, 1])
-@pytest.mark.parametrize("obs,hid,act", [(3, 16, 2), (16, 17, 9), (17, 48, 8), (20, 33, 16), (32, 64, 5), (33, 16, 3), (48, 60, 16), (64, 32, 12), (64, 48, 4), (48, 64, 16)])
-def test_binary32_precision(es, obs, hid, act, relu):  # noqa: F811
-    """Three steps: each product is good to 2^-24, each sum of up to 64 of them to some 2^-24 of its terms, each tanh to 1.2e-7, so a step moves a reward (1 less means of squares) by
-    1e-7 or so; 2e-6 leaves a factor of ten.  Two pieces of either factor instead of three would be off by 2^-17 = 8e-6 of a product."""
-    _precise(es, replace(F, name=f"split-{obs}-{hid}-{act}", obs=obs, hid=hid, act=act, hidden_act=relu, seed=901 + obs + hid), norm=False)
 
 
 @pytest.mark.parametrize("norm,act", [(True, 4), (False, 16)])
