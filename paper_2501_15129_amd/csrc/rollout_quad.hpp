@@ -252,7 +252,7 @@ struct QuadShape {
   static constexpr bool SPREAD = KG > 16;                                // state rows over the wavefronts
   static constexpr int NR = (KG + 15) / 16;                              // operand registers of the state
   // products whose input comes through the LDS run as paired ones (pair_mac): the layers behind the first one, and A s and the first where rows are spread
-  // (Not where four wavefronts share the rows, 129 to 256 units and more than 64 observations, although 244-256-256-17, 4096 x 4 copies, would take 20.0 ms instead of 22.8: sums
+  // (Not where four wavefronts share the rows, 129 to 256 units and more than 64 observations, although 244-256-256-17, 4096 x 4 copies, would take 20.0 ms instead of 22.0: sums
   // in another order round a few operands the other way, of which some individuals' loops there settle elsewhere - in one seed of 24, a rank by 1224 of 4096 places.)
   // (Nor for four layers in the class of 64 observations, which statistics take at any width: paired products need their operands beside the weights, seven of which are then reloaded from scratch
   // memory in every step.  100 steps, 4x4 / paired: 62-256x4-8 128 x 1 207 / 293 us, 1000 x 1 813 / 1140, with statistics 27-256x4-8 128 x 1 217 / 303, 512 x 4 701 / 754.)
@@ -262,6 +262,19 @@ struct QuadShape {
   static constexpr int KGA = SPREAD ? 8 : 4;                             // action width in groups of four
   static constexpr int NA = 4 * KGA;                                     // padded action width
   static constexpr int ENV_ROWS = SPREAD ? 64 * NW : 64;
+  // The two accumulators' sum of a copy stands right in front of its activation: with all four sums first a one-layer step of four copies is 2 to 3 % longer, binary32 34-156-8, 462 x 12, 401 steps
+  // 2301 / 2371 us - but in bf16, in the class of 64 observations, up to 4 % shorter (50-200-5, 256 x 4, 400 steps 235 / 224 us; 25-113-5 with statistics, 300 x 4, 300 steps 185 / 177; 60-100-9,
+  // 300 x 7, 100 steps 87 / 86)
+  static constexpr bool SUMS_FIRST = BF16 && M == 1 && NC == 4 && KG == 16;
+  // One layer: where a step's loop begins in the windows in which instructions are fetched (instructions of four bytes behind a multiple of 64; -1: as it comes).  The loop is short and 1 to 5 % longer at the
+  // wrong place, which code in front of it used to decide.  256 x 4 copies, 400 steps, best / worst of the eight places in 32 bytes, here: binary32 13-113-5 274 / 282, with ReLU 259 / 269; bf16 25-200-5
+  // 202 / 212 and 188 / 198, 25-113-5 198 / 203; 256 x 2 154 / 160 and 150 / 158; 128 x 1 130 / 136; where the eight differ by less or by the activation, and with statistics, it is left alone.
+  static constexpr int loop_at() {
+    if (M != 1 || SPREAD || NORM) return -1;
+    if (!BF16) return NW == 2 && NC == 4 && KG <= 8 ? (KG == 4 ? 2 : 0) : -1;
+    constexpr int two[3][2] = {{6, 2}, {5, 3}, {0, -1}}, four[3][2] = {{-1, -1}, {7, 4}, {2, -1}};      // copies, observations
+    return (NW == 2 ? two : four)[NC / 2][KG / 16];
+  }
   static constexpr int COLS = KG < 8 ? 16 : BF16 && KG >= 16 ? 64 : 32;    // columns of a staging round
   static constexpr int GR = COLS / 4;                                    // ... in groups
   static constexpr int PWIN = PAIRS_H || PAIRS_X ? 64 + 8 : O::PITCH;                                  // window pitch: vector reads of consecutive rows hit distinct banks
@@ -331,7 +344,7 @@ struct QuadShape {
       constexpr int n = 4 * NR, at[6] = {0, n * 3 / 8, n * 3 / 8, n * 3 / 8, n, n};
       return at[k];
     }
-    // (244-256-256-17: 3 470 cycles a step with the split below, 3 330 with more of it behind the barriers.  One copy a pass, 400 steps, 7/8 / 3/4 of it before the action's tanh: 244-256-256-17
+    // (244-256-256-17: 3 470 cycles a step with the split below, 3 330 with more of it behind the barriers, 3 220 since the transposes in front of the LDS are gone.  One copy a pass, 400 steps, 7/8 / 3/4 of it before the action's tanh: 244-256-256-17
     // 128 x 1 500 / 494 us, 100-256-256-17 405 / 398; four copies, 1024 x 4, 600 steps: 3 320 / 3 390)
     if (SPREAD && two) {
       constexpr int at[6] = {0, KG / 8, KG * 3 / 8, KG / 2, NC == 1 ? KG * 3 / 4 : KG * 7 / 8, KG};
@@ -638,6 +651,7 @@ void rollout_quad_kernel(const QuadArgs a) {
       // (the end of a copy, or of the horizon); what follows from it stands behind the loop, which is entered again while copies run.
       uint32_t t = 0u, stop, seen = 0u;      // seen: SPREAD, copies ended by any row so far
       unsigned long long over[NC];
+      if constexpr (S::loop_at() >= 0) asm volatile(".p2align 6\n\t.rept %0\n\ts_nop 0\n\t.endr" ::"i"(S::loop_at() < 0 ? 0 : S::loop_at()));
       while (true) {
       do {
 #pragma unroll
@@ -684,7 +698,13 @@ void rollout_quad_kernel(const QuadArgs a) {
             pair_units<NC>(v, upper, z);
 #pragma unroll
             for (int c = 0; c < NC; ++c) h[c] = squash(z[c]);
-          } else {      // (a copy's sum right in front of its activation: with all four sums first a one-layer step of four copies is 2 to 3 % longer, binary32 34-156-8, 462 x 12, 401 steps 2301 / 2371 us)
+          } else if constexpr (S::SUMS_FIRST) {
+            float z[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) z[c] = v[0][c] + v[1][c];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) h[c] = squash(z[c]);
+          } else {
 #pragma unroll
             for (int c = 0; c < NC; ++c) h[c] = squash(v[0][c] + v[1][c]);
           }
