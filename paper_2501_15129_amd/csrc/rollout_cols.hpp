@@ -11,8 +11,8 @@
 // return; a copy that ends is a bit of a compare mask behind a branch that is not taken.
 // Binary32 runs on the bf16 shape too, values cut into three pieces (Split), wherever the pieces fit the registers (all but the widest classes) and carry the individual's values (P_BITS): binary32 products take 32 cycles
 // for four inputs and share the multipliers with vector instructions, in one wavefront and between two, so that the two add up - 19-48-48-5 (ReLU, statistics),
-// 1000 x 16 copies: 77 products, 2464 of 3300 cycles a step, and 809 of vector issue.  Now 70 products (1120 cycles) beside 331 vector instructions, 2500 cycles:
-// 4.29 ms in passes of four copies -> 1.40 -> 1.04 ms per 1000 steps.  100 steps of 1000 x 16 copies: 10-16-4 70 -> 72 us (4000 x 16: 280 -> 171), 18-32-4 135 -> 112, 30-64-12 292 -> 189,
+// 1000 x 16 copies: 77 products, 2464 of 3300 cycles a step, and 809 of vector issue.  Now 70 products (1120 cycles) beside 325 vector instructions, 2440 cycles:
+// 4.29 ms in passes of four copies -> 1.40 -> 1.02 ms per 1000 steps.  100 steps of 1000 x 16 copies: 10-16-4 60 -> 58 us (4000 x 16: 213 -> 186), 18-32-4 135 -> 112, 30-64-12 292 -> 189,
 // 44-48-4 264 -> 172, 60-48-12 350 -> 217; widest, as before: 60-64-4 419.  Bound: vector issue of a lone wavefront, and products with nothing beside them (state, first and last products of a layer).
 // bf16: the activations (29 cycles per tanh of a register); 17-64-64-6, 1000 x 16 copies x 60 steps: 137 -> 64 us.
 #pragma once
