@@ -264,8 +264,8 @@ struct QuadShape {
   static constexpr int ENV_ROWS = SPREAD ? 64 * NW : 64;
   // The two accumulators' sum of a copy stands right in front of its activation: with all four sums first a one-layer step of four copies is 2 to 3 % longer, binary32 34-156-8, 462 x 12, 401 steps
   // 2301 / 2371 us - but in bf16, in the class of 64 observations, up to 4 % shorter (50-200-5, 256 x 4, 400 steps 235 / 224 us; 25-113-5 with statistics, 300 x 4, 300 steps 185 / 177; 60-100-9,
-  // 300 x 7, 100 steps 87 / 86)
-  static constexpr bool SUMS_FIRST = BF16 && M == 1 && NC == 4 && KG == 16;
+  // 300 x 7, 100 steps 87 / 86; three layers 50-100x3-5 300 x 4, 200 steps 577 / 564)
+  static constexpr bool SUMS_FIRST = BF16 && (M == 1 || M == 3) && NC == 4 && KG == 16;
   // One layer: where a step's loop begins in the windows in which instructions are fetched (instructions of four bytes behind a multiple of 64; -1: as it comes).  The loop is short and 1 to 5 % longer at the
   // wrong place, which code in front of it used to decide.  256 x 4 copies, 400 steps, best / worst of the eight places in 32 bytes, here: binary32 13-113-5 274 / 282, with ReLU 259 / 269; bf16 25-200-5
   // 202 / 212 and 188 / 198, 25-113-5 198 / 203; 256 x 2 154 / 160 and 150 / 158; 128 x 1 130 / 136; where the eight differ by less or by the activation, and with statistics, it is left alone.
